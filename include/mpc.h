@@ -69,8 +69,14 @@ typedef enum {
  *          Each operand's k range (K of a product; each of the two halves of
  *          a Beaver finish, whose summed k is 2K) is at most 2,097,088 long;
  *          longer ones return MPC_E_UNSUPPORTED.
- *   AUTO:  the library's choice (LIMB8 unless the problem is tiny or its k
- *          is longer than LIMB8 takes; then PLAIN).
+ *   AUTO:  the library's choice: PLAIN if the problem is tiny or its k is
+ *          longer than LIMB8 takes; else LIMB8 or, where each operand element
+ *          enters many outputs, a residue form of its own: the product modulo
+ *          18 coprime moduli of at most 256, each an exact INT8 GEMM, put
+ *          together by the Chinese remainder theorem.  Bit-identical to PLAIN;
+ *          it takes a larger workspace (18 bytes a packed element and output,
+ *          where LIMB8 takes 8 a packed element) and gives way to LIMB8 where
+ *          the workspace cannot grow that far.
  *   FP64LIMB: the paper's own GPU method (Section 5.3, off-loading to the
  *          GPU): operands split into four 16-bit limbs (ten pairwise products)
  *          or, when the summed k is below 1024, three 22-bit limbs (six), each
@@ -237,7 +243,9 @@ mpc_status mpc_ring_gemm(mpc_ctx *ctx, int64_t M, int64_t N, int64_t K, const ui
  * launches since the last read, their summed event-measured duration and
  * their algorithmic work (ring multiply-accumulates M*N*K over true, unpadded
  * sizes; the limb form also performs 36 int8 multiply-accumulates per ring
- * one, the fp64 limb form 6 or 10 float64 ones), and clears the record.  In
+ * one, the fp64 limb form 6 or 10 float64 ones), and clears the record.  The
+ * residue form that AUTO may take (18 int8 multiply-accumulates per ring one)
+ * is recorded as the limb form.  In
  * the fp64 limb form the bracket covers its vendor-BLAS GEMM calls (one per
  * limb diagonal) as one launch.  Any output pointer may be NULL. */
 typedef struct {

@@ -9,10 +9,10 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libmpc.so")
 BUILD = os.path.join(ROOT, "_build")
-SOURCES = ["api.cpp", "elementwise.hip", "gemm_plain.hip", "gemm_limb.hip", "gemm_fp64.hip",
+SOURCES = ["api.cpp", "elementwise.hip", "gemm_plain.hip", "gemm_limb.hip", "gemm_residue.hip", "gemm_fp64.hip",
            "multiparty.hip", "binary.hip"]
 ARCH = os.environ.get("MPC_OFFLOAD_ARCH", "gfx950")
-FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
+FLAGS = ["-O3", "-std=c++20", "-fPIC", f"--offload-arch={ARCH}",
          # keep the compiler from forming packed fp32 instructions
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall"]

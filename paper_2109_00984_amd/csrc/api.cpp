@@ -390,22 +390,43 @@ Epilogue make_ep(const u64* cadd, int csign, int trunc, u64* out, OutView v) {
   return e;
 }
 
-// AUTO: the limb form for products of 2^22 ring MACs or more, when it can
-// address their k segments (each kseg long; K is the total).
-mpc_form resolve_form(mpc_form f, i64 M, i64 N, i64 K, i64 kseg) {
+// An mpc_form, or the residue form (gemm_residue.hip), which no caller names.
+using Form = int;
+constexpr Form kFormResidue = 16;
+
+// Whether AUTO takes a product of the limb form to the residue form, which
+// halves the int8 work (18 products against 36) and writes 2.25 times the
+// packed bytes (18 a packed element against 8): it pays where each packed
+// element is used by many outputs and the sums are long.  reuse = M N / (M + N)
+// outputs per operand element; K is the summed k.  Beaver matmuls, limb against
+// residue: 1024 x 1024 x 1024 125 / 153 us, 512 x 2048 x 4096 490 / 490,
+// 1024 x 2048 x 1024 227 / 246, 1024 x 2048 x 2048 453 / 396, 2048 x 2048 x 1024
+// 434 / 411, 2048^3 841 / 692, 4096^3 6540 / 4480.
+bool residue_pays(i64 M, i64 N, i64 K) {
+  const double reuse = (double)M * (double)N / (double)(M + N);
+  return reuse >= 512 && reuse * (double)K >= 2.5e6;
+}
+Form packing_form(i64 M, i64 N, i64 K) { return residue_pays(M, N, K) ? kFormResidue : MPC_FORM_LIMB8; }
+
+// AUTO: a matrix-core form for products of 2^22 ring MACs or more, when the
+// limb form can address their k segments (each kseg long; K is the total).
+Form resolve_form(Form f, i64 M, i64 N, i64 K, i64 kseg) {
   if (f != MPC_FORM_AUTO) return f;
   if (kseg > kLimbMaxSegK) return MPC_FORM_PLAIN;
   const double work = (double)M * (double)N * (double)K;
-  return work >= (double)(1 << 22) ? MPC_FORM_LIMB8 : MPC_FORM_PLAIN;
+  if (work < (double)(1 << 22)) return MPC_FORM_PLAIN;
+  return packing_form(M, N, K);
 }
+bool packs(Form f) { return f == MPC_FORM_LIMB8 || f == kFormResidue; }
 
 // The limb form asked for a k segment longer than it addresses.
-mpc_status check_limb_k(mpc_form f, i64 kseg) {
+mpc_status check_limb_k(Form f, i64 kseg) {
   return f == MPC_FORM_LIMB8 && kseg > kLimbMaxSegK ? MPC_E_UNSUPPORTED : MPC_OK;
 }
 
 // ------------------------------------------------------------------ plain form
-size_t packed_bytes(i64 rows, i64 K) {
+size_t packed_bytes(i64 rows, i64 K, Form form = MPC_FORM_LIMB8) {
+  if (form == kFormResidue) return (size_t)kRes * (size_t)res_rblocks(rows) * (size_t)res_kblocks(K) * kResBlockBytes;
   return (size_t)limb_rblocks(rows) * (size_t)limb_kblocks(K) * kLimbBlockBytes;
 }
 
@@ -631,11 +652,13 @@ struct JobSpec {
   u64* share[2] = {nullptr, nullptr};
 };
 
-size_t job_bytes(const JobSpec& j) { return (size_t)pack_nout(j.mode) * align_up(packed_bytes(j.rows, j.K)); }
+size_t job_bytes(const JobSpec& j, Form form) {
+  return (size_t)pack_nout(j.mode) * align_up(packed_bytes(j.rows, j.K, form));
+}
 
 // Places a job's packed outputs in the workspace carve; with ws_outs >= 0
 // only the first ws_outs of them (the caller points the rest elsewhere).
-PackJob place_job(const JobSpec& j, Carve& cv, int ws_outs = -1) {
+PackJob place_job(const JobSpec& j, Carve& cv, Form form, int ws_outs = -1) {
   PackJob p{};
   p.kind = j.kind;
   p.mode = j.mode;
@@ -652,12 +675,13 @@ PackJob place_job(const JobSpec& j, Carve& cv, int ws_outs = -1) {
     p.key[i] = j.key[i];
     p.share[i] = j.share[i];
   }
-  p.rblocks = limb_rblocks(j.rows);
-  p.rreal = (j.rows + 31) / 32;
-  p.kblocks = limb_kblocks(j.K);
+  const bool res = form == kFormResidue;
+  p.rblocks = res ? res_rblocks(j.rows) : limb_rblocks(j.rows);
+  p.rreal = res ? (j.rows + 15) / 16 : (j.rows + 31) / 32;
+  p.kblocks = res ? res_kblocks(j.K) : limb_kblocks(j.K);
   const int nws = ws_outs < 0 ? pack_nout(j.mode) : ws_outs;
   for (int o = 0; o < kPackMaxOut; ++o)
-    p.dst[o] = o < nws ? cv.take<uint8_t>(packed_bytes(j.rows, j.K)) : nullptr;
+    p.dst[o] = o < nws ? cv.take<uint8_t>(packed_bytes(j.rows, j.K, form)) : nullptr;
   return p;
 }
 
@@ -776,6 +800,67 @@ std::vector<Region> limb_regions(const LimbReq& r, const TileSched& ts) {
   return limb_regions(r.M, r.N, r.cls, ts.variant, r.ep.view.ld_q == 0 && r.ep.view.n_div >= r.N);
 }
 
+// The pack launches of one call: one per (kind, mode), the kernel being
+// specialised on both, each with the prefix sums of its jobs' block counts.
+struct PackLaunches {
+  std::vector<PackJob> jobs;
+  std::vector<std::pair<int, int>> km;
+  std::vector<size_t> first;
+  std::vector<std::vector<i64>> bstarts;
+  std::vector<size_t> obstart;
+  size_t ojobs = 0;
+  explicit PackLaunches(const std::vector<PackJob>& in) {
+    for (int kind : {kPackRow, kPackCol, kPackIm2col})
+      for (int mode : {kModeCopy, kModeSum2, kModeOpenLeft, kModeOpenRight, kModePrgSum2, kModePrgSum2A, kModePrgSum2B,
+                       kModeOpenLeft2, kModeOpenRight1}) {
+        bool any = false;
+        for (const PackJob& j : in) {
+          if (j.kind != kind || j.mode != mode) continue;
+          if (!any) {
+            first.push_back(jobs.size());
+            km.push_back({kind, mode});
+            any = true;
+          }
+          jobs.push_back(j);
+        }
+      }
+    first.push_back(jobs.size());
+    bstarts.resize(km.size());
+    for (size_t L = 0; L < km.size(); ++L) {
+      bstarts[L].assign(1, 0);
+      for (size_t i = first[L]; i < first[L + 1]; ++i) bstarts[L].push_back(bstarts[L].back() + jobs[i].rreal * jobs[i].kblocks);
+    }
+  }
+  // whether every launch's tables fit the kernel arguments
+  bool fits_inline() const {
+    for (size_t L = 0; L < km.size(); ++L)
+      if (first[L + 1] - first[L] > (size_t)kInlineJobs) return false;
+    return true;
+  }
+  void add(Blob& blob) {
+    for (const auto& b : bstarts) obstart.push_back(blob.add(b.data(), b.size()));
+    ojobs = blob.add(jobs.data(), jobs.size());
+  }
+  // dev: the uploaded blob, or null for tables in the kernel arguments
+  mpc_status issue(mpc_ctx* c, const uint8_t* dev, hipError_t (*launch)(hipStream_t, const PackTables&, i64, int, int)) const {
+    for (size_t L = 0; L < km.size(); ++L) {
+      const int n = (int)(first[L + 1] - first[L]);
+      PackTables t{};
+      t.njobs = n;
+      if (!dev) {
+        for (int i = 0; i < n; ++i) t.ijobs[i] = jobs[first[L] + i];
+        for (int i = 0; i <= n; ++i) t.ibstart[i] = bstarts[L][i];
+      } else {
+        t.jobs = (const PackJob*)(dev + ojobs) + first[L];
+        t.block_start = (const i64*)(dev + obstart[L]);
+      }
+      CHK(hip_status(launch(c->s[0], t, bstarts[L].back(), km[L].first, km[L].second)));
+      c->stats.launches++;
+    }
+    return MPC_OK;
+  }
+};
+
 // One pack launch over all jobs, then one GEMM launch per K chunk (a problem
 // whose concatenated K exceeds the int32-safe range continues in the next
 // launch, adding into its output; truncation is applied by its last chunk).
@@ -790,34 +875,8 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
   for (const LimbReq& r : reqs)
     if (r.K0 > kLimbMaxSegK || r.K1 > kLimbMaxSegK) return MPC_E_UNSUPPORTED;
   hipStream_t st = c->s[0];
-  // one pack launch per (kind, mode): the kernel is specialised on both
-  std::vector<PackJob> jobs;
-  std::vector<std::pair<int, int>> launch_km;
-  std::vector<size_t> first_job;
-  for (int kind : {kPackRow, kPackCol, kPackIm2col})
-    for (int mode : {kModeCopy, kModeSum2, kModeOpenLeft, kModeOpenRight, kModePrgSum2, kModePrgSum2A, kModePrgSum2B,
-                     kModeOpenLeft2, kModeOpenRight1}) {
-      bool any = false;
-      for (const PackJob& j : jobs_in) {
-        if (j.kind != kind || j.mode != mode) continue;
-        if (!any) {
-          first_job.push_back(jobs.size());
-          launch_km.push_back({kind, mode});
-          any = true;
-        }
-        jobs.push_back(j);
-      }
-    }
-  first_job.push_back(jobs.size());
-  const size_t nj = jobs.size(), nreq = reqs.size();
-  // per launch: prefix sums of its jobs' block counts
-  std::vector<std::vector<i64>> bstarts(launch_km.size());
-  for (size_t L = 0; L < launch_km.size(); ++L) {
-    std::vector<i64>& bstart = bstarts[L];
-    bstart.assign(1, 0);
-    for (size_t i = first_job[L]; i < first_job[L + 1]; ++i)
-      bstart.push_back(bstart.back() + jobs[i].rreal * jobs[i].kblocks);
-  }
+  PackLaunches pk(jobs_in);
+  const size_t nreq = reqs.size();
 
   // K pieces per request.  The int32 bound needs kbt / kLimbMaxKBlocks chunks,
   // run as consecutive launches that add into the output.  When the whole
@@ -956,22 +1015,18 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
   std::stable_sort(launches.begin(), launches.end(),
                    [](const Launch& a, const Launch& b) { return a.chunk < b.chunk; });
   const size_t nlaunch = launches.size();
-  bool inl = reduces.empty();
-  for (size_t L = 0; L < launch_km.size(); ++L)
-    if (first_job[L + 1] - first_job[L] > (size_t)kInlineJobs) inl = false;
+  bool inl = reduces.empty() && pk.fits_inline();
   for (const Launch& l : launches)
     if (l.pieces.size() > (size_t)kInlineProbs) inl = false;
   // with split-K off, a no-alloc call has one job per operand side and two
   // problems per launch
   if (no_alloc && !inl) return MPC_E_UNSUPPORTED;
   Blob blob;
-  std::vector<size_t> obstart(launch_km.size()), oprob(nlaunch), otile(nlaunch);
-  size_t ojobs = 0;
+  std::vector<size_t> oprob(nlaunch), otile(nlaunch);
   ReduceTable rt{};
   uint8_t* dev = nullptr;
   if (!inl) {
-    for (size_t L = 0; L < launch_km.size(); ++L) obstart[L] = blob.add(bstarts[L].data(), bstarts[L].size());
-    ojobs = blob.add(jobs.data(), nj);
+    pk.add(blob);
     for (size_t L = 0; L < nlaunch; ++L) {
       oprob[L] = blob.add(launches[L].pieces.data(), launches[L].pieces.size());
       otile[L] = blob.add(launches[L].tstarts.data(), launches[L].tstarts.size());
@@ -979,20 +1034,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
     rt = add_reduces(blob, reduces);
     CHK(upload(c, blob, &dev));
   }
-  for (size_t L = 0; L < launch_km.size(); ++L) {
-    const int njl = (int)(first_job[L + 1] - first_job[L]);
-    PackTables t{};
-    t.njobs = njl;
-    if (inl) {
-      for (int i = 0; i < njl; ++i) t.ijobs[i] = jobs[first_job[L] + i];
-      for (int i = 0; i <= njl; ++i) t.ibstart[i] = bstarts[L][i];
-    } else {
-      t.jobs = (const PackJob*)(dev + ojobs) + first_job[L];
-      t.block_start = (const i64*)(dev + obstart[L]);
-    }
-    CHK(hip_status(launch_pack(st, t, bstarts[L].back(), launch_km[L].first, launch_km[L].second)));
-    c->stats.launches++;
-  }
+  CHK(pk.issue(c, dev, launch_pack));
   for (size_t L = 0; L < nlaunch; ++L) {
     const Launch& l = launches[L];
     if (l.pieces.empty()) continue;
@@ -1025,8 +1067,152 @@ LimbReq limb_req(i64 M, i64 N, i64 K0, i64 K1, const uint8_t* PA0, const uint8_t
   return LimbReq{M, N, K0, K1, PA0, PA1, PB0, PB1, ep, false, TileSched{}, 0};
 }
 
+// Residue form: workspace of a product's residues, one plane per modulus and
+// chunk of k.
+size_t res_chunks(i64 K0, i64 K1) {
+  return (size_t)std::max<i64>(1, (res_kblocks(K0) + res_kblocks(K1) + kResMaxKBlocks - 1) / kResMaxKBlocks);
+}
+i64 res_plane(i64 M, i64 N) { return res_rblocks(M) * (res_rblocks(N) / 4) * kResBlockBytes; }
+size_t res_out_bytes(i64 M, i64 N, i64 K0, i64 K1) {
+  return align_up(res_chunks(K0, K1) * (size_t)kRes * (size_t)res_plane(M, N));
+}
+
+// Workgroup tile of a residue launch: the one whose rounds over the compute
+// units take least, a round being a fixed part (first loads, epilogue) and one
+// part per 64-wide k step, both as measured on 4096 x 4096 outputs.
+int res_tile_for(const mpc_ctx* c, const std::vector<LimbReq>& reqs) {
+  static const double fixed_us[kResTiles] = {5.8, 3.9, 3.9, 2.0}, step_us[kResTiles] = {0.71, 0.82, 0.82, 0.48};
+  double best = 0;
+  int pick = kRes128x128;
+  for (int v = 0; v < kResTiles; ++v) {
+    int bm, bn;
+    res_tile_shape(v, &bm, &bn);
+    double steps = 0, tiles = 0;
+    for (const LimbReq& r : reqs) {
+      const double n = (double)kRes * (double)((r.M + bm - 1) / bm) * (double)((r.N + bn - 1) / bn);
+      tiles += n;
+      steps += n * (double)(res_kblocks(r.K0) + res_kblocks(r.K1));
+    }
+    if (tiles == 0) continue;
+    const double cost = std::ceil(tiles / ((double)c->num_cu * res_tile_per_cu(v))) * (fixed_us[v] + step_us[v] * steps / tiles);
+    if (best == 0 || cost < best) {
+      best = cost;
+      pick = v;
+    }
+  }
+  return pick;
+}
+
+// The residue form of issue_limb: the pack launches, one GEMM launch over the
+// tiles of every product, modulus and chunk of k, one combine launch with the
+// products' epilogues.  `cv` provides res_out_bytes per product.
+mpc_status issue_residue(mpc_ctx* c, Carve& cv, const std::vector<PackJob>& jobs, const std::vector<LimbReq>& reqs) {
+  const hipStream_t st = c->s[0];
+  PackLaunches pk(jobs);
+  const int tile = res_tile_for(c, reqs);
+  int bm, bn;
+  res_tile_shape(tile, &bm, &bn);
+  std::vector<ResProblem> probs;
+  std::vector<ResOut> outs;
+  std::vector<int> tstart{0};
+  std::vector<i64> ustart{0};
+  double macs = 0;
+  for (const LimbReq& r : reqs) {
+    // one segment, or two of the same length
+    if (r.K1 && r.K1 != r.K0) return MPC_E_INVAL;
+    const int kb0 = (int)res_kblocks(r.K0), kb1 = (int)res_kblocks(r.K1), nch = (int)res_chunks(r.K0, r.K1);
+    ResOut o{};
+    o.pr = res_plane(r.M, r.N);
+    o.pc = kRes * o.pr;
+    o.nch = nch;
+    o.n64 = (int)(res_rblocks(r.N) / 4);
+    o.M = r.M;
+    o.N = r.N;
+    o.ep = r.ep;
+    uint8_t* R = cv.take<uint8_t>(res_out_bytes(r.M, r.N, r.K0, r.K1));
+    o.R = R;
+    outs.push_back(o);
+    ustart.push_back(ustart.back() + (r.M + 15) / 16 * ((r.N + 63) / 64));
+    for (int ch = 0; ch < nch; ++ch) {
+      ResProblem p{};
+      p.PA0 = r.PA0;
+      p.PA1 = r.PA1 ? r.PA1 : r.PA0;
+      p.PB0 = r.PB0;
+      p.PB1 = r.PB1 ? r.PB1 : r.PB0;
+      p.pa = res_rblocks(r.M) * kb0 * kResBlockBytes;
+      p.pb = res_rblocks(r.N) * kb0 * kResBlockBytes;
+      p.kbs = kb0;
+      // chunks of equal length, to a block
+      p.kb_begin = (int)((i64)(kb0 + kb1) * ch / nch);
+      p.kb_end = (int)((i64)(kb0 + kb1) * (ch + 1) / nch);
+      p.ntm = (int)((r.M + bm - 1) / bm);
+      p.ntn = (int)((r.N + bn - 1) / bn);
+      p.n64 = o.n64;
+      p.R = R + ch * o.pc;
+      p.pr = o.pr;
+      probs.push_back(p);
+      tstart.push_back(tstart.back() + kRes * p.ntm * p.ntn);
+    }
+    macs += (double)r.M * (double)r.N * (double)(r.K0 + r.K1);
+  }
+  // Tiles of one length run in a persistent launch, whose workgroups fetch the
+  // next tile's first steps during their epilogue; of uneven ones the hardware
+  // hands each workgroup one.
+  bool even = true;
+  for (const ResProblem& p : probs) even = even && p.kb_end - p.kb_begin == probs[0].kb_end - probs[0].kb_begin;
+  const int grid = even ? std::min(tstart.back(), res_tile_per_cu(tile) * c->num_cu) : tstart.back();
+  const bool inl = pk.fits_inline() && probs.size() <= (size_t)kResInline && outs.size() <= (size_t)kResInline;
+  ResGemmTables gt{};
+  ResOutTables ot{};
+  gt.nprob = (int)probs.size();
+  ot.nout = (int)outs.size();
+  uint8_t* dev = nullptr;
+  if (inl) {
+    std::copy(probs.begin(), probs.end(), gt.iprobs);
+    std::copy(tstart.begin(), tstart.end(), gt.itile_start);
+    std::copy(outs.begin(), outs.end(), ot.iouts);
+    std::copy(ustart.begin(), ustart.end(), ot.iunit_start);
+  } else {
+    Blob blob;
+    pk.add(blob);
+    const size_t op = blob.add(probs.data(), probs.size()), ots = blob.add(tstart.data(), tstart.size());
+    const size_t oo = blob.add(outs.data(), outs.size()), ous = blob.add(ustart.data(), ustart.size());
+    CHK(upload(c, blob, &dev));
+    gt.probs = (const ResProblem*)(dev + op);
+    gt.tile_start = (const int*)(dev + ots);
+    ot.outs = (const ResOut*)(dev + oo);
+    ot.unit_start = (const i64*)(dev + ous);
+  }
+  CHK(pk.issue(c, dev, launch_res_pack));
+  LaunchTimer tm(c, MPC_FORM_LIMB8, macs);
+  CHK(tm.start());
+  CHK(hip_status(launch_res_gemm(st, gt, tstart.back(), tile, grid)));
+  CHK(tm.stop());
+  CHK(hip_status(launch_res_combine(st, ot, ustart.back())));
+  c->stats.launches += 2;
+  c->stats.gemm_problems += reqs.size();
+  return MPC_OK;
+}
+
+// A packing form's launches: issue_residue or issue_limb.
+mpc_status issue_packed(mpc_ctx* c, Form form, Carve& cv, const std::vector<PackJob>& jobs, const std::vector<LimbReq>& reqs) {
+  return form == kFormResidue ? issue_residue(c, cv, jobs, reqs) : issue_limb(c, jobs, reqs, c->sched_default);
+}
+
+// Workspace for a packing form: `need(form)` bytes.  The residue form's is the
+// larger; where it cannot be had (the workspace may not move under a capture
+// or a live graph, or the memory is not there) the limb form takes its place.
+template <class F>
+mpc_status ensure_packing_ws(mpc_ctx* c, Form* form, F need) {
+  if (*form == kFormResidue) {
+    if (ensure_ws(c, need(kFormResidue)) == MPC_OK) return MPC_OK;
+    *form = MPC_FORM_LIMB8;
+  }
+  return ensure_ws(c, need(*form));
+}
+
 mpc_status check_trunc(int bits) { return (bits < 0 || bits > 63) ? MPC_E_INVAL : MPC_OK; }
-mpc_status check_form(mpc_form f) {
+mpc_status check_form(Form f) {
   return (f == MPC_FORM_PLAIN || f == MPC_FORM_LIMB8 || f == MPC_FORM_AUTO || f == MPC_FORM_FP64LIMB)
              ? MPC_OK
              : MPC_E_INVAL;
@@ -1315,7 +1501,7 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
     for (int j = 0; j < i; ++j)
       if (overlap(bufs[i], ns[i], bufs[j], ns[j])) return MPC_E_ALIAS;
 
-  const mpc_form form = resolve_form(MPC_FORM_AUTO, M, N, K, K);
+  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, K);
   const Epilogue ep = make_ep(t->c0, -1, 0, t->c1, view);
   // the left factor is a (matmul) or the weight b (conv); the right one b or im2col(a)
   const u64 *L0 = kind == MPC_TRIPLE_MATMUL ? t->a0 : t->b0, *L1 = kind == MPC_TRIPLE_MATMUL ? t->a1 : t->b1;
@@ -1323,11 +1509,11 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
   JobSpec jl = left_job(M, K, K), jr = kind == MPC_TRIPLE_MATMUL ? right_job(K, N, N) : im2col_job(cs, lout);
   set_mode(jl, kModeSum2, {L0, L1});
   set_mode(jr, kModeSum2, {R0, R1});
-  // In the limb form a matrix operand's shares are drawn inside its pack
+  // In a packing form a matrix operand's shares are drawn inside its pack
   // (each element is packed exactly once), so they are written once and never
   // read back; an im2col operand (overlapping windows, possibly uncovered
   // tail elements) and the plain form take the shares from PRG fills.
-  const bool limb = form == MPC_FORM_LIMB8 && nc > 0;
+  const bool limb = packs(form) && nc > 0;
   const bool a_left = kind == MPC_TRIPLE_MATMUL;  // which triple factor is the left operand
   u64* Ls[2] = {a_left ? t->a0 : t->b0, a_left ? t->a1 : t->b1};
   u64* Rs[2] = {a_left ? t->b0 : t->a0, a_left ? t->b1 : t->a1};
@@ -1335,10 +1521,10 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
   const bool fuse_r = limb && kind == MPC_TRIPLE_MATMUL;
   if (limb) set_prg_sum2(jl, key[Lslot], key[Lslot + 1], Ls[0], Ls[1]);
   if (fuse_r) set_prg_sum2(jr, key[Rslot], key[Rslot + 1], Rs[0], Rs[1]);
-  size_t need = kAlign;
-  if (form == MPC_FORM_LIMB8) need += job_bytes(jl) + job_bytes(jr);
-  else if (kind == MPC_TRIPLE_CONV1D) need += align_up((size_t)(K * N) * 8);
-  CHK(ensure_ws(c, need));
+  CHK(ensure_packing_ws(c, &form, [&](Form f) {
+    return kAlign + (packs(f) ? job_bytes(jl, f) + job_bytes(jr, f) : kind == MPC_TRIPLE_CONV1D ? align_up((size_t)(K * N) * 8) : 0) +
+           (f == kFormResidue ? res_out_bytes(M, N, K, 0) : 0);
+  }));
   const size_t nl = a_left ? na : nb, nr = a_left ? nb : na;
   if (!limb) {
     CHK(hip_status(launch_prg_fill(st, key[Lslot], Ls[0], nl)));
@@ -1354,9 +1540,9 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
   c->stats.launches += 1;
   if (nc) {
     Carve cv(c->ws);
-    if (form == MPC_FORM_LIMB8) {
-      std::vector<PackJob> jobs{place_job(jl, cv), place_job(jr, cv)};
-      CHK(issue_limb(c, jobs, {limb_req(M, N, K, 0, jobs[0].dst[0], nullptr, jobs[1].dst[0], nullptr, ep)}, c->sched_default));
+    if (packs(form)) {
+      std::vector<PackJob> jobs{place_job(jl, cv, form), place_job(jr, cv, form)};
+      CHK(issue_packed(c, form, cv, jobs, {limb_req(M, N, K, 0, jobs[0].dst[0], nullptr, jobs[1].dst[0], nullptr, ep)}));
     } else if (kind == MPC_TRIPLE_MATMUL) {
       CHK(issue_plain(c, {plain_problem(M, N, K, 0, L0, L1, K, nullptr, 0, R0, R1, N, nullptr, 0, ep)}));
     } else {
@@ -1507,7 +1693,10 @@ mpc_status issue_opens(mpc_ctx* c, const std::vector<OpenJob>& opens) {
 }
 
 // Workspace of one Beaver matmul in a form.
-size_t matmul_ws(const MatmulPlan& m, mpc_form form) {
+size_t matmul_ws(const MatmulPlan& m, Form form) {
+  if (form == kFormResidue)
+    return 3 * align_up(packed_bytes(m.M, m.K, form)) + 3 * align_up(packed_bytes(m.N, m.K, form)) +
+           2 * res_out_bytes(m.M, m.N, m.K, m.K);
   if (form == MPC_FORM_LIMB8 && m.packed)  // eps, g0 and delta only
     return 2 * align_up(packed_bytes(m.M, m.K)) + align_up(packed_bytes(m.N, m.K));
   if (form == MPC_FORM_LIMB8)
@@ -1568,21 +1757,21 @@ void matmul_plain(const MatmulPlan& m, Carve& cv, int trunc, std::vector<OpenJob
                                           rowmajor_view(m.N))));
 }
 
-// Limb form: one fused open+pack job per operand side, then the same finish
+// Packing forms: one fused open+pack job per operand side, then the same finish
 // over packed operands.
-void matmul_limb(const MatmulPlan& m, Carve& cv, int trunc, std::vector<PackJob>& jobs,
-                 std::vector<LimbReq>& reqs) {
+void matmul_packed(const MatmulPlan& m, Carve& cv, int trunc, Form form, std::vector<PackJob>& jobs,
+                   std::vector<LimbReq>& reqs) {
   JobSpec jl = left_job(m.M, m.K, m.K), jr = right_job(m.K, m.N, m.N);
   open_left(jl, m.x0, m.x1, m.t.a0, m.t.a1);
   open_right(jr, m.y0, m.y1, m.t.b0, m.t.b1);
-  if (m.packed) {
+  if (m.packed && form == MPC_FORM_LIMB8) {
     // a_1, b_0, b_1 come packed from the dealer: the open packs eps, g0 and
     // delta only
     jl.mode = kModeOpenLeft2;
     jr.mode = kModeOpenRight1;
     size_t off[3];
     packed_triple_layout(m.M, m.N, m.K, off);
-    PackJob L = place_job(jl, cv), R = place_job(jr, cv);
+    PackJob L = place_job(jl, cv, form), R = place_job(jr, cv, form);
     jobs.push_back(L);
     jobs.push_back(R);
     const uint8_t *a1 = m.packed + off[0], *b0 = m.packed + off[1], *b1 = m.packed + off[2];
@@ -1592,7 +1781,7 @@ void matmul_limb(const MatmulPlan& m, Carve& cv, int trunc, std::vector<PackJob>
                                       rowmajor_view(m.N))));
     return;
   }
-  const PackJob L = place_job(jl, cv), R = place_job(jr, cv);
+  const PackJob L = place_job(jl, cv, form), R = place_job(jr, cv, form);
   jobs.push_back(L);
   jobs.push_back(R);
   // L.dst: eps, g0, a1;  R.dst: delta, b0, b1
@@ -1603,29 +1792,54 @@ void matmul_limb(const MatmulPlan& m, Carve& cv, int trunc, std::vector<PackJob>
                                     rowmajor_view(m.N))));
 }
 
-mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int trunc, mpc_form form) {
+std::vector<Form> packing_forms(const std::vector<MatmulPlan>& plans) {
+  std::vector<Form> f;
+  for (const MatmulPlan& m : plans) f.push_back(packing_form(m.M, m.N, 2 * m.K));
+  return f;
+}
+
+// Every plan has a form of its own under the packing forms (`forms`: one per
+// plan, LIMB8 or residue); otherwise `form` is all plans' form.
+mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int trunc, Form form,
+                       std::vector<Form> forms = {}) {
+  if (packs(form) && forms.empty()) forms.assign(plans.size(), form);
   if (form == MPC_FORM_FP64LIMB) {
     CHK(run_matmuls_fp64(c, plans, trunc));
-  } else if (form == MPC_FORM_LIMB8) {
-    size_t need = kAlign;
-    for (const MatmulPlan& m : plans) need += matmul_ws(m, form);
-    CHK(ensure_ws(c, need));
+  } else if (packs(form)) {
+    // both forms' operands side by side in the workspace; where that much
+    // cannot be had, every plan takes the limb form
+    Form any = std::count(forms.begin(), forms.end(), kFormResidue) ? kFormResidue : MPC_FORM_LIMB8;
+    CHK(ensure_packing_ws(c, &any, [&](Form f) {
+      size_t need = kAlign;
+      for (size_t q = 0; q < plans.size(); ++q) need += matmul_ws(plans[q], f == kFormResidue ? forms[q] : f);
+      return need;
+    }));
+    if (any == MPC_FORM_LIMB8) forms.assign(plans.size(), any);
     Carve cv(c->ws);
-    std::vector<PackJob> jobs;
-    std::vector<LimbReq> reqs;
+    std::vector<PackJob> jobs, rjobs;
+    std::vector<LimbReq> reqs, rreqs;
     std::vector<std::array<i64, 3>> shapes;
-    for (const MatmulPlan& m : plans) {
-      matmul_limb(m, cv, trunc, jobs, reqs);
-      shapes.push_back({m.M, m.N, m.K});
+    for (size_t q = 0; q < plans.size(); ++q) {
+      const MatmulPlan& m = plans[q];
+      const bool res = forms[q] == kFormResidue;
+      matmul_packed(m, cv, trunc, forms[q], res ? rjobs : jobs, res ? rreqs : reqs);
+      if (!res) shapes.push_back({m.M, m.N, m.K});
     }
-    // every problem's two finish GEMMs take its schedule and tile class
-    const std::vector<ProbSched> ts = scheds_for(c, shapes);
-    for (size_t q = 0; q < reqs.size(); ++q) {
-      reqs[q].own_sched = true;
-      reqs[q].sched = ts[q / 2].s;
-      reqs[q].cls = ts[q / 2].cls;
+    if (!rreqs.empty()) {
+      CHK(issue_residue(c, cv, rjobs, rreqs));
+      // a limb part uploads its own tables: this slot is read only by the work issued so far
+      if (!reqs.empty()) CHK(mark_slot(c));
     }
-    CHK(issue_limb(c, jobs, reqs, c->sched_default));
+    if (!reqs.empty()) {
+      // every problem's two finish GEMMs take its schedule and tile class
+      const std::vector<ProbSched> ts = scheds_for(c, shapes);
+      for (size_t q = 0; q < reqs.size(); ++q) {
+        reqs[q].own_sched = true;
+        reqs[q].sched = ts[q / 2].s;
+        reqs[q].cls = ts[q / 2].cls;
+      }
+      CHK(issue_limb(c, jobs, reqs, c->sched_default));
+    }
   } else if (plans.size() == 1 && plans[0].K <= kSmallMatmulK && plans[0].M * plans[0].N <= kSmallMatmulMacs &&
              plans[0].M * plans[0].N * plans[0].K <= kSmallMatmulMacs) {
     // a small product: open and finish in one launch, no workspace
@@ -1657,14 +1871,14 @@ mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int tru
 
 mpc_status mpc_beaver_matmul(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const uint64_t* x0,
                              const uint64_t* x1, const uint64_t* y0, const uint64_t* y1,
-                             const mpc_triple* t, int trunc_bits, mpc_form form, uint64_t* z0,
+                             const mpc_triple* t, int trunc_bits, mpc_form want, uint64_t* z0,
                              uint64_t* z1) {
   if (!c || !t) return MPC_E_INVAL;
   CHK(check_trunc(trunc_bits));
-  CHK(check_form(form));
+  CHK(check_form(want));
   MatmulPlan m{M, N, K, x0, x1, y0, y1, *t, z0, z1};
   CHK(validate_matmul(m));
-  form = resolve_form(form, M, N, 2 * K, K);
+  Form form = resolve_form(want, M, N, 2 * K, K);
   CHK(check_limb_k(form, K));
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
@@ -1726,7 +1940,7 @@ mpc_status mpc_dealer_triples_packed(mpc_ctx* c, uint64_t dseed, uint64_t tag, i
   CHK(hip_status(launch_prg_fill(c->s[0], key[kSlotC0], t->c0, nc)));
   c->stats.launches++;
   Carve cv(c->ws);
-  PackJob L = place_job(jl, cv, 1), R = place_job(jr, cv, 1);
+  PackJob L = place_job(jl, cv, MPC_FORM_LIMB8, 1), R = place_job(jr, cv, MPC_FORM_LIMB8, 1);
   uint8_t* pk = (uint8_t*)packed;
   L.dst[1] = pk + off[0];
   R.dst[1] = pk + off[1];
@@ -1748,7 +1962,7 @@ mpc_status mpc_beaver_matmul_prepacked(mpc_ctx* c, int64_t M, int64_t N, int64_t
   CHK(check_limb_k(MPC_FORM_LIMB8, K));
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
-  CHK(run_matmuls(c, {m}, trunc_bits, MPC_FORM_LIMB8));
+  CHK(run_matmuls(c, {m}, trunc_bits, packing_form(M, N, 2 * K)));
   return end_call(c);
 }
 
@@ -1784,7 +1998,7 @@ mpc_status mpc_beaver_matmul_grouped_prepacked(mpc_ctx* c, size_t count, const m
   CHK(batch_disjoint(std::move(outs), ins));
   CHK(set_device(c));
   std::stable_sort(plans.begin(), plans.end(), [](const MatmulPlan& a, const MatmulPlan& b) { return a.K > b.K; });
-  CHK(run_matmuls(c, plans, trunc_bits, MPC_FORM_LIMB8));
+  CHK(run_matmuls(c, plans, trunc_bits, MPC_FORM_LIMB8, packing_forms(plans)));
   return end_call(c);
 }
 
@@ -1814,7 +2028,7 @@ mpc_status mpc_beaver_matmul_noalloc(mpc_ctx* c, int64_t M, int64_t N, int64_t K
     Carve cv(c->scratch);
     std::vector<PackJob> jobs;
     std::vector<LimbReq> reqs;
-    matmul_limb(m, cv, trunc_bits, jobs, reqs);
+    matmul_packed(m, cv, trunc_bits, MPC_FORM_LIMB8, jobs, reqs);
     const ProbSched ts = scheds_for(c, {{M, N, K}})[0];
     for (LimbReq& r : reqs) r.cls = ts.cls;
     CHK(issue_limb(c, jobs, reqs, ts.s, true));
@@ -1827,12 +2041,12 @@ mpc_status mpc_beaver_matmul_noalloc(mpc_ctx* c, int64_t M, int64_t N, int64_t K
 
 mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const uint64_t* x0,
                              const uint64_t* x1, const uint64_t* w0, const uint64_t* w1,
-                             const mpc_triple* t, int trunc_bits, mpc_form form, uint64_t* z0,
+                             const mpc_triple* t, int trunc_bits, mpc_form want, uint64_t* z0,
                              uint64_t* z1) {
   if (!c || !t) return MPC_E_INVAL;
   CHK(check_conv(shape));
   CHK(check_trunc(trunc_bits));
-  CHK(check_form(form));
+  CHK(check_form(want));
   const mpc_conv1d_shape s = *shape;
   const i64 lout = conv_lout(s);
   const size_t nx = (size_t)(s.batch * s.cin * s.length), nw = (size_t)(s.cout * s.cin * s.ksize);
@@ -1850,21 +2064,23 @@ mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const ui
   // transposed orientation: z_p[b][o][l] is element (o, b*Lout + l) of
   //   c_p + Wm(b_p) @ im2col(eps) + Wm(delta) @ im2col(g_p),  g_0 = a_0 + eps, g_1 = a_1
   const i64 M = s.cout, N = s.batch * lout, K = s.cin * s.ksize;
-  form = resolve_form(form, M, N, 2 * K, K);
+  Form form = resolve_form(want, M, N, 2 * K, K);
   CHK(check_limb_k(form, K));
   const OutView view{lout, std::max<i64>(lout, 1), s.cout * lout};
-  if (form == MPC_FORM_LIMB8) {
+  if (packs(form)) {
     JobSpec jw = left_job(M, K, K), jx = im2col_job(s, lout);
     open_right(jw, w0, w1, t->b0, t->b1);  // delta, b0, b1 (weights)
     open_left(jx, x0, x1, t->a0, t->a1);   // im2col of eps, g0, a1 (activations)
-    CHK(ensure_ws(c, kAlign + job_bytes(jw) + job_bytes(jx)));
+    CHK(ensure_packing_ws(c, &form, [&](Form f) {
+      return kAlign + job_bytes(jw, f) + job_bytes(jx, f) + (f == kFormResidue ? 2 * res_out_bytes(M, N, K, K) : 0);
+    }));
     Carve cv(c->ws);
-    const PackJob W = place_job(jw, cv), X = place_job(jx, cv);
+    const PackJob W = place_job(jw, cv, form), X = place_job(jx, cv, form);
     std::vector<LimbReq> reqs;
     for (int p = 0; p < 2; ++p)
       reqs.push_back(limb_req(M, N, K, K, W.dst[p == 0 ? 1 : 2], W.dst[0], X.dst[0], X.dst[p == 0 ? 1 : 2],
                               make_ep(p == 0 ? t->c0 : t->c1, +1, trunc_bits, p == 0 ? z0 : z1, view)));
-    CHK(issue_limb(c, {W, X}, reqs, c->sched_default));
+    CHK(issue_packed(c, form, cv, {W, X}, reqs));
   } else {
     // plain and fp64 limb forms: open, then im2col of eps, g_0 and a_1 into
     // row-major K x N matrices
@@ -1912,9 +2128,9 @@ mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const ui
 }
 
 mpc_status mpc_ring_gemm(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const uint64_t* A,
-                         const uint64_t* B, uint64_t* C, mpc_form form) {
+                         const uint64_t* B, uint64_t* C, mpc_form want) {
   if (!c) return MPC_E_INVAL;
-  CHK(check_form(form));
+  CHK(check_form(want));
   CHK(check_mnk(M, N, K));
   CHK(check_ptr(A, (size_t)(M * K)));
   CHK(check_ptr(B, (size_t)(K * N)));
@@ -1923,17 +2139,19 @@ mpc_status mpc_ring_gemm(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const uint
     return MPC_E_ALIAS;
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
-  form = resolve_form(form, M, N, K, K);
+  Form form = resolve_form(want, M, N, K, K);
   CHK(check_limb_k(form, K));
   const Epilogue ep = make_ep(nullptr, +1, 0, C, rowmajor_view(N));
-  if (form == MPC_FORM_LIMB8) {
+  if (packs(form)) {
     JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
     set_mode(ja, kModeCopy, {A});
     set_mode(jb, kModeCopy, {B});
-    CHK(ensure_ws(c, kAlign + job_bytes(ja) + job_bytes(jb)));
+    CHK(ensure_packing_ws(c, &form, [&](Form f) {
+      return kAlign + job_bytes(ja, f) + job_bytes(jb, f) + (f == kFormResidue ? res_out_bytes(M, N, K, 0) : 0);
+    }));
     Carve cv(c->ws);
-    const PackJob PA = place_job(ja, cv), PB = place_job(jb, cv);
-    CHK(issue_limb(c, {PA, PB}, {limb_req(M, N, K, 0, PA.dst[0], nullptr, PB.dst[0], nullptr, ep)}, c->sched_default));
+    const PackJob PA = place_job(ja, cv, form), PB = place_job(jb, cv, form);
+    CHK(issue_packed(c, form, cv, {PA, PB}, {limb_req(M, N, K, 0, PA.dst[0], nullptr, PB.dst[0], nullptr, ep)}));
   } else if (form == MPC_FORM_FP64LIMB) {
     if (K >= kFp64MaxK) return MPC_E_UNSUPPORTED;
     CHK(ensure_ws(c, kAlign + fp64_ws(M, N, K)));
@@ -1946,10 +2164,10 @@ mpc_status mpc_ring_gemm(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const uint
 }
 
 mpc_status mpc_beaver_matmul_grouped(mpc_ctx* c, size_t count, const mpc_matmul_desc* descs,
-                                     int trunc_bits, mpc_form form) {
+                                     int trunc_bits, mpc_form want) {
   if (!c || (count && !descs)) return MPC_E_INVAL;
   CHK(check_trunc(trunc_bits));
-  CHK(check_form(form));
+  CHK(check_form(want));
   std::vector<MatmulPlan> plans;
   for (size_t i = 0; i < count; ++i) {
     const mpc_matmul_desc& d = descs[i];
@@ -1961,7 +2179,9 @@ mpc_status mpc_beaver_matmul_grouped(mpc_ctx* c, size_t count, const mpc_matmul_
   // AUTO: the limb form, unless a problem's k is longer than it addresses
   i64 kmax = 0;
   for (const MatmulPlan& m : plans) kmax = std::max(kmax, m.K);
-  if (form == MPC_FORM_AUTO) form = kmax > kLimbMaxSegK ? MPC_FORM_PLAIN : MPC_FORM_LIMB8;
+  Form form = want;
+  const bool each = form == MPC_FORM_AUTO;  // then each product takes its own packing form
+  if (each) form = kmax > kLimbMaxSegK ? MPC_FORM_PLAIN : MPC_FORM_LIMB8;
   CHK(check_limb_k(form, kmax));
   if (plans.empty()) return MPC_OK;
   {
@@ -1984,7 +2204,7 @@ mpc_status mpc_beaver_matmul_grouped(mpc_ctx* c, size_t count, const mpc_matmul_
   std::stable_sort(plans.begin(), plans.end(), [](const MatmulPlan& a, const MatmulPlan& b) {
     return a.K > b.K;
   });
-  CHK(run_matmuls(c, plans, trunc_bits, form));
+  CHK(run_matmuls(c, plans, trunc_bits, form, each && packs(form) ? packing_forms(plans) : std::vector<Form>{}));
   return end_call(c);
 }
 
@@ -2597,12 +2817,13 @@ mpc_status mpc_mp_dealer_triples(mpc_ctx* c, int P, mpc_triple_kind kind, uint64
   CHK(mp_alias(a, P, na, {{&bi, nb}, {&ci, nc}}));
   CHK(mp_alias(b, P, nb, {{&ci, nc}}));
   if (!na && !nb && !nc) return MPC_OK;
-  const mpc_form form = resolve_form(MPC_FORM_AUTO, M, N, K, K);
+  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, K);
   // workspace: a = sum a_p, b = sum b_p, S = sum_{p<P-1} c_p, then the GEMM's packs
   JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
-  size_t need = kAlign + align_up(na * 8) + align_up(nb * 8) + align_up(nc * 8);
-  if (form == MPC_FORM_LIMB8) need += job_bytes(ja) + job_bytes(jb);
-  CHK(ensure_ws(c, need));
+  CHK(ensure_packing_ws(c, &form, [&](Form f) {
+    return kAlign + align_up(na * 8) + align_up(nb * 8) + align_up(nc * 8) + (packs(f) ? job_bytes(ja, f) + job_bytes(jb, f) : 0) +
+           (f == kFormResidue ? res_out_bytes(M, N, K, 0) : 0);
+  }));
   Carve cv(c->ws);
   u64* as = cv.take<u64>(na);
   u64* bs = cv.take<u64>(nb);
@@ -2614,12 +2835,11 @@ mpc_status mpc_mp_dealer_triples(mpc_ctx* c, int P, mpc_triple_kind kind, uint64
   if (!nc) return end_call(c);
   // c_{P-1} = a @ b - S
   const Epilogue ep = make_ep(S, -1, 0, cc.p[P - 1], rowmajor_view(N));
-  if (form == MPC_FORM_LIMB8) {
+  if (packs(form)) {
     set_mode(ja, kModeCopy, {as});
     set_mode(jb, kModeCopy, {bs});
-    const PackJob PA = place_job(ja, cv), PB = place_job(jb, cv);
-    CHK(issue_limb(c, {PA, PB}, {limb_req(M, N, K, 0, PA.dst[0], nullptr, PB.dst[0], nullptr, ep)},
-                   c->sched_default));
+    const PackJob PA = place_job(ja, cv, form), PB = place_job(jb, cv, form);
+    CHK(issue_packed(c, form, cv, {PA, PB}, {limb_req(M, N, K, 0, PA.dst[0], nullptr, PB.dst[0], nullptr, ep)}));
   } else {
     CHK(issue_plain(c, {plain_problem(M, N, K, 0, as, nullptr, K, nullptr, 0, bs, nullptr, N, nullptr, 0, ep)}));
   }
@@ -2668,12 +2888,12 @@ mpc_status mpc_mp_beaver_mul(mpc_ctx* c, int P, size_t n, const uint64_t* const*
 }
 
 mpc_status mpc_mp_beaver_matmul(mpc_ctx* c, int P, int64_t M, int64_t N, int64_t K, const uint64_t* const* x,
-                                const uint64_t* const* y, const mpc_mp_triple* t, mpc_form form,
+                                const uint64_t* const* y, const mpc_mp_triple* t, mpc_form want,
                                 uint64_t* const* z) {
   if (!c || !t) return MPC_E_INVAL;
   CHK(check_parties(P));
-  CHK(check_form(form));
-  if (form == MPC_FORM_FP64LIMB) return MPC_E_UNSUPPORTED;
+  CHK(check_form(want));
+  if (want == MPC_FORM_FP64LIMB) return MPC_E_UNSUPPORTED;
   CHK(check_mnk(M, N, K));
   const size_t na = (size_t)(M * K), nb = (size_t)(K * N), nc = (size_t)(M * N);
   MpIn xi, yi, ai, bi, ci;
@@ -2687,44 +2907,45 @@ mpc_status mpc_mp_beaver_matmul(mpc_ctx* c, int P, int64_t M, int64_t N, int64_t
   CHK(mp_alias(zo, P, nc, {{&xi, na}, {&yi, nb}, {&ai, na}, {&bi, nb}, {&ci, nc}}));
   if (!nc) return MPC_OK;
   CHK(set_device(c));
-  form = resolve_form(form, M, N, 2 * K, K);
+  Form form = resolve_form(want, M, N, 2 * K, K);
   CHK(check_limb_k(form, K));
   const hipStream_t st = c->s[0];
   // open eps (MxK) and delta (KxN) into the workspace, then party p's finish
   // z_p = c_p + [a_p + [p=0] eps | eps] @ [delta ; b_p]
-  size_t need = kAlign + align_up(na * 8) + align_up(nb * 8);
-  if (form == MPC_FORM_LIMB8)
-    need += (size_t)(P + 1) * align_up(packed_bytes(M, K)) + (size_t)(P + 1) * align_up(packed_bytes(N, K));
-  CHK(ensure_ws(c, need));
+  CHK(ensure_packing_ws(c, &form, [&](Form f) {
+    return kAlign + align_up(na * 8) + align_up(nb * 8) +
+           (packs(f) ? (size_t)(P + 1) * (align_up(packed_bytes(M, K, f)) + align_up(packed_bytes(N, K, f))) : 0) +
+           (f == kFormResidue ? (size_t)P * res_out_bytes(M, N, K, K) : 0);
+  }));
   Carve cv(c->ws);
   u64* eps = cv.take<u64>(na);
   u64* del = cv.take<u64>(nb);
   CHK(hip_status(launch_mp_open(st, xi, ai, P, na, eps)));
   CHK(hip_status(launch_mp_open(st, yi, bi, P, nb, del)));
   c->stats.launches += 2;
-  if (form == MPC_FORM_LIMB8) {
+  if (packs(form)) {
     std::vector<PackJob> jobs;
     JobSpec je = left_job(M, K, K), jd = right_job(K, N, N);
     set_mode(je, kModeCopy, {eps});
     set_mode(jd, kModeCopy, {del});
-    jobs.push_back(place_job(je, cv));
-    jobs.push_back(place_job(jd, cv));
+    jobs.push_back(place_job(je, cv, form));
+    jobs.push_back(place_job(jd, cv, form));
     std::vector<const uint8_t*> pa(P), pb(P);
     for (int p = 0; p < P; ++p) {
       JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
       if (p == 0) set_mode(ja, kModeSum2, {ai.p[0], eps});
       else set_mode(ja, kModeCopy, {ai.p[p]});
       set_mode(jb, kModeCopy, {bi.p[p]});
-      jobs.push_back(place_job(ja, cv));
+      jobs.push_back(place_job(ja, cv, form));
       pa[p] = jobs.back().dst[0];
-      jobs.push_back(place_job(jb, cv));
+      jobs.push_back(place_job(jb, cv, form));
       pb[p] = jobs.back().dst[0];
     }
     std::vector<LimbReq> reqs;
     for (int p = 0; p < P; ++p)
       reqs.push_back(limb_req(M, N, K, K, pa[p], jobs[0].dst[0], jobs[1].dst[0], pb[p],
                               make_ep(ci.p[p], +1, 0, zo.p[p], rowmajor_view(N))));
-    CHK(issue_limb(c, jobs, reqs, c->sched_default));
+    CHK(issue_packed(c, form, cv, jobs, reqs));
   } else {
     std::vector<PlainProblem> probs;
     for (int p = 0; p < P; ++p)

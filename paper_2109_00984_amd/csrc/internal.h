@@ -313,6 +313,80 @@ struct TileSched {
   int group_m;    // tile rows per raster group
   int xcd_remap;  // hand tiles to the XCDs in runs of neighbouring tiles
 };
+// ---------------------------------------------------------------- residue form
+// Ring GEMM through residues (gemm_residue.hip).  An operand element is read
+// as the integer v = sum_j d_j 2^(8j) of its signed 8-bit limbs, |v| <= kLimbTop,
+// and packed as one int8 residue per modulus; the products of one modulus are
+// one int8 GEMM, exact in int32, and the Chinese remainder theorem gives the
+// integer sum of kResK products back from the kRes residues, hence its value
+// mod 2^64.  18 int8 GEMMs per ring GEMM where the limb form needs 36.
+// The moduli are pairwise coprime and at most 256, so balanced residues are
+// int8; their product M is above 2^140.45, and kResK * kLimbTop^2 stays below
+// M/2 * (1 - 2^-8), the margin in which the quotient's 24-bit fractions decide.
+constexpr int kRes = 18;
+constexpr int kResModuli[kRes] = {256, 255, 253, 251, 247, 241, 239, 233, 229, 227, 223, 217, 211, 199, 197, 193, 191, 181};
+constexpr int kResMaxKBlocks = 173;  // 64-wide k blocks of one exact sum: 173 * 64 = 11072 <= 11082
+// A packed operand holds, for every modulus, a plane of 1 KiB blocks of 16
+// rows (or columns) x 64 k in MFMA lane order: lane l owns row l % 16 and
+// k = (l / 16) * 16 + 0..15.  Block (rb, kb) starts at (rb * kblocks + kb) << 10
+// of its plane.  Row counts are padded to kResRowPad blocks (the largest tile);
+// padding rows are never written and reach only outputs that are never stored.
+constexpr int kResBlockBytes = 1024;
+constexpr int kResRowPad = 16;
+i64 res_rblocks(i64 rows);  // padded 16-row block count
+i64 res_kblocks(i64 K);     // 64-wide k blocks
+// Longest k segment the residue GEMM addresses: 16 strips of 1 KiB blocks
+// through one 32-bit buffer descriptor.
+constexpr i64 kResMaxSegK = (i64)65536 * 64;
+
+// One chunk of k of one product: blocks [kb_begin, kb_end) of the
+// concatenation [segment 0 | segment 1] of kbs blocks each, at most
+// kResMaxKBlocks of them.  Its
+// residues go to R: per modulus a plane of 1 KiB units of 16 rows x 64 columns,
+// lane l of a unit holding row l % 16 and the columns 16 y + 4 (l / 16) + e at
+// byte 4 y + e.
+struct ResProblem {
+  const uint8_t *PA0, *PA1, *PB0, *PB1;
+  i64 pa, pb;              // plane strides of the operands
+  int kbs, kb_begin, kb_end;
+  int ntm, ntn;            // output tiles
+  int n64;                 // units per row of units
+  uint8_t* R;
+  i64 pr;                  // plane stride of R
+};
+// The combine of one product: residues of nch chunks -> ring elements -> epilogue.
+struct ResOut {
+  const uint8_t* R;
+  i64 pr, pc;              // plane and chunk strides
+  int nch, n64;
+  i64 M, N;
+  Epilogue ep;
+};
+constexpr int kResInline = 4;
+struct ResGemmTables {
+  const ResProblem* probs;
+  const int* tile_start;   // nprob + 1 prefix sums of kRes * ntm * ntn
+  int nprob, tiles;
+  ResProblem iprobs[kResInline];
+  int itile_start[kResInline + 1];
+};
+struct ResOutTables {
+  const ResOut* outs;
+  const i64* unit_start;   // nout + 1 prefix sums of the products' units
+  int nout;
+  ResOut iouts[kResInline];
+  i64 iunit_start[kResInline + 1];
+};
+// Workgroup tiles of the residue GEMM.
+enum ResTile : int { kRes256x256 = 0, kRes256x128 = 1, kRes128x256 = 2, kRes128x128 = 3, kResTiles = 4 };
+void res_tile_shape(int tile, int* bm, int* bn);
+int res_tile_per_cu(int tile);  // workgroups per compute unit
+struct PackTables;
+hipError_t launch_res_pack(hipStream_t s, const PackTables& t, i64 total_blocks, int kind, int mode);
+// grid <= total_tiles workgroups take tiles b, b + grid, ...
+hipError_t launch_res_gemm(hipStream_t s, const ResGemmTables& t, int total_tiles, int tile, int grid);
+hipError_t launch_res_combine(hipStream_t s, const ResOutTables& t, i64 total_units);
+
 // ---------------------------------------------------------------- binary sharing (two parties)
 // Slots: 0x700 share, 0x701..0x705 AND triple a0, a1, b0, b1, c0, 0x706/0x707
 // the parties' re-sharing in A2B, 0x708..0x70a Algorithm 2's bit r, <r>_0, [r]_0.

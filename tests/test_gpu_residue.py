@@ -1,0 +1,153 @@
+"""The residue form (what AUTO takes for products with many rows and columns) gives the oracle's bits: edges of its
+16-, 64-, 128- and 256-wide blocks, k at and past one exact sum (11072), operands of the largest magnitude, and every
+entry point that can take it.  (The plain form, itself checked against the oracle, stands in for it on whole outputs.)"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.gpu_util import dev, host, pair, say
+
+pytestmark = pytest.mark.gpu
+
+SEED, DSEED = 2051, 3051
+# the signed-limb readings of largest magnitude: all limbs -128, all 127, and the int64 ends
+EDGE = np.array([0x8080808080808080, 0x7f7f7f7f7f7f7f7f, 1 << 63, (1 << 63) - 1, 0, 1, 2**64 - 1, 0x80], dtype=np.uint64)
+
+
+@pytest.fixture(scope="module")
+def m():
+    import paper_2109_00984_amd as mpc
+    return mpc
+
+
+@pytest.fixture(scope="module")
+def c(m):
+    ctx = m.Context(device=0, seed=SEED)
+    yield ctx
+    ctx.close()
+
+
+def rnd(seed, shape, kind="uniform"):
+    g = np.random.default_rng(seed)
+    if kind == "uniform":
+        return g.integers(0, 2**64, size=shape, dtype=np.uint64)
+    if kind == "edge":
+        return g.choice(EDGE, size=shape)
+    return np.full(shape, EDGE[0], dtype=np.uint64)  # "top": every product at its largest
+
+
+def same(a, b):
+    return torch.equal(a.s0, b.s0) and torch.equal(a.s1, b.s1)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "edge"])
+def test_ring_gemm_matches_oracle(m, c, kind):
+    M, N, K = 1025, 1030, 4929
+    say(f"residue ring GEMM {M}x{N}x{K} {kind}")
+    A, B = rnd(M + K, (M, K), kind), rnd(N + K, (K, N), kind)
+    rows, cols = np.r_[0:1025:97, 1008:1025], np.r_[0:1030:61, 1013:1030]
+    r, q = (v.ravel() for v in np.meshgrid(rows, cols))
+    got = host(c, c.ring_gemm(dev(A), dev(B)))
+    assert np.array_equal(got[r, q], oracle.ring_gemm_at(A, B, r, q))
+
+
+@pytest.mark.parametrize("M,N,K", [(1024, 1024, 4896), (1039, 1089, 4928), (1281, 1537, 4097), (3000, 700, 8191), (1024, 1024, 11008),
+                                   (1024, 1024, 11072), (1024, 1024, 11073), (1030, 1100, 22144), (1030, 1100, 22145)])
+@pytest.mark.parametrize("kind", ["uniform", "top"])
+def test_ring_gemm_matches_plain(m, c, M, N, K, kind):
+    say(f"residue ring GEMM {M}x{N}x{K} {kind}")
+    A, B = dev(rnd(K, (M, K), kind)), dev(rnd(K + 1, (K, N), kind))
+    assert torch.equal(c.ring_gemm(A, B), c.ring_gemm(A, B, "plain"))
+
+
+@pytest.mark.parametrize("M,N,K,trunc", [(1025, 1300, 2200, 16), (1024, 1024, 2464, 0), (2050, 1050, 1900, 63)])
+def test_beaver_matmul_matches_plain(m, c, M, N, K, trunc):
+    say(f"residue Beaver matmul {M}x{N}x{K} trunc {trunc}")
+    tag = M + 7 * N + 11 * K
+    x, y = c.share(dev(rnd(tag, (M, K))), 0, 1), c.share(dev(rnd(tag + 1, (K, N))), 1, 2)
+    t, packed = c.dealer_packed(DSEED, tag, (M, N, K))
+    tr = c.dealer(m.TRIPLE_MATMUL, DSEED, tag, (M, N, K))
+    assert torch.equal(t.c0, tr.c0) and torch.equal(t.c1, tr.c1)
+    assert torch.equal(tr.c0 + tr.c1, c.ring_gemm(tr.a0 + tr.a1, tr.b0 + tr.b1, "plain"))
+    want = c.beaver_matmul(x, y, tr, trunc, "plain")
+    for z in (c.beaver_matmul(x, y, tr, trunc), c.beaver_matmul_prepacked(x, y, t, packed, trunc),
+              c.beaver_matmul_grouped([(x, y, tr)], trunc)[0]):
+        assert same(z, want)
+
+
+def test_mixed_group_and_graph_replay(m):
+    """A group with products of both packing forms, more than fit the kernel arguments, eager and replayed."""
+    say("residue and limb products in one group")
+    streams = (torch.cuda.Stream(), torch.cuda.Stream())
+    c = m.Context(device=0, seed=SEED, streams=streams)
+    with torch.cuda.stream(streams[0]):
+        shapes = [(300, 220, 500), (1040, 1030, 2500), (17, 200, 300), (1500, 1100, 3000), (40, 600, 64), (1025, 1281, 2304)]
+        probs = []
+        for i, (M, N, K) in enumerate(shapes):
+            x, y = c.share(dev(rnd(i, (M, K))), 0, 2 * i), c.share(dev(rnd(50 + i, (K, N))), 1, 2 * i + 1)
+            probs.append((x, y, c.dealer(m.TRIPLE_MATMUL, DSEED, i, (M, N, K))))
+        want = [c.beaver_matmul(*p, trunc_bits=16, form="plain") for p in probs]
+        outs = c.beaver_matmul_grouped(probs, 16)
+        c.sync()
+        assert all(same(z, w) for z, w in zip(outs, want))
+        c.graph_begin()
+        c.beaver_matmul_grouped(probs, 16, outs=outs)
+        g = c.graph_end()
+        for _ in range(3):
+            for z in outs:
+                z.s0.zero_()
+                z.s1.zero_()
+            c.graph_launch(g)
+            c.sync()
+            assert all(same(z, w) for z, w in zip(outs, want))
+    c.close()
+
+
+def test_small_workspace_falls_back(m):
+    """Where the workspace may not grow (under capture), a product that fits it in the limb form still runs."""
+    streams = (torch.cuda.Stream(), torch.cuda.Stream())
+    c, d = (m.Context(device=0, seed=SEED, streams=streams) for _ in range(2))
+    M, N, K = 1040, 1060, 2500
+    with torch.cuda.stream(streams[0]):
+        x, y = c.share(dev(rnd(1, (M, K))), 0, 1), c.share(dev(rnd(2, (K, N))), 1, 2)
+        t = c.dealer(m.TRIPLE_MATMUL, DSEED, 3, (M, N, K))
+        want = c.beaver_matmul(x, y, t, 16, "plain")
+        c.sync()
+        d.beaver_matmul(x, y, t, 16, "limb8")
+        d.sync()
+        z = m.SharedPair(torch.empty_like(want.s0), torch.empty_like(want.s1))
+        d.graph_begin()
+        d.beaver_matmul(x, y, t, 16, out=z)
+        g = d.graph_end()
+        d.graph_launch(g)
+        d.sync()
+        assert same(z, want)
+    d.close()
+    c.close()
+
+
+@pytest.mark.parametrize("B,cin,L,cout,k,s", [(4, 60, 320, 1100, 40, 1), (8, 80, 300, 1030, 31, 2)])
+def test_conv_matches_plain(m, c, B, cin, L, cout, k, s):
+    say(f"residue conv {B}x{cin}x{L} -> {cout}, k {k} stride {s}")
+    x, w = c.share(dev(rnd(1, (B, cin, L))), 0, 1), c.share(dev(rnd(2, (cout, cin, k))), 1, 2)
+    t = c.dealer(m.TRIPLE_CONV1D, DSEED, 9, (B, cin, L, cout, k, s))
+    z, p = c.beaver_conv1d(x, w, t, s, 16), c.beaver_conv1d(x, w, t, s, 16, "plain")
+    assert same(z, p)
+    a, b = host(c, t.a0 + t.a1), host(c, t.b0 + t.b1)
+    lout = (L - k) // s + 1
+    bs, os_, ls = np.array([0, B - 1, 1]), np.array([0, cout - 1, cout // 2]), np.array([0, lout - 1, lout // 2])
+    assert np.array_equal(host(c, t.c0 + t.c1)[bs, os_, ls], oracle.conv1d_at(a, b, s, bs, os_, ls))
+
+
+@pytest.mark.parametrize("P", [2, 3, 5])
+def test_multiparty_matches_plain(m, c, P):
+    M, N, K = 1030, 1100, 2400
+    x, y = c.mp_share(dev(rnd(1, (M, K))), P, 0, 1), c.mp_share(dev(rnd(2, (K, N))), P, 1, 2)
+    t = c.mp_dealer(P, m.TRIPLE_MATMUL, DSEED, 4, (M, N, K))
+    a, b = c.mp_beaver_matmul(x, y, t), c.mp_beaver_matmul(x, y, t, "plain")
+    for u, v in zip(a, b):
+        assert torch.equal(u, v)
+    # the dealer's product: sum of c = (sum of a) @ (sum of b)
+    tot = [sum(s[1:], s[0]) for s in (t.a, t.b, t.c)]
+    assert torch.equal(tot[2], c.ring_gemm(tot[0], tot[1], "plain"))
