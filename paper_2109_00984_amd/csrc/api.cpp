@@ -394,6 +394,19 @@ Epilogue make_ep(const u64* cadd, int csign, int trunc, u64* out, OutView v) {
 using Form = int;
 constexpr Form kFormResidue = 16;
 
+i64 conv_lout(const mpc_conv1d_shape& s) {
+  return s.length < s.ksize ? 0 : (s.length - s.ksize) / s.stride + 1;
+}
+
+// Whether the residue form takes a convolution without im2col (ResConv):
+// channels padded to 64 add at
+// most a quarter to k, and 32-bit offsets reach a whole plane.
+bool conv_direct(const mpc_conv1d_shape& s) {
+  const i64 groups = (s.cin + 63) / 64;
+  return groups * 64 * 4 <= s.cin * 5 && groups * s.ksize <= kResMaxSegK / 64 && s.batch * groups * s.length <= (i64)1 << 24 &&
+         s.batch * conv_lout(s) <= (i64)1 << 30;
+}
+
 // Whether AUTO takes a product of the limb form to the residue form, which
 // halves the int8 work (18 products against 36) and writes 2.25 times the
 // packed bytes (18 a packed element against 8): it pays where each packed
@@ -406,16 +419,26 @@ bool residue_pays(i64 M, i64 N, i64 K) {
   const double reuse = (double)M * (double)N / (double)(M + N);
   return reuse >= 512 && reuse * (double)K >= 2.5e6;
 }
+// A convolution packed without im2col writes its activation once, not once per
+// tap, so only its k (against the combine, 18 bytes an output) and its whole
+// work (against the launches) have to be long.  Limb against residue, batch 8:
+// 250 -> 250 channels, 7 taps, 771 long 424 / 281 us; 512 -> 512, 3 taps, 398
+// long 334 / 268; 64 -> 128, 5 taps, 496 long 59 / 81; 128 -> 128, 9 taps, 992
+// long: batch 2 79 / 94, batch 4 113 / 111, batch 8 201 / 157.
+bool residue_pays_conv(const mpc_conv1d_shape& s, i64 N, i64 K) {
+  if (!conv_direct(s)) return residue_pays(s.cout, N, K);
+  return s.cout >= 128 && K >= 1536 && (double)s.cout * (double)N * (double)K >= 1.3e9;
+}
 Form packing_form(i64 M, i64 N, i64 K) { return residue_pays(M, N, K) ? kFormResidue : MPC_FORM_LIMB8; }
 
 // AUTO: a matrix-core form for products of 2^22 ring MACs or more, when the
 // limb form can address their k segments (each kseg long; K is the total).
-Form resolve_form(Form f, i64 M, i64 N, i64 K, i64 kseg) {
+Form resolve_form(Form f, i64 M, i64 N, i64 K, i64 kseg, const mpc_conv1d_shape* conv = nullptr) {
   if (f != MPC_FORM_AUTO) return f;
   if (kseg > kLimbMaxSegK) return MPC_FORM_PLAIN;
   const double work = (double)M * (double)N * (double)K;
   if (work < (double)(1 << 22)) return MPC_FORM_PLAIN;
-  return packing_form(M, N, K);
+  return conv ? (residue_pays_conv(*conv, N, K) ? kFormResidue : MPC_FORM_LIMB8) : packing_form(M, N, K);
 }
 bool packs(Form f) { return f == MPC_FORM_LIMB8 || f == kFormResidue; }
 
@@ -642,6 +665,9 @@ mpc_status issue_fp64(mpc_ctx* c, Carve& cv, i64 M, i64 N, i64 K0, i64 K1, const
 
 // ------------------------------------------------------------------ limb form
 // A pack job before its outputs are placed in the workspace.
+// Plane of a channels-last activation (ResConv), in whole blocks.
+i64 res_chan_plane(i64 batch, i64 cin, i64 len) { return align_up((size_t)(batch * ((cin + 63) / 64) * len) * 64, kResBlockBytes); }
+
 struct JobSpec {
   int kind = kPackRow;
   int mode = kModeCopy;
@@ -652,9 +678,11 @@ struct JobSpec {
   u64* share[2] = {nullptr, nullptr};
 };
 
-size_t job_bytes(const JobSpec& j, Form form) {
-  return (size_t)pack_nout(j.mode) * align_up(packed_bytes(j.rows, j.K, form));
+// Bytes of one packed output.
+size_t job_out_bytes(const JobSpec& j, Form form) {
+  return j.kind == kPackChan ? (size_t)kRes * (size_t)res_chan_plane(j.rows, j.cin, j.len) : packed_bytes(j.rows, j.K, form);
 }
+size_t job_bytes(const JobSpec& j, Form form) { return (size_t)pack_nout(j.mode) * align_up(job_out_bytes(j, form)); }
 
 // Places a job's packed outputs in the workspace carve; with ws_outs >= 0
 // only the first ws_outs of them (the caller points the rest elsewhere).
@@ -679,9 +707,19 @@ PackJob place_job(const JobSpec& j, Carve& cv, Form form, int ws_outs = -1) {
   p.rblocks = res ? res_rblocks(j.rows) : limb_rblocks(j.rows);
   p.rreal = res ? (j.rows + 15) / 16 : (j.rows + 31) / 32;
   p.kblocks = res ? res_kblocks(j.K) : limb_kblocks(j.K);
+  p.units = p.rreal * p.kblocks;
+  if (j.kind == kPackConvRow) {
+    // a workgroup's four waves per 16 rows, 64 channels and four taps
+    p.units = p.rreal * ((j.cin + 63) / 64) * 4 * ((j.ksz + 3) / 4);
+  } else if (j.kind == kPackChan) {
+    // rows: the batch; one wave per 16 channels of 64 positions
+    p.rblocks = res_chan_plane(j.rows, j.cin, j.len) / kResBlockBytes;
+    p.kblocks = 1;
+    p.units = j.rows * ((j.cin + 63) / 64) * 4 * ((j.len + 63) / 64);
+  }
   const int nws = ws_outs < 0 ? pack_nout(j.mode) : ws_outs;
   for (int o = 0; o < kPackMaxOut; ++o)
-    p.dst[o] = o < nws ? cv.take<uint8_t>(packed_bytes(j.rows, j.K, form)) : nullptr;
+    p.dst[o] = o < nws ? cv.take<uint8_t>(job_out_bytes(j, form)) : nullptr;
   return p;
 }
 
@@ -726,6 +764,29 @@ JobSpec im2col_job(const mpc_conv1d_shape& s, i64 lout) {
   j.lout = lout;
   return j;
 }
+// The residue form's operands of a convolution without im2col: weights in the
+// k order of the activation's channel groups and taps, and the activation.
+JobSpec conv_weight_job(const mpc_conv1d_shape& s) {
+  JobSpec j;
+  j.kind = kPackConvRow;
+  j.rows = s.cout;
+  j.K = (s.cin + 63) / 64 * s.ksize * 64;
+  j.ld = s.cin * s.ksize;
+  j.cin = s.cin;
+  j.ksz = s.ksize;
+  return j;
+}
+JobSpec conv_chan_job(const mpc_conv1d_shape& s) {
+  JobSpec j;
+  j.kind = kPackChan;
+  j.rows = s.batch;
+  j.cin = s.cin;
+  j.len = s.length;
+  return j;
+}
+ResConv conv_geometry(const mpc_conv1d_shape& s) {
+  return ResConv{(int)s.ksize, (int)((s.cin + 63) / 64), (int)s.length, (int)s.stride, (int)conv_lout(s), (int)(s.batch * conv_lout(s))};
+}
 void set_mode(JobSpec& j, int mode, std::initializer_list<const u64*> ins) {
   j.mode = mode;
   int n = 0;
@@ -756,6 +817,7 @@ struct LimbReq {
   bool own_sched;   // use `sched` instead of the call's schedule
   TileSched sched;
   int cls;          // tile class under the classes variants
+  ResConv cv;       // residue form: a convolution's right operand (ksz 0: none)
 };
 
 // A rectangle of a product's output: rows [r0, r0 + m), columns [c0, c0 + n)
@@ -810,7 +872,7 @@ struct PackLaunches {
   std::vector<size_t> obstart;
   size_t ojobs = 0;
   explicit PackLaunches(const std::vector<PackJob>& in) {
-    for (int kind : {kPackRow, kPackCol, kPackIm2col})
+    for (int kind : {kPackRow, kPackCol, kPackIm2col, kPackConvRow, kPackChan})
       for (int mode : {kModeCopy, kModeSum2, kModeOpenLeft, kModeOpenRight, kModePrgSum2, kModePrgSum2A, kModePrgSum2B,
                        kModeOpenLeft2, kModeOpenRight1}) {
         bool any = false;
@@ -828,7 +890,7 @@ struct PackLaunches {
     bstarts.resize(km.size());
     for (size_t L = 0; L < km.size(); ++L) {
       bstarts[L].assign(1, 0);
-      for (size_t i = first[L]; i < first[L + 1]; ++i) bstarts[L].push_back(bstarts[L].back() + jobs[i].rreal * jobs[i].kblocks);
+      for (size_t i = first[L]; i < first[L + 1]; ++i) bstarts[L].push_back(bstarts[L].back() + jobs[i].units);
     }
   }
   // whether every launch's tables fit the kernel arguments
@@ -1064,7 +1126,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
 
 LimbReq limb_req(i64 M, i64 N, i64 K0, i64 K1, const uint8_t* PA0, const uint8_t* PA1,
                  const uint8_t* PB0, const uint8_t* PB1, const Epilogue& ep) {
-  return LimbReq{M, N, K0, K1, PA0, PA1, PB0, PB1, ep, false, TileSched{}, 0};
+  return LimbReq{M, N, K0, K1, PA0, PA1, PB0, PB1, ep, false, TileSched{}, 0, ResConv{}};
 }
 
 // Residue form: workspace of a product's residues, one plane per modulus and
@@ -1140,7 +1202,8 @@ mpc_status issue_residue(mpc_ctx* c, Carve& cv, const std::vector<PackJob>& jobs
       p.PB0 = r.PB0;
       p.PB1 = r.PB1 ? r.PB1 : r.PB0;
       p.pa = res_rblocks(r.M) * kb0 * kResBlockBytes;
-      p.pb = res_rblocks(r.N) * kb0 * kResBlockBytes;
+      p.pb = r.cv.ksz ? res_chan_plane((r.N / r.cv.lout), (i64)r.cv.groups * 64, r.cv.len) : res_rblocks(r.N) * kb0 * kResBlockBytes;
+      p.cv = r.cv;
       p.kbs = kb0;
       // chunks of equal length, to a block
       p.kb_begin = (int)((i64)(kb0 + kb1) * ch / nch);
@@ -1186,7 +1249,7 @@ mpc_status issue_residue(mpc_ctx* c, Carve& cv, const std::vector<PackJob>& jobs
   CHK(pk.issue(c, dev, launch_res_pack));
   LaunchTimer tm(c, MPC_FORM_LIMB8, macs);
   CHK(tm.start());
-  CHK(hip_status(launch_res_gemm(st, gt, tstart.back(), tile, grid)));
+  CHK(hip_status(launch_res_gemm(st, gt, tstart.back(), tile, grid, reqs[0].cv.ksz > 0)));
   CHK(tm.stop());
   CHK(hip_status(launch_res_combine(st, ot, ustart.back())));
   c->stats.launches += 2;
@@ -1219,9 +1282,6 @@ mpc_status check_form(Form f) {
 }
 
 
-i64 conv_lout(const mpc_conv1d_shape& s) {
-  return s.length < s.ksize ? 0 : (s.length - s.ksize) / s.stride + 1;
-}
 
 mpc_status check_conv(const mpc_conv1d_shape* s) {
   if (!s) return MPC_E_INVAL;
@@ -1501,14 +1561,12 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
     for (int j = 0; j < i; ++j)
       if (overlap(bufs[i], ns[i], bufs[j], ns[j])) return MPC_E_ALIAS;
 
-  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, K);
+  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, K, kind == MPC_TRIPLE_CONV1D ? &cs : nullptr);
   const Epilogue ep = make_ep(t->c0, -1, 0, t->c1, view);
   // the left factor is a (matmul) or the weight b (conv); the right one b or im2col(a)
   const u64 *L0 = kind == MPC_TRIPLE_MATMUL ? t->a0 : t->b0, *L1 = kind == MPC_TRIPLE_MATMUL ? t->a1 : t->b1;
   const u64 *R0 = kind == MPC_TRIPLE_MATMUL ? t->b0 : t->a0, *R1 = kind == MPC_TRIPLE_MATMUL ? t->b1 : t->a1;
-  JobSpec jl = left_job(M, K, K), jr = kind == MPC_TRIPLE_MATMUL ? right_job(K, N, N) : im2col_job(cs, lout);
-  set_mode(jl, kModeSum2, {L0, L1});
-  set_mode(jr, kModeSum2, {R0, R1});
+  const bool conv = kind == MPC_TRIPLE_CONV1D;
   // In a packing form a matrix operand's shares are drawn inside its pack
   // (each element is packed exactly once), so they are written once and never
   // read back; an im2col operand (overlapping windows, possibly uncovered
@@ -1519,11 +1577,19 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
   u64* Rs[2] = {a_left ? t->b0 : t->a0, a_left ? t->b1 : t->a1};
   const int Lslot = a_left ? kSlotA0 : kSlotB0, Rslot = a_left ? kSlotB0 : kSlotA0;
   const bool fuse_r = limb && kind == MPC_TRIPLE_MATMUL;
-  if (limb) set_prg_sum2(jl, key[Lslot], key[Lslot + 1], Ls[0], Ls[1]);
-  if (fuse_r) set_prg_sum2(jr, key[Rslot], key[Rslot + 1], Rs[0], Rs[1]);
+  auto ops = [&](Form f) {
+    const bool direct = conv && f == kFormResidue && conv_direct(cs);
+    std::array<JobSpec, 2> j{direct ? conv_weight_job(cs) : left_job(M, K, K),
+                             !conv ? right_job(K, N, N) : direct ? conv_chan_job(cs) : im2col_job(cs, lout)};
+    set_prg_sum2(j[0], key[Lslot], key[Lslot + 1], Ls[0], Ls[1]);
+    if (fuse_r) set_prg_sum2(j[1], key[Rslot], key[Rslot + 1], Rs[0], Rs[1]);
+    else set_mode(j[1], kModeSum2, {R0, R1});
+    return j;
+  };
   CHK(ensure_packing_ws(c, &form, [&](Form f) {
-    return kAlign + (packs(f) ? job_bytes(jl, f) + job_bytes(jr, f) : kind == MPC_TRIPLE_CONV1D ? align_up((size_t)(K * N) * 8) : 0) +
-           (f == kFormResidue ? res_out_bytes(M, N, K, 0) : 0);
+    if (!packs(f)) return kAlign + (conv ? align_up((size_t)(K * N) * 8) : 0);
+    const auto j = ops(f);
+    return kAlign + job_bytes(j[0], f) + job_bytes(j[1], f) + (f == kFormResidue ? res_out_bytes(M, N, j[0].K, 0) : 0);
   }));
   const size_t nl = a_left ? na : nb, nr = a_left ? nb : na;
   if (!limb) {
@@ -1541,8 +1607,11 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
   if (nc) {
     Carve cv(c->ws);
     if (packs(form)) {
-      std::vector<PackJob> jobs{place_job(jl, cv, form), place_job(jr, cv, form)};
-      CHK(issue_packed(c, form, cv, jobs, {limb_req(M, N, K, 0, jobs[0].dst[0], nullptr, jobs[1].dst[0], nullptr, ep)}));
+      const auto j = ops(form);
+      std::vector<PackJob> jobs{place_job(j[0], cv, form), place_job(j[1], cv, form)};
+      std::vector<LimbReq> reqs{limb_req(M, N, j[0].K, 0, jobs[0].dst[0], nullptr, jobs[1].dst[0], nullptr, ep)};
+      if (j[1].kind == kPackChan) reqs[0].cv = conv_geometry(cs);
+      CHK(issue_packed(c, form, cv, jobs, reqs));
     } else if (kind == MPC_TRIPLE_MATMUL) {
       CHK(issue_plain(c, {plain_problem(M, N, K, 0, L0, L1, K, nullptr, 0, R0, R1, N, nullptr, 0, ep)}));
     } else {
@@ -2064,22 +2133,32 @@ mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const ui
   // transposed orientation: z_p[b][o][l] is element (o, b*Lout + l) of
   //   c_p + Wm(b_p) @ im2col(eps) + Wm(delta) @ im2col(g_p),  g_0 = a_0 + eps, g_1 = a_1
   const i64 M = s.cout, N = s.batch * lout, K = s.cin * s.ksize;
-  Form form = resolve_form(want, M, N, 2 * K, K);
+  Form form = resolve_form(want, M, N, 2 * K, K, &s);
   CHK(check_limb_k(form, K));
   const OutView view{lout, std::max<i64>(lout, 1), s.cout * lout};
   if (packs(form)) {
-    JobSpec jw = left_job(M, K, K), jx = im2col_job(s, lout);
-    open_right(jw, w0, w1, t->b0, t->b1);  // delta, b0, b1 (weights)
-    open_left(jx, x0, x1, t->a0, t->a1);   // im2col of eps, g0, a1 (activations)
+    // delta, b0, b1 (weights); im2col of eps, g0, a1 (activations), or in the
+    // residue form the activations themselves
+    auto ops = [&](Form f) {
+      const bool direct = f == kFormResidue && conv_direct(s);
+      std::array<JobSpec, 2> j{direct ? conv_weight_job(s) : left_job(M, K, K), direct ? conv_chan_job(s) : im2col_job(s, lout)};
+      open_right(j[0], w0, w1, t->b0, t->b1);
+      open_left(j[1], x0, x1, t->a0, t->a1);
+      return j;
+    };
     CHK(ensure_packing_ws(c, &form, [&](Form f) {
-      return kAlign + job_bytes(jw, f) + job_bytes(jx, f) + (f == kFormResidue ? 2 * res_out_bytes(M, N, K, K) : 0);
+      const auto j = ops(f);
+      return kAlign + job_bytes(j[0], f) + job_bytes(j[1], f) + (f == kFormResidue ? 2 * res_out_bytes(M, N, j[0].K, j[0].K) : 0);
     }));
     Carve cv(c->ws);
-    const PackJob W = place_job(jw, cv, form), X = place_job(jx, cv, form);
+    const auto j = ops(form);
+    const PackJob W = place_job(j[0], cv, form), X = place_job(j[1], cv, form);
     std::vector<LimbReq> reqs;
-    for (int p = 0; p < 2; ++p)
-      reqs.push_back(limb_req(M, N, K, K, W.dst[p == 0 ? 1 : 2], W.dst[0], X.dst[0], X.dst[p == 0 ? 1 : 2],
+    for (int p = 0; p < 2; ++p) {
+      reqs.push_back(limb_req(M, N, j[0].K, j[0].K, W.dst[p == 0 ? 1 : 2], W.dst[0], X.dst[0], X.dst[p == 0 ? 1 : 2],
                               make_ep(p == 0 ? t->c0 : t->c1, +1, trunc_bits, p == 0 ? z0 : z1, view)));
+      if (j[1].kind == kPackChan) reqs.back().cv = conv_geometry(s);
+    }
     CHK(issue_packed(c, form, cv, {W, X}, reqs));
   } else {
     // plain and fp64 limb forms: open, then im2col of eps, g_0 and a_1 into

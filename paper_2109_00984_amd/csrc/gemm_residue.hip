@@ -224,26 +224,63 @@ __global__ void __launch_bounds__(kPackThreads) k_res_pack(PackTables) {
   const PackView tv = pack_view();
   const cptr<i64> block_start = tv.bstart;
   const int njobs = tv.njobs;
-  __shared__ u64 tile[4][KIND == kPackRow ? 16 * kResTPad : 1];
+  __shared__ u64 tile[4][KIND == kPackRow || KIND == kPackConvRow ? 16 * kResTPad : 1];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const i64 blk = (i64)blockIdx.x * 4 + wave;
-  if (blk >= block_start[njobs]) return;  // whole wave leaves; only wave-level sync below
+  // (CONV_ROW: neighbouring workgroups share lines, so an XCD takes runs of
+  // them: 0.33 ms for a 2000 x 250 x 32 weight, 0.46 without)
+  const i64 blk = (i64)(KIND == kPackConvRow ? remap_tile(blockIdx.x, gridDim.x, 32) : (int)blockIdx.x) * 4 + wave;
+  // A whole wave leaves; only CONV_ROW, whose units come in whole workgroups, syncs beyond the wave.
+  if (blk >= block_start[njobs]) return;
   const int ji = find_job(block_start, njobs, blk);
   const PackJob jb = tv.jobs[ji];
   const i64 local = blk - block_start[ji];
   // the waves of a workgroup take neighbouring blocks along the operand's rows in memory
-  const i64 rb = KIND == kPackRow ? local / jb.kblocks : local % jb.rreal;
-  const i64 kb = KIND == kPackRow ? local % jb.kblocks : local / jb.rreal;
+  constexpr bool left = KIND == kPackRow || KIND == kPackConvRow;
+  const i64 rb = left ? local / jb.kblocks : local % jb.rreal;
+  const i64 kb = left ? local % jb.kblocks : local / jb.rreal;
   const i64 plane = jb.rblocks * jb.kblocks * kResBlockBytes;
-  const size_t boff = (size_t)(rb * jb.kblocks + kb) * kResBlockBytes + (size_t)lane * 16;
+  size_t boff = (size_t)(rb * jb.kblocks + kb) * kResBlockBytes + (size_t)lane * 16;
 
   i64 off[16];
-  bool ok[16];
-  res_offsets<KIND>(jb, rb, kb, lane, off, ok);
+  bool ok[16], interior, skip = false;
+  if constexpr (KIND == kPackChan) {
+    // 16 channels of 64 neighbouring positions, one position per lane: the four
+    // waves of a workgroup take the quarters of one 64-channel group
+    const i64 groups = (jb.cin + 63) / 64, runs = (jb.len + 63) / 64;
+    const i64 quarter = local % 4, run = local / 4 % runs, bg = local / 4 / runs, g = bg % groups, b = bg / groups;
+    const i64 pos = run * 64 + lane, c0 = g * 64 + quarter * 16;
+    if (pos >= jb.len) return;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      ok[q] = c0 + q < jb.cin;
+      off[q] = (b * jb.cin + c0 + q) * jb.len + pos;
+    }
+    interior = c0 + 16 <= jb.cin;
+    boff = (size_t)((bg * jb.len + pos) * 64 + quarter * 16);
+  } else if constexpr (KIND == kPackConvRow) {
+    // A workgroup packs 16 rows x 64 channels x 4 taps, wave w the block of tap
+    // w.  Loads run along the taps, as the weight does, and turn through LDS: a
+    // 2000 x 250 x 32 weight takes 0.33 ms (reading in packed order, which uses
+    // 8 bytes of each line, 0.65; writing from that order in 16-byte pieces 0.54).
+    const i64 chunks = (jb.ksz + 3) / 4, groups = (jb.cin + 63) / 64, rg = local / 4 / chunks;
+    const i64 tap0 = local / 4 % chunks * 4, g = rg % groups, rb16 = rg / groups;
+    const i64 c = g * 64 + (threadIdx.x >> 2), j = tap0 + (threadIdx.x & 3);
+    const bool in = c < jb.cin && j < jb.ksz;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      ok[q] = in && rb16 * 16 + q < jb.rows;
+      off[q] = (rb16 * 16 + q) * jb.ld + c * jb.ksz + j;
+    }
+    interior = (rb16 + 1) * 16 <= jb.rows && (g + 1) * 64 <= jb.cin && tap0 + 4 <= jb.ksz;
+    skip = tap0 + wave >= jb.ksz;
+    boff = (size_t)((rb16 * jb.kblocks + g * jb.ksz + tap0 + wave) * kResBlockBytes + lane * 16);
+  } else {
+    res_offsets<KIND>(jb, rb, kb, lane, off, ok);
+    interior = (rb + 1) * 16 <= jb.rows && (kb + 1) * 64 <= jb.K;
+  }
   gcu64* in[Md::nin];
 #pragma unroll
   for (int i = 0; i < Md::nin; ++i) in[i] = gptr(jb.in[i]);
-  const bool interior = (rb + 1) * 16 <= jb.rows && (kb + 1) * 64 <= jb.K;
   u64 v[16][Md::nin];
   if constexpr (MODE == kModePrgSum2) {
 #pragma unroll
@@ -279,7 +316,16 @@ __global__ void __launch_bounds__(kPackThreads) k_res_pack(PackTables) {
       for (int q = 0; q < 16; ++q) w[q] = t[(lane & 15) * kResTPad + (lane >> 4) * 16 + q];
       __builtin_amdgcn_wave_barrier();
     }
-    write_residues<KIND != kPackRow>(jb.dst[o] + boff, plane, w);
+    if constexpr (KIND == kPackConvRow) {
+      u64* t = &tile[0][0];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) t[((threadIdx.x & 3) * 16 + q) * kResTPad + (threadIdx.x >> 2)] = w[q];
+      __syncthreads();
+#pragma unroll
+      for (int q = 0; q < 16; ++q) w[q] = t[(wave * 16 + (lane & 15)) * kResTPad + (lane >> 4) * 16 + q];
+      __syncthreads();
+    }
+    if (!skip) write_residues<!left>(jb.dst[o] + boff, plane, w);
   }
 }
 
@@ -346,33 +392,54 @@ __device__ __forceinline__ void step_barrier() {
 }
 
 // One wave's copies: CA neighbouring strips of the left operand and CB of the
-// right one, 1 KiB each per step.  The second segment's pointers are moved back
-// by one segment, so that block kg of the concatenation is at kg KiB of either.
+// right one, 1 KiB each per step.  The second segment's left pointer is moved
+// back by one segment, so that block kg of the concatenation is at kg KiB of
+// either; so is the right one's, unless it is a convolution's activation, whose
+// steps follow its channel groups and taps.
+template <class G, bool CONV>
 struct CopySrc {
-  const uint8_t *a0, *a1, *b0, *b1;  // first strip of each operand in segment 0 and 1
+  const uint8_t *a0, *a1, *b0, *b1;  // first strip (or plane) of each operand in segment 0 and 1
   int kbs;                           // blocks per segment
+  int kg, kend;                      // the next block to copy, and the end of the tile's
+  int tap, boff, ksz, wrap;          // CONV: the block's tap, its offset, and the step back to the next group's tap 0
+  unsigned vb[CONV ? G::CB : 1];     // CONV: this lane's bytes in each strip's columns
 };
 // The copies of one step.
 struct Copies {
   const uint8_t *a, *b;
-  int n;     // bytes that the descriptors cover: past the last step 0, and the loads return zeros without a fetch
-  int off;   // kg KiB
-  int next;  // from strip to strip, less the 1 KiB that the instruction's offset adds on both sides
+  int n;            // bytes that the descriptors cover: past the last step 0, and the loads return zeros without a fetch
+  int aoff, boff;   // the block's offsets
+  int next;         // from strip to strip, less the 1 KiB that the instruction's offset adds on both sides
 };
-__device__ __forceinline__ Copies copies_of(const CopySrc& s, int kg, bool live) {
-  const bool seg0 = kg < s.kbs;
-  return Copies{seg0 ? s.a0 : s.a1, seg0 ? s.b0 : s.b1, live ? 0x7fffffff : 0, kg * kResBlockBytes, (s.kbs - 1) * kResBlockBytes};
+template <class G, bool CONV>
+__device__ __forceinline__ Copies next_copies(CopySrc<G, CONV>& s) {
+  const bool seg0 = s.kg < s.kbs;
+  const Copies c{seg0 ? s.a0 : s.a1, seg0 ? s.b0 : s.b1, s.kg < s.kend ? 0x7fffffff : 0, s.kg * kResBlockBytes,
+                 CONV ? s.boff : s.kg * kResBlockBytes, (s.kbs - 1) * kResBlockBytes};
+  ++s.kg;
+  if constexpr (CONV) {
+    const bool last = ++s.tap == s.ksz;
+    s.boff += last ? s.wrap : 64;
+    s.tap = last ? 0 : s.tap;
+    s.boff = s.kg == s.kbs ? 0 : s.boff;
+  }
+  return c;
 }
 // Copy J of a wave's step: the immediate offset moves source and destination
 // alike, so up to four strips share one LDS base.
-template <class G, int J>
-__device__ __forceinline__ void copy_one(const Copies& c, lds_u8* buf, int wave, unsigned lane16) {
+template <class G, bool CONV, int J>
+__device__ __forceinline__ void copy_one(const CopySrc<G, CONV>& s, const Copies& c, lds_u8* buf, int wave, unsigned lane16) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the host pass only parses the kernels
+  using lds_void = __attribute__((address_space(3))) void;
   constexpr bool left = J < G::CA;
   constexpr int q = left ? J : J - G::CA;
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)(left ? c.a : c.b), 0, c.n, kBufferWord3);
   lds_u8* base = buf + (left ? wave * G::CA : G::SA + wave * G::CB) * kResBlockBytes;
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)base, 16, lane16, c.off + q * c.next,
-                                           q * kResBlockBytes, 0);
+  if constexpr (CONV && !left)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(base + q * kResBlockBytes), 16, s.vb[q], c.boff, 0, 0);
+  else
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)base, 16, lane16, (left ? c.aoff : c.boff) + q * c.next, q * kResBlockBytes, 0);
+#endif
 }
 
 template <class G>
@@ -381,7 +448,9 @@ struct RFrags {
 };
 
 // What one step touches besides its accumulators and fragments.
+template <class G, bool CONV>
 struct RStep {
+  const CopySrc<G, CONV>& src;
   Copies c;
   const lds_u8 *ra, *rb;  // the next step's fragments
   lds_u8* wbuf;        // where the copies go
@@ -390,8 +459,8 @@ struct RStep {
 };
 
 // MFMA number I of a step and what follows it.
-template <class G, bool FIRST, int I>
-__device__ __forceinline__ void res_mfma(v4i (&acc)[G::HA][G::HB], const RFrags<G>& cur, RFrags<G>& nxt, const RStep& st) {
+template <class G, bool CONV, bool FIRST, int I>
+__device__ __forceinline__ void res_mfma(v4i (&acc)[G::HA][G::HB], const RFrags<G>& cur, RFrags<G>& nxt, const RStep<G, CONV>& st) {
   constexpr int HA = G::HA, HB = G::HB;
   if constexpr (I < G::kNM) {
     constexpr int x = I / HB, y = I % HB;
@@ -413,10 +482,10 @@ __device__ __forceinline__ void res_mfma(v4i (&acc)[G::HA][G::HB], const RFrags<
       }(), ...);
     }(std::make_integer_sequence<int, G::reads_upto(I) - r0>{});
     [&]<int... Q>(std::integer_sequence<int, Q...>) {
-      (copy_one<G, c0 + Q>(st.c, st.wbuf, st.wave, st.lane16), ...);
+      (copy_one<G, CONV, c0 + Q>(st.src, st.c, st.wbuf, st.wave, st.lane16), ...);
     }(std::make_integer_sequence<int, G::copies_upto(I) - c0>{});
     __builtin_amdgcn_sched_barrier(0);
-    res_mfma<G, FIRST, I + 1>(acc, cur, nxt, st);
+    res_mfma<G, CONV, FIRST, I + 1>(acc, cur, nxt, st);
   }
 }
 
@@ -457,32 +526,53 @@ __device__ __forceinline__ ResPos res_pos(const ResView& tv, int idx) {
   return q;
 }
 
-template <class G>
-__device__ __forceinline__ CopySrc res_source(cptr<ResProblem> pp, const ResPos& q, int wave) {
-  CopySrc c;
+template <class G, bool CONV>
+__device__ __forceinline__ CopySrc<G, CONV> res_source(cptr<ResProblem> pp, const ResPos& q, int wave, int lane) {
+  CopySrc<G, CONV> c;
   c.kbs = pp->kbs;
+  c.kg = pp->kb_begin;
+  c.kend = pp->kb_end;
   const i64 seg = (i64)c.kbs * kResBlockBytes;  // one strip's bytes in a segment
-  const i64 oa = q.mi * pp->pa + ((i64)q.tm * G::SA + wave * G::CA) * seg, ob = q.mi * pp->pb + ((i64)q.tn * G::SB + wave * G::CB) * seg;
+  const i64 oa = q.mi * pp->pa + ((i64)q.tm * G::SA + wave * G::CA) * seg;
   c.a0 = pp->PA0 + oa;
   c.a1 = pp->PA1 + oa - seg;
-  c.b0 = pp->PB0 + ob;
-  c.b1 = pp->PB1 + ob - seg;
+  if constexpr (CONV) {
+    c.b0 = pp->PB0 + q.mi * pp->pb;
+    c.b1 = pp->PB1 + q.mi * pp->pb;
+    const cptr<ResConv> cv = &pp->cv;
+    const int ksz = cv->ksz, len = cv->len, kk = c.kg < c.kbs ? c.kg : c.kg - c.kbs;
+    c.ksz = ksz;
+    c.wrap = (len - ksz + 1) * 64;
+    c.tap = kk % ksz;
+    c.boff = (kk / ksz * len + c.tap) * 64;
+#pragma unroll
+    for (int j = 0; j < G::CB; ++j) {
+      // columns past the product's read its last one
+      const int n = min((q.tn * G::SB + wave * G::CB + j) * 16 + (lane & 15), cv->n - 1);
+      const int b = n / cv->lout, l = n % cv->lout;
+      c.vb[j] = (unsigned)((b * cv->groups * len + l * cv->stride) * 64 + (lane >> 4) * 16);
+    }
+  } else {
+    const i64 ob = q.mi * pp->pb + ((i64)q.tn * G::SB + wave * G::CB) * seg;
+    c.b0 = pp->PB0 + ob;
+    c.b1 = pp->PB1 + ob - seg;
+  }
   return c;
 }
 
 // The copies of a tile's first kAhead steps.
-template <class G>
-__device__ __forceinline__ void res_prefetch(const CopySrc& src, int kbeg, int nsteps, lds_u8* lds, int wave, unsigned lane16) {
+template <class G, bool CONV>
+__device__ __forceinline__ void res_prefetch(CopySrc<G, CONV>& src, lds_u8* lds, int wave, unsigned lane16) {
 #pragma unroll
   for (int s = 0; s < G::kAhead; ++s) {
-    const Copies c = copies_of(src, kbeg + s, s < nsteps);
+    const Copies c = next_copies(src);
     [&]<int... J>(std::integer_sequence<int, J...>) {
-      (copy_one<G, J>(c, lds + s * G::kStepBytes, wave, lane16), ...);
+      (copy_one<G, CONV, J>(src, c, lds + s * G::kStepBytes, wave, lane16), ...);
     }(std::make_integer_sequence<int, G::kCopies>{});
   }
 }
 
-template <class G>
+template <class G, bool CONV>
 __global__ void __launch_bounds__(256, G::kPerCU) k_res_gemm(ResGemmTables) {
   constexpr int HA = G::HA, HB = G::HB;
   __shared__ v4i lds_words[G::kDepth * G::kStepBytes / 16];
@@ -495,9 +585,9 @@ __global__ void __launch_bounds__(256, G::kPerCU) k_res_gemm(ResGemmTables) {
   const unsigned roff_a = wr * HA * kResBlockBytes + lane16, roff_b = (G::SA + wc * HB) * kResBlockBytes + lane16;
   ResPos pos = res_pos<G>(tv, blockIdx.x);
   cptr<ResProblem> pp = tv.probs + pos.pi;
-  CopySrc src = res_source<G>(pp, pos, wave);
-  int kbeg = pp->kb_begin, nsteps = pp->kb_end - kbeg;
-  res_prefetch<G>(src, kbeg, nsteps, lds, wave, lane16);
+  CopySrc<G, CONV> src = res_source<G, CONV>(pp, pos, wave, lane);
+  int nsteps = pp->kb_end - pp->kb_begin;
+  res_prefetch(src, lds, wave, lane16);
   for (int idx = blockIdx.x;;) {
     v4i acc[HA][HB];
     // step 0's copies (and the previous tile's stores: loads and stores share the counter)
@@ -515,8 +605,8 @@ __global__ void __launch_bounds__(256, G::kPerCU) k_res_gemm(ResGemmTables) {
       auto step = [&]<bool FIRST>(int s, const RFrags<G>& cur, RFrags<G>& nxt) {
         lds_u8* rbuf = lds + ((s + 1) % G::kDepth) * G::kStepBytes;
         lds_u8* wbuf = lds + ((s + G::kAhead) % G::kDepth) * G::kStepBytes;
-        const int sc = s + G::kAhead;
-        res_mfma<G, FIRST, 0>(acc, cur, nxt, RStep{copies_of(src, kbeg + sc, sc < nsteps), rbuf + roff_a, rbuf + roff_b, wbuf, wave, lane16});
+        const Copies c = next_copies(src);
+        res_mfma<G, CONV, FIRST, 0>(acc, cur, nxt, RStep<G, CONV>{src, c, rbuf + roff_a, rbuf + roff_b, wbuf, wave, lane16});
       };
       step.template operator()<true>(0, f0, f1);
       int s = 1;
@@ -541,10 +631,9 @@ __global__ void __launch_bounds__(256, G::kPerCU) k_res_gemm(ResGemmTables) {
       // the next tile's first steps travel during this one's epilogue
       pos = res_pos<G>(tv, idx);
       pp = tv.probs + pos.pi;
-      src = res_source<G>(pp, pos, wave);
-      kbeg = pp->kb_begin;
-      nsteps = pp->kb_end - kbeg;
-      res_prefetch<G>(src, kbeg, nsteps, lds, wave, lane16);
+      src = res_source<G, CONV>(pp, pos, wave, lane);
+      nsteps = pp->kb_end - pp->kb_begin;
+      res_prefetch(src, lds, wave, lane16);
     }
     // wait states between the last MFMAs and the reads of their results
 #pragma unroll
@@ -737,6 +826,10 @@ hipError_t launch_res_pack(hipStream_t s, const PackTables& t, i64 total_blocks,
   MPC_PACK_CASE(kPackCol, kModeCopy)
   MPC_PACK_CASE(kPackCol, kModeOpenRight)
   MPC_PACK_CASE(kPackCol, kModePrgSum2)
+  MPC_PACK_CASE(kPackConvRow, kModeOpenRight)
+  MPC_PACK_CASE(kPackConvRow, kModePrgSum2)
+  MPC_PACK_CASE(kPackChan, kModeSum2)
+  MPC_PACK_CASE(kPackChan, kModeOpenLeft)
   MPC_PACK_CASE(kPackIm2col, kModeSum2)
   MPC_PACK_CASE(kPackIm2col, kModeOpenLeft)
 #undef MPC_PACK_CASE
@@ -748,18 +841,24 @@ int res_tile_per_cu(int tile) {
   return per[tile];
 }
 
-hipError_t launch_res_gemm(hipStream_t s, const ResGemmTables& tables, int total_tiles, int tile, int grid) {
+hipError_t launch_res_gemm(hipStream_t s, const ResGemmTables& tables, int total_tiles, int tile, int grid, bool conv) {
   if (total_tiles <= 0) return hipSuccess;
   if (grid < 1 || grid > total_tiles) return hipErrorInvalidValue;
   ResGemmTables t = tables;
   t.tiles = total_tiles;
+#define MPC_RES_CASE(T, G)                                                                      \
+  case T:                                                                                       \
+    if (conv) hipLaunchKernelGGL((k_res_gemm<G, true>), dim3(grid), dim3(256), 0, s, t);        \
+    else hipLaunchKernelGGL((k_res_gemm<G, false>), dim3(grid), dim3(256), 0, s, t);            \
+    break;
   switch (tile) {
-    case kRes256x256: hipLaunchKernelGGL(k_res_gemm<R256x256>, dim3(grid), dim3(256), 0, s, t); break;
-    case kRes256x128: hipLaunchKernelGGL(k_res_gemm<R256x128>, dim3(grid), dim3(256), 0, s, t); break;
-    case kRes128x256: hipLaunchKernelGGL(k_res_gemm<R128x256>, dim3(grid), dim3(256), 0, s, t); break;
-    case kRes128x128: hipLaunchKernelGGL(k_res_gemm<R128x128>, dim3(grid), dim3(256), 0, s, t); break;
+    MPC_RES_CASE(kRes256x256, R256x256)
+    MPC_RES_CASE(kRes256x128, R256x128)
+    MPC_RES_CASE(kRes128x256, R128x256)
+    MPC_RES_CASE(kRes128x128, R128x128)
     default: return hipErrorInvalidValue;
   }
+#undef MPC_RES_CASE
   return hipGetLastError();
 }
 

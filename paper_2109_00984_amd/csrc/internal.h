@@ -101,7 +101,11 @@ constexpr int kLimbRowPad = 4;
 //   kind COL:    right operand KxN, in[k*ld + r]  (r is the column)
 //   kind IM2COL: right operand, k = c*ksz + j, n = b*Lout + l, element
 //                in[b][c][l*stride + j] of a [B][Cin][L] activation
-enum PackKind : int { kPackRow = 0, kPackCol = 1, kPackIm2col = 2 };
+// The residue form lowers a convolution without im2col (ResConv below):
+//   kind CONV_ROW: left operand M = Cout, in[m][c][j] of a [Cout][Cin][ksz]
+//                  weight at k = ((c / 64) * ksz + j) * 64 + c % 64
+//   kind CHAN:     the [B][Cin][L] activation itself, channels last
+enum PackKind : int { kPackRow = 0, kPackCol = 1, kPackIm2col = 2, kPackConvRow = 3, kPackChan = 4 };
 // kModePrgSum2 draws the two inputs from the PRG instead of reading them:
 // element e (its row-major offset) gets v_i = G(key[i], e), which is also
 // written to share[i][e]; the packed output is v_0 + v_1.  Used by the
@@ -133,6 +137,7 @@ struct PackJob {
   // tiles but only reach outputs past the last row or column, which are never
   // stored.  (All kblocks are written: zeros past K enter every output.)
   i64 rreal;
+  i64 units;     // waves that the job takes (rreal * kblocks blocks, unless its kind says otherwise)
   u64 key[2];    // kModePrgSum2: PRG stream keys of the two shares
   u64* share[2];  // kModePrgSum2: where the two shares are written
 };
@@ -276,7 +281,7 @@ hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceJob* jobs, co
 // kernel-argument segment, as constant memory.
 constexpr int kInlineJobs = 4, kInlineProbs = 4;
 // Jobs of one pack launch: `jobs`/`block_start` (device; njobs+1 prefix sums
-// of rreal*kblocks), or when `jobs` is null the first njobs entries of
+// of their units), or when `jobs` is null the first njobs entries of
 // ijobs/ibstart.  Every job of one launch has the launch's kind and mode.
 struct PackTables {
   const PackJob* jobs;
@@ -339,6 +344,14 @@ i64 res_kblocks(i64 K);     // 64-wide k blocks
 // through one 32-bit buffer descriptor.
 constexpr i64 kResMaxSegK = (i64)65536 * 64;
 
+// A convolution's right operand: the activation's planes are
+// [B][ceil(Cin / 64)][L][64] bytes, channels last in groups of 64, so that
+// column n = (b, l) of im2col is, for channel group g and tap j, the 64 bytes at
+// ((b * groups + g) * L + l * stride + j) * 64, and a k step (g, j) of 16
+// columns of one batch row is one run of 1 KiB at stride 1.  ksz = 0: none.
+struct ResConv {
+  int ksz, groups, len, stride, lout, n;  // n: columns
+};
 // One chunk of k of one product: blocks [kb_begin, kb_end) of the
 // concatenation [segment 0 | segment 1] of kbs blocks each, at most
 // kResMaxKBlocks of them.  Its
@@ -353,6 +366,7 @@ struct ResProblem {
   int n64;                 // units per row of units
   uint8_t* R;
   i64 pr;                  // plane stride of R
+  ResConv cv;
 };
 // The combine of one product: residues of nch chunks -> ring elements -> epilogue.
 struct ResOut {
@@ -383,8 +397,8 @@ void res_tile_shape(int tile, int* bm, int* bn);
 int res_tile_per_cu(int tile);  // workgroups per compute unit
 struct PackTables;
 hipError_t launch_res_pack(hipStream_t s, const PackTables& t, i64 total_blocks, int kind, int mode);
-// grid <= total_tiles workgroups take tiles b, b + grid, ...
-hipError_t launch_res_gemm(hipStream_t s, const ResGemmTables& t, int total_tiles, int tile, int grid);
+// grid <= total_tiles workgroups take tiles b, b + grid, ...; conv: every problem's right operand is a ResConv
+hipError_t launch_res_gemm(hipStream_t s, const ResGemmTables& t, int total_tiles, int tile, int grid, bool conv);
 hipError_t launch_res_combine(hipStream_t s, const ResOutTables& t, i64 total_units);
 
 // ---------------------------------------------------------------- binary sharing (two parties)

@@ -127,7 +127,9 @@ def test_small_workspace_falls_back(m):
     c.close()
 
 
-@pytest.mark.parametrize("B,cin,L,cout,k,s", [(4, 60, 320, 1100, 40, 1), (8, 80, 300, 1030, 31, 2)])
+@pytest.mark.parametrize("B,cin,L,cout,k,s", [(4, 60, 320, 1100, 40, 1), (8, 80, 300, 1030, 31, 2),  # im2col and channels-last forms
+                                                (3, 250, 777, 250, 7, 1), (5, 130, 901, 129, 6, 2), (2, 192, 600, 600, 9, 3),
+                                                (1, 52, 5000, 141, 31, 1), (2, 250, 200, 2000, 32, 1), (3, 64, 1030, 400, 45, 1)])
 def test_conv_matches_plain(m, c, B, cin, L, cout, k, s):
     say(f"residue conv {B}x{cin}x{L} -> {cout}, k {k} stride {s}")
     x, w = c.share(dev(rnd(1, (B, cin, L))), 0, 1), c.share(dev(rnd(2, (cout, cin, k))), 1, 2)
@@ -136,7 +138,7 @@ def test_conv_matches_plain(m, c, B, cin, L, cout, k, s):
     assert same(z, p)
     a, b = host(c, t.a0 + t.a1), host(c, t.b0 + t.b1)
     lout = (L - k) // s + 1
-    bs, os_, ls = np.array([0, B - 1, 1]), np.array([0, cout - 1, cout // 2]), np.array([0, lout - 1, lout // 2])
+    bs, os_, ls = np.array([0, B - 1, B // 2]), np.array([0, cout - 1, cout // 2]), np.array([0, lout - 1, lout // 2])
     assert np.array_equal(host(c, t.c0 + t.c1)[bs, os_, ls], oracle.conv1d_at(a, b, s, bs, os_, ls))
 
 
