@@ -219,21 +219,9 @@ __device__ __forceinline__ void write_residues(uint8_t* dst, i64 plane, const u6
 // lanes along a row and transposed through LDS, right ones in packed order (16
 // lanes along n: whole 128-byte lines).
 template <int KIND, int MODE>
-__global__ void __launch_bounds__(kPackThreads) k_res_pack(PackTables) {
+__device__ __forceinline__ void res_pack_block(const PackJob& jb, i64 local, u64* tiles, int wave, int lane) {
   using Md = Mode<MODE>;
-  const PackView tv = pack_view();
-  const cptr<i64> block_start = tv.bstart;
-  const int njobs = tv.njobs;
-  __shared__ u64 tile[4][KIND == kPackRow || KIND == kPackConvRow ? 16 * kResTPad : 1];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  // (CONV_ROW: neighbouring workgroups share lines, so an XCD takes runs of
-  // them: 0.33 ms for a 2000 x 250 x 32 weight, 0.46 without)
-  const i64 blk = (i64)(KIND == kPackConvRow ? remap_tile(blockIdx.x, gridDim.x, 32) : (int)blockIdx.x) * 4 + wave;
-  // A whole wave leaves; only CONV_ROW, whose units come in whole workgroups, syncs beyond the wave.
-  if (blk >= block_start[njobs]) return;
-  const int ji = find_job(block_start, njobs, blk);
-  const PackJob jb = tv.jobs[ji];
-  const i64 local = blk - block_start[ji];
+  u64* tile = tiles + wave * 16 * kResTPad;
   // the waves of a workgroup take neighbouring blocks along the operand's rows in memory
   constexpr bool left = KIND == kPackRow || KIND == kPackConvRow;
   const i64 rb = left ? local / jb.kblocks : local % jb.rreal;
@@ -308,7 +296,7 @@ __global__ void __launch_bounds__(kPackThreads) k_res_pack(PackTables) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) w[q] = Md::out(o, v[q]);
     if constexpr (KIND == kPackRow) {
-      u64* t = tile[wave];
+      u64* t = tile;
 #pragma unroll
       for (int q = 0; q < 16; ++q) t[q * kResTPad + lane] = w[q];
       __builtin_amdgcn_wave_barrier();
@@ -317,7 +305,7 @@ __global__ void __launch_bounds__(kPackThreads) k_res_pack(PackTables) {
       __builtin_amdgcn_wave_barrier();
     }
     if constexpr (KIND == kPackConvRow) {
-      u64* t = &tile[0][0];
+      u64* t = tiles;
 #pragma unroll
       for (int q = 0; q < 16; ++q) t[((threadIdx.x & 3) * 16 + q) * kResTPad + (threadIdx.x >> 2)] = w[q];
       __syncthreads();
@@ -327,6 +315,32 @@ __global__ void __launch_bounds__(kPackThreads) k_res_pack(PackTables) {
     }
     if (!skip) write_residues<!left>(jb.dst[o] + boff, plane, w);
   }
+}
+
+// One launch packs both operands of a call.
+template <int... KM>
+__global__ void __launch_bounds__(kPackThreads) k_res_pack(PackTables, PackPairs<KM...>) {
+  using P = PackPairs<KM...>;
+  const PackView tv = pack_view();
+  const cptr<i64> start = tv.bstart;
+  const int njobs = tv.njobs;
+  __shared__ u64 tiles[P::has(kPackRow) || P::has(kPackConvRow) ? 4 * 16 * kResTPad : 1];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // (CONV_ROW: neighbouring workgroups share lines, so an XCD takes runs of
+  // them: 0.33 ms for a 2000 x 250 x 32 weight, 0.46 without)
+  const i64 unit = (i64)(P::has(kPackConvRow) ? remap_tile(blockIdx.x, gridDim.x, 32) : (int)blockIdx.x) * 4 + wave;
+  // A whole wave leaves; only CONV_ROW, whose job comes first and in whole
+  // workgroups, syncs beyond the wave.
+  if (unit >= start[njobs]) return;
+  const int ji = find_job(start, njobs, unit);
+  const PackJob jb = tv.jobs[ji];
+  const int pair = km(jb.kind, jb.mode);
+  ((pair == KM ? res_pack_block<KM / 16, KM % 16>(jb, unit - start[ji], tiles, wave, lane) : (void)0), ...);
+}
+template <int... KM>
+hipError_t launch_res_pack_set(hipStream_t s, const PackTables& t, i64 units, PackPairs<KM...> pairs) {
+  hipLaunchKernelGGL((k_res_pack<KM...>), dim3((unsigned)((units + 3) / 4)), dim3(kPackThreads), 0, s, t, pairs);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ GEMM
@@ -810,30 +824,19 @@ void res_tile_shape(int tile, int* bm, int* bn) {
   *bn = cols[tile];
 }
 
-hipError_t launch_res_pack(hipStream_t s, const PackTables& t, i64 total_blocks, int kind, int mode) {
-  if (total_blocks <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((total_blocks + 3) / 4)), block(kPackThreads);
-#define MPC_PACK_CASE(K, MO)                                        \
-  if (kind == K && mode == MO) {                                    \
-    hipLaunchKernelGGL((k_res_pack<K, MO>), grid, block, 0, s, t);  \
-    return hipGetLastError();                                       \
+hipError_t launch_res_pack(hipStream_t s, const PackTables& t, i64 total_units, PackSet set) {
+  if (total_units <= 0) return hipSuccess;
+  switch (set) {
+    case kPackMatmul: return launch_res_pack_set(s, t, total_units, SetPairs<kPackMatmul>::T{});
+    case kPackConv: return launch_res_pack_set(s, t, total_units, SetPairs<kPackConv>::T{});
+    case kPackConvDirect: return launch_res_pack_set(s, t, total_units, SetPairs<kPackConvDirect>::T{});
+    case kPackDeal: return launch_res_pack_set(s, t, total_units, SetPairs<kPackDeal>::T{});
+    case kPackDealConv: return launch_res_pack_set(s, t, total_units, SetPairs<kPackDealConv>::T{});
+    case kPackDealConvDirect: return launch_res_pack_set(s, t, total_units, SetPairs<kPackDealConvDirect>::T{});
+    case kPackRing: return launch_res_pack_set(s, t, total_units, SetPairs<kPackRing>::T{});
+    case kPackParty: return launch_res_pack_set(s, t, total_units, SetPairs<kPackParty>::T{});
+    default: return hipErrorInvalidValue;
   }
-  MPC_PACK_CASE(kPackRow, kModeCopy)
-  MPC_PACK_CASE(kPackRow, kModeSum2)
-  MPC_PACK_CASE(kPackRow, kModeOpenLeft)
-  MPC_PACK_CASE(kPackRow, kModeOpenRight)
-  MPC_PACK_CASE(kPackRow, kModePrgSum2)
-  MPC_PACK_CASE(kPackCol, kModeCopy)
-  MPC_PACK_CASE(kPackCol, kModeOpenRight)
-  MPC_PACK_CASE(kPackCol, kModePrgSum2)
-  MPC_PACK_CASE(kPackConvRow, kModeOpenRight)
-  MPC_PACK_CASE(kPackConvRow, kModePrgSum2)
-  MPC_PACK_CASE(kPackChan, kModeSum2)
-  MPC_PACK_CASE(kPackChan, kModeOpenLeft)
-  MPC_PACK_CASE(kPackIm2col, kModeSum2)
-  MPC_PACK_CASE(kPackIm2col, kModeOpenLeft)
-#undef MPC_PACK_CASE
-  return hipErrorInvalidValue;
 }
 
 int res_tile_per_cu(int tile) {

@@ -279,10 +279,10 @@ hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceJob* jobs, co
 // arguments: then no upload (no copy on the stream, no host staging) precedes
 // the launch.  The kernels read whichever the host filled through the
 // kernel-argument segment, as constant memory.
-constexpr int kInlineJobs = 4, kInlineProbs = 4;
+constexpr int kInlineJobs = 12, kInlineProbs = 4;
 // Jobs of one pack launch: `jobs`/`block_start` (device; njobs+1 prefix sums
 // of their units), or when `jobs` is null the first njobs entries of
-// ijobs/ibstart.  Every job of one launch has the launch's kind and mode.
+// ijobs/ibstart.
 struct PackTables {
   const PackJob* jobs;
   const i64* block_start;
@@ -290,7 +290,13 @@ struct PackTables {
   PackJob ijobs[kInlineJobs];
   i64 ibstart[kInlineJobs + 1];
 };
-hipError_t launch_pack(hipStream_t s, const PackTables& t, i64 total_blocks, int kind, int mode);
+// The (kind, mode) pairs that the jobs of one call have: a call packs both its
+// operands in one launch, a kernel per set.
+enum PackSet : int {
+  kPackMatmul, kPackMatmulPre, kPackConv, kPackConvDirect, kPackDeal, kPackDealPre, kPackDealConv, kPackDealConvDirect,
+  kPackRing, kPackParty, kPackSets
+};
+hipError_t launch_pack(hipStream_t s, const PackTables& t, i64 total_units, PackSet set);
 // Tile shapes of the limb GEMM (workgroup output tile) and the tile order.
 // Variants 3..8 stage the outer operand through LDS (k_limb_gemm_lds); 6, 7
 // and 8 run eight waves per workgroup (two per SIMD): 6 and 7 with 16x64 and
@@ -395,8 +401,7 @@ struct ResOutTables {
 enum ResTile : int { kRes256x256 = 0, kRes256x128 = 1, kRes128x256 = 2, kRes128x128 = 3, kResTiles = 4 };
 void res_tile_shape(int tile, int* bm, int* bn);
 int res_tile_per_cu(int tile);  // workgroups per compute unit
-struct PackTables;
-hipError_t launch_res_pack(hipStream_t s, const PackTables& t, i64 total_blocks, int kind, int mode);
+hipError_t launch_res_pack(hipStream_t s, const PackTables& t, i64 total_units, PackSet set);
 // grid <= total_tiles workgroups take tiles b, b + grid, ...; conv: every problem's right operand is a ResConv
 hipError_t launch_res_gemm(hipStream_t s, const ResGemmTables& t, int total_tiles, int tile, int grid, bool conv);
 hipError_t launch_res_combine(hipStream_t s, const ResOutTables& t, i64 total_units);

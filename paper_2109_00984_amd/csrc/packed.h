@@ -104,6 +104,26 @@ template <> struct Mode<kModeOpenRight1> {  // y0, y1, b0, b1 -> delta
   __device__ static u64 out(int, const u64* v) { return v[0] + v[1] - v[2] - v[3]; }
 };
 
+// The (kind, mode) pairs of one pack kernel: its waves' jobs each have one of them.
+constexpr int km(int kind, int mode) { return kind * 16 + mode; }
+template <int... KM>
+struct PackPairs {
+  static constexpr bool has(int kind) { return ((KM / 16 == kind) || ...); }
+};
+template <PackSet S> struct SetPairs;
+template <> struct SetPairs<kPackMatmul> { using T = PackPairs<km(kPackRow, kModeOpenLeft), km(kPackCol, kModeOpenRight)>; };
+template <> struct SetPairs<kPackMatmulPre> { using T = PackPairs<km(kPackRow, kModeOpenLeft2), km(kPackCol, kModeOpenRight1)>; };
+template <> struct SetPairs<kPackConv> { using T = PackPairs<km(kPackRow, kModeOpenRight), km(kPackIm2col, kModeOpenLeft)>; };
+template <> struct SetPairs<kPackConvDirect> { using T = PackPairs<km(kPackConvRow, kModeOpenRight), km(kPackChan, kModeOpenLeft)>; };
+template <> struct SetPairs<kPackDeal> { using T = PackPairs<km(kPackRow, kModePrgSum2), km(kPackCol, kModePrgSum2)>; };
+template <> struct SetPairs<kPackDealPre> { using T = PackPairs<km(kPackRow, kModePrgSum2A), km(kPackCol, kModePrgSum2B)>; };
+template <> struct SetPairs<kPackDealConv> { using T = PackPairs<km(kPackRow, kModePrgSum2), km(kPackIm2col, kModeSum2)>; };
+template <> struct SetPairs<kPackDealConvDirect> { using T = PackPairs<km(kPackConvRow, kModePrgSum2), km(kPackChan, kModeSum2)>; };
+template <> struct SetPairs<kPackRing> { using T = PackPairs<km(kPackRow, kModeCopy), km(kPackCol, kModeCopy)>; };
+template <> struct SetPairs<kPackParty> {
+  using T = PackPairs<km(kPackRow, kModeCopy), km(kPackRow, kModeSum2), km(kPackCol, kModeCopy)>;
+};
+
 // ------------------------------------------------------------------ GEMM
 __device__ __forceinline__ int find_problem(cptr<int> start, int nprob, int t) {
   int lo = 0, hi = nprob - 1;
