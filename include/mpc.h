@@ -69,14 +69,16 @@ typedef enum {
  *          Each operand's k range (K of a product; each of the two halves of
  *          a Beaver finish, whose summed k is 2K) is at most 2,097,088 long;
  *          longer ones return MPC_E_UNSUPPORTED.
- *   AUTO:  the library's choice: PLAIN if the problem is tiny or its k is
- *          longer than LIMB8 takes; else LIMB8 or, where each operand element
+ *   AUTO:  the library's choice: PLAIN if its k is below 16 or longer than
+ *          LIMB8 takes, or for a Beaver matmul of at most 3 * 2^20
+ *          multiply-accumulates per party with k of at most 1024 (one launch);
+ *          else LIMB8 or, where each operand element
  *          enters many outputs, a residue form of its own: the product modulo
  *          18 coprime moduli of at most 256, each an exact INT8 GEMM, put
  *          together by the Chinese remainder theorem.  Bit-identical to PLAIN;
  *          it takes a larger workspace (18 bytes a packed element and output,
- *          where LIMB8 takes 8 a packed element) and gives way to LIMB8 where
- *          the workspace cannot grow that far.
+ *          where LIMB8 takes 8 a packed element) and gives way to LIMB8, and
+ *          that to PLAIN, where the workspace cannot grow that far.
  *   FP64LIMB: the paper's own GPU method (Section 5.3, off-loading to the
  *          GPU): operands split into four 16-bit limbs (ten pairwise products)
  *          or, when the summed k is below 1024, three 22-bit limbs (six), each
@@ -211,7 +213,7 @@ mpc_status mpc_beaver_matmul(mpc_ctx *ctx, int64_t M, int64_t N, int64_t K, cons
  * must be ordered by the caller.  The packed operands must fit it:
  * 24*(M*K + K*N) bytes up to padding (e.g. M = N = K = 1024), else
  * MPC_E_SHAPE.  form: MPC_FORM_LIMB8, or MPC_FORM_AUTO, which also takes the
- * one-launch plain product for products of at most 2^18 multiply-accumulates
+ * one-launch plain product of a small product, as AUTO does elsewhere
  * (no workspace); other forms return MPC_E_UNSUPPORTED.  The limb GEMM runs
  * without split-K and its descriptor tables travel in the kernel arguments.
  * MPC_E_HIP if the array's address could not be found when the context was

@@ -431,13 +431,17 @@ bool residue_pays_conv(const mpc_conv1d_shape& s, i64 N, i64 K) {
 }
 Form packing_form(i64 M, i64 N, i64 K) { return residue_pays(M, N, K) ? kFormResidue : MPC_FORM_LIMB8; }
 
-// AUTO: a matrix-core form for products of 2^22 ring MACs or more, when the
-// limb form can address their k segments (each kseg long; K is the total).
+// AUTO: a matrix-core form, unless the limb form cannot address the k segments
+// (each kseg long; K is the total) or they fill less than a quarter of its
+// 64-wide k step.  The plain form's launches cost more than a small product
+// (ring GEMM in a captured loop, plain against limb: 64 x 32 x 128 17.5 / 10.8
+// us, 200 x 100 x 50 28.6 / 10.4, 4 x 4 x 8192 34 / 19, 512 x 512 x 16 10.8 /
+// 10.9, 1024 x 1024 x 4 11.6 / 12.2; among three parties 23.8 / 18.6, 33.0 /
+// 17.6, 94 / 36, 24.3 / 18.9, 26.0 / 35.4).
+constexpr i64 kLimbMinSegK = 16;
 Form resolve_form(Form f, i64 M, i64 N, i64 K, i64 kseg, const mpc_conv1d_shape* conv = nullptr) {
   if (f != MPC_FORM_AUTO) return f;
-  if (kseg > kLimbMaxSegK) return MPC_FORM_PLAIN;
-  const double work = (double)M * (double)N * (double)K;
-  if (work < (double)(1 << 22)) return MPC_FORM_PLAIN;
+  if (kseg > kLimbMaxSegK || kseg < kLimbMinSegK) return MPC_FORM_PLAIN;
   return conv ? (residue_pays_conv(*conv, N, K) ? kFormResidue : MPC_FORM_LIMB8) : packing_form(M, N, K);
 }
 bool packs(Form f) { return f == MPC_FORM_LIMB8 || f == kFormResidue; }
@@ -517,25 +521,34 @@ mpc_status plan_splitk(mpc_ctx* c, std::vector<PlainProblem>& probs) {
 // Split-K reductions of one call: their job table rides in the call's
 // descriptor blob, and one launch reduces every split problem.
 struct ReduceTable {
+  std::vector<ReduceJob> jobs;
+  std::vector<i64> start;
   size_t ojobs = 0, ostart = 0;
-  int njobs = 0;
-  i64 chunks = 0;
 };
-ReduceTable add_reduces(Blob& blob, const std::vector<ReduceJob>& jobs) {
+ReduceTable reduce_table(const std::vector<ReduceJob>& jobs) {
   ReduceTable t;
-  if (jobs.empty()) return t;
-  std::vector<i64> cs(jobs.size() + 1, 0);
-  for (size_t i = 0; i < jobs.size(); ++i) cs[i + 1] = cs[i] + (jobs[i].M * jobs[i].N + kReduceChunk - 1) / kReduceChunk;
-  t.ojobs = blob.add(jobs.data(), jobs.size());
-  t.ostart = blob.add(cs.data(), cs.size());
-  t.njobs = (int)jobs.size();
-  t.chunks = cs.back();
+  t.jobs = jobs;
+  t.start.assign(1, 0);
+  for (const ReduceJob& j : jobs) t.start.push_back(t.start.back() + (j.M * j.N + kReduceChunk - 1) / kReduceChunk);
   return t;
 }
-mpc_status issue_reduces(mpc_ctx* c, hipStream_t st, const ReduceTable& t, const uint8_t* dev) {
-  if (!t.njobs || !t.chunks) return MPC_OK;
-  CHK(hip_status(launch_splitk_reduce_grouped(st, (const ReduceJob*)(dev + t.ojobs), (const i64*)(dev + t.ostart),
-                                              t.njobs, t.chunks)));
+void add_reduces(Blob& blob, ReduceTable& t) {
+  t.ojobs = blob.add(t.jobs.data(), t.jobs.size());
+  t.ostart = blob.add(t.start.data(), t.start.size());
+}
+// dev: the uploaded blob, or null for tables in the kernel arguments
+mpc_status issue_reduces(mpc_ctx* c, hipStream_t st, const ReduceTable& r, const uint8_t* dev) {
+  if (!r.start.back()) return MPC_OK;
+  ReduceTables t{};
+  t.njobs = (int)r.jobs.size();
+  if (dev) {
+    t.jobs = (const ReduceJob*)(dev + r.ojobs);
+    t.chunk_start = (const i64*)(dev + r.ostart);
+  } else {
+    std::copy(r.jobs.begin(), r.jobs.end(), t.ijobs);
+    std::copy(r.start.begin(), r.start.end(), t.ichunk_start);
+  }
+  CHK(hip_status(launch_splitk_reduce_grouped(st, t, r.start.back())));
   c->stats.launches++;
   return MPC_OK;
 }
@@ -559,7 +572,8 @@ mpc_status issue_plain(mpc_ctx* c, const std::vector<PlainProblem>& probs_in) {
   Blob blob;
   const size_t oprob = blob.add(probs.data(), n);
   const size_t otile = blob.add(tstart.data(), n + 1);
-  const ReduceTable rt = add_reduces(blob, reduces);
+  ReduceTable rt = reduce_table(reduces);
+  add_reduces(blob, rt);
   uint8_t* dev = nullptr;
   CHK(upload(c, blob, &dev));
   TileMap map{(int)n, (const int*)(dev + otile)};
@@ -1017,7 +1031,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
       return kb <= kb0 ? std::min<i64>(kb * 32, r.K0) : r.K0 + std::min<i64>((kb - kb0) * 32, r.K1);
     };
     const TileSched ts = sched_of(q);
-    auto piece = [&](int chunk, int kb_begin, int kb_end, const Epilogue& ep) -> mpc_status {
+    auto piece = [&](int chunk, int kb_begin, int kb_end, const Epilogue& ep, int slices = 1) -> mpc_status {
       // the GEMM steps over pairs of k-blocks inside one segment
       if ((kb0 | kb1 | kb_begin | kb_end) & 1) return MPC_E_INVAL;
       Launch& l = launch_of(chunk, ts);
@@ -1043,23 +1057,20 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
         p.ep.Out = ep.Out + eoff;
         if (ep.Cadd) p.ep.Cadd = ep.Cadd + eoff;
         p.cls = g.cls;
+        p.slices = slices;
+        p.pstride = r.M * r.N;
         l.pieces.push_back(p);
-        l.tstarts.push_back(l.tstarts.back() +
-                            (limb_per_class(ts.variant) ? limb_class_tiles(g.m, g.n, g.cls)
-                                                        : limb_tiles(g.m, g.n, ts.variant)));
+        l.tstarts.push_back(l.tstarts.back() + slices * (limb_per_class(ts.variant) ? limb_class_tiles(g.m, g.n, g.cls)
+                                                                                     : limb_tiles(g.m, g.n, ts.variant)));
       }
       l.macs += (double)r.M * (double)r.N * (double)(true_k(kb_end) - true_k(kb_begin));
       return MPC_OK;
     };
     if (nslices[q] > 1) {
       const int ks = nslices[q];
-      const i64 steps = kbt / 2;
       u64* part = (u64*)(c->splitk + part_off);
       part_off += align_up((size_t)(ks * r.M * r.N) * 8);
-      for (int sl = 0; sl < ks; ++sl) {
-        const int b0 = (int)(2 * (steps * sl / ks)), b1 = (int)(2 * (steps * (sl + 1) / ks));
-        CHK(piece(0, b0, b1, make_ep(nullptr, +1, 0, part + (size_t)sl * (size_t)(r.M * r.N), rowmajor_view(r.N))));
-      }
+      CHK(piece(0, 0, kbt, make_ep(nullptr, +1, 0, part, rowmajor_view(r.N)), ks));
       reduces.push_back(ReduceJob{part, ks, r.M, r.N, r.ep});
     } else {
       for (int ch = 0; ch < nchunks[q]; ++ch) {
@@ -1076,7 +1087,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
   std::stable_sort(launches.begin(), launches.end(),
                    [](const Launch& a, const Launch& b) { return a.chunk < b.chunk; });
   const size_t nlaunch = launches.size();
-  bool inl = reduces.empty() && pk.fits_inline();
+  bool inl = reduces.size() <= (size_t)kInlineReduces && pk.fits_inline();
   for (const Launch& l : launches)
     if (l.pieces.size() > (size_t)kInlineProbs) inl = false;
   // with split-K off, a no-alloc call has one job per operand side and two
@@ -1084,7 +1095,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
   if (no_alloc && !inl) return MPC_E_UNSUPPORTED;
   Blob blob;
   std::vector<size_t> oprob(nlaunch), otile(nlaunch);
-  ReduceTable rt{};
+  ReduceTable rt = reduce_table(reduces);
   uint8_t* dev = nullptr;
   if (!inl) {
     pk.add(blob);
@@ -1092,7 +1103,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
       oprob[L] = blob.add(launches[L].pieces.data(), launches[L].pieces.size());
       otile[L] = blob.add(launches[L].tstarts.data(), launches[L].tstarts.size());
     }
-    rt = add_reduces(blob, reduces);
+    add_reduces(blob, rt);
     CHK(upload(c, blob, &dev));
   }
   CHK(pk.issue(c, dev, launch_pack));
@@ -1118,7 +1129,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
     CHK(tm.stop());
     c->stats.launches++;
   }
-  if (!inl) CHK(issue_reduces(c, st, rt, dev));
+  CHK(issue_reduces(c, st, rt, dev));
   c->stats.gemm_problems += nreq;
   return MPC_OK;
 }
@@ -1261,15 +1272,19 @@ mpc_status issue_packed(mpc_ctx* c, Form form, Carve& cv, const std::vector<Pack
   return form == kFormResidue ? issue_residue(c, cv, jobs, reqs) : issue_limb(c, jobs, reqs, c->sched_default);
 }
 
-// Workspace for a packing form: `need(form)` bytes.  The residue form's is the
-// larger; where it cannot be had (the workspace may not move under a capture
-// or a live graph, or the memory is not there) the limb form takes its place.
+// Workspace for a form: `need(form)` bytes.  Where a packing form's cannot be
+// had (the workspace may not move under a capture or a live graph, or the
+// memory is not there) a form that needs less takes its place: the limb form
+// for the residue form, and for a choice of AUTO the plain form for that.
 template <class F>
-mpc_status ensure_packing_ws(mpc_ctx* c, Form* form, F need) {
+mpc_status ensure_form_ws(mpc_ctx* c, Form* form, bool automatic, F need) {
   if (*form == kFormResidue) {
     if (ensure_ws(c, need(kFormResidue)) == MPC_OK) return MPC_OK;
     *form = MPC_FORM_LIMB8;
   }
+  const mpc_status st = ensure_ws(c, need(*form));
+  if (st != MPC_E_NOMEM || !automatic || *form != MPC_FORM_LIMB8) return st;
+  *form = MPC_FORM_PLAIN;
   return ensure_ws(c, need(*form));
 }
 
@@ -1566,30 +1581,29 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
   const u64 *L0 = kind == MPC_TRIPLE_MATMUL ? t->a0 : t->b0, *L1 = kind == MPC_TRIPLE_MATMUL ? t->a1 : t->b1;
   const u64 *R0 = kind == MPC_TRIPLE_MATMUL ? t->b0 : t->a0, *R1 = kind == MPC_TRIPLE_MATMUL ? t->b1 : t->a1;
   const bool conv = kind == MPC_TRIPLE_CONV1D;
-  // In a packing form a matrix operand's shares are drawn inside its pack
-  // (each element is packed exactly once), so they are written once and never
-  // read back; an im2col operand (overlapping windows, possibly uncovered
-  // tail elements) and the plain form take the shares from PRG fills.
-  const bool limb = packs(form) && nc > 0;
   const bool a_left = kind == MPC_TRIPLE_MATMUL;  // which triple factor is the left operand
   u64* Ls[2] = {a_left ? t->a0 : t->b0, a_left ? t->a1 : t->b1};
   u64* Rs[2] = {a_left ? t->b0 : t->a0, a_left ? t->b1 : t->a1};
   const int Lslot = a_left ? kSlotA0 : kSlotB0, Rslot = a_left ? kSlotB0 : kSlotA0;
-  const bool fuse_r = limb && kind == MPC_TRIPLE_MATMUL;
   auto ops = [&](Form f) {
     const bool direct = conv && f == kFormResidue && conv_direct(cs);
     std::array<JobSpec, 2> j{direct ? conv_weight_job(cs) : left_job(M, K, K),
                              !conv ? right_job(K, N, N) : direct ? conv_chan_job(cs) : im2col_job(cs, lout)};
     set_prg_sum2(j[0], key[Lslot], key[Lslot + 1], Ls[0], Ls[1]);
-    if (fuse_r) set_prg_sum2(j[1], key[Rslot], key[Rslot + 1], Rs[0], Rs[1]);
+    if (!conv) set_prg_sum2(j[1], key[Rslot], key[Rslot + 1], Rs[0], Rs[1]);
     else set_mode(j[1], kModeSum2, {R0, R1});
     return j;
   };
-  CHK(ensure_packing_ws(c, &form, [&](Form f) {
+  CHK(ensure_form_ws(c, &form, true, [&](Form f) {
     if (!packs(f)) return kAlign + (conv ? align_up((size_t)(K * N) * 8) : 0);
     const auto j = ops(f);
     return kAlign + job_bytes(j[0], f) + job_bytes(j[1], f) + (f == kFormResidue ? res_out_bytes(M, N, j[0].K, 0) : 0);
   }));
+  // In a packing form a matrix operand's shares are drawn inside its pack
+  // (each element is packed exactly once), so they are written once and never
+  // read back; the activation of a convolution (overlapping windows, possibly
+  // uncovered tail elements) and the plain form take the shares from PRG fills.
+  const bool limb = packs(form) && nc > 0, fuse_r = limb && !conv;
   const size_t nl = a_left ? na : nb, nr = a_left ? nb : na;
   if (!limb) {
     CHK(hip_status(launch_prg_fill(st, key[Lslot], Ls[0], nl)));
@@ -1877,7 +1891,7 @@ mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int tru
     // both forms' operands side by side in the workspace; where that much
     // cannot be had, every plan takes the limb form
     Form any = std::count(forms.begin(), forms.end(), kFormResidue) ? kFormResidue : MPC_FORM_LIMB8;
-    CHK(ensure_packing_ws(c, &any, [&](Form f) {
+    CHK(ensure_form_ws(c, &any, false, [&](Form f) {
       size_t need = kAlign;
       for (size_t q = 0; q < plans.size(); ++q) need += matmul_ws(plans[q], f == kFormResidue ? forms[q] : f);
       return need;
@@ -1908,8 +1922,7 @@ mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int tru
       }
       CHK(issue_limb(c, jobs, reqs, c->sched_default));
     }
-  } else if (plans.size() == 1 && plans[0].K <= kSmallMatmulK && plans[0].M * plans[0].N <= kSmallMatmulMacs &&
-             plans[0].M * plans[0].N * plans[0].K <= kSmallMatmulMacs) {
+  } else if (plans.size() == 1 && small_matmul(plans[0].M, plans[0].N, plans[0].K)) {
     // a small product: open and finish in one launch, no workspace
     const MatmulPlan& m = plans[0];
     const SmallMatmul s{m.M, m.N, m.K, m.x0, m.x1, m.y0, m.y1, m.t.a0, m.t.a1, m.t.b0, m.t.b1,
@@ -1946,11 +1959,15 @@ mpc_status mpc_beaver_matmul(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const 
   CHK(check_form(want));
   MatmulPlan m{M, N, K, x0, x1, y0, y1, *t, z0, z1};
   CHK(validate_matmul(m));
-  Form form = resolve_form(want, M, N, 2 * K, K);
+  const bool automatic = want == MPC_FORM_AUTO;
+  const Form form = automatic && small_matmul(M, N, K) ? MPC_FORM_PLAIN : resolve_form(want, M, N, 2 * K, K);
   CHK(check_limb_k(form, K));
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
-  CHK(run_matmuls(c, {m}, trunc_bits, form));
+  mpc_status st = run_matmuls(c, {m}, trunc_bits, form);
+  // no memory for the packed operands, and nothing issued yet
+  if (st == MPC_E_NOMEM && automatic && packs(form)) st = run_matmuls(c, {m}, trunc_bits, MPC_FORM_PLAIN);
+  CHK(st);
   return end_call(c);
 }
 
@@ -2085,8 +2102,7 @@ mpc_status mpc_beaver_matmul_noalloc(mpc_ctx* c, int64_t M, int64_t N, int64_t K
   if (M == 0 || N == 0) return MPC_OK;
   if (!c->scratch) return MPC_E_HIP;
   CHK(set_device(c));
-  if (form == MPC_FORM_AUTO && resolve_form(form, M, N, 2 * K, K) == MPC_FORM_PLAIN && K <= kSmallMatmulK &&
-      M * N <= kSmallMatmulMacs && M * N * K <= kSmallMatmulMacs) {
+  if (form == MPC_FORM_AUTO && small_matmul(M, N, K)) {
     // a small product: open and finish in one launch, no workspace at all
     const SmallMatmul s{M, N, K, x0, x1, y0, y1, t->a0, t->a1, t->b0, t->b1, t->c0, t->c1, z0, z1, trunc_bits};
     CHK(hip_status(launch_beaver_matmul_small(c->s[0], s)));
@@ -2135,20 +2151,24 @@ mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const ui
   Form form = resolve_form(want, M, N, 2 * K, K, &s);
   CHK(check_limb_k(form, K));
   const OutView view{lout, std::max<i64>(lout, 1), s.cout * lout};
-  if (packs(form)) {
-    // delta, b0, b1 (weights); im2col of eps, g0, a1 (activations), or in the
-    // residue form the activations themselves
-    auto ops = [&](Form f) {
-      const bool direct = f == kFormResidue && conv_direct(s);
-      std::array<JobSpec, 2> j{direct ? conv_weight_job(s) : left_job(M, K, K), direct ? conv_chan_job(s) : im2col_job(s, lout)};
-      open_right(j[0], w0, w1, t->b0, t->b1);
-      open_left(j[1], x0, x1, t->a0, t->a1);
-      return j;
-    };
-    CHK(ensure_packing_ws(c, &form, [&](Form f) {
+  // delta, b0, b1 (weights); im2col of eps, g0, a1 (activations), or in the
+  // residue form the activations themselves
+  auto ops = [&](Form f) {
+    const bool direct = f == kFormResidue && conv_direct(s);
+    std::array<JobSpec, 2> j{direct ? conv_weight_job(s) : left_job(M, K, K), direct ? conv_chan_job(s) : im2col_job(s, lout)};
+    open_right(j[0], w0, w1, t->b0, t->b1);
+    open_left(j[1], x0, x1, t->a0, t->a1);
+    return j;
+  };
+  const size_t kn = (size_t)(K * N);
+  const size_t opened = kAlign + 2 * align_up(nx * 8) + align_up(nw * 8) + 3 * align_up(kn * 8);
+  if (packs(form))
+    CHK(ensure_form_ws(c, &form, want == MPC_FORM_AUTO, [&](Form f) {
+      if (!packs(f)) return opened;
       const auto j = ops(f);
       return kAlign + job_bytes(j[0], f) + job_bytes(j[1], f) + (f == kFormResidue ? 2 * res_out_bytes(M, N, j[0].K, j[0].K) : 0);
     }));
+  if (packs(form)) {
     Carve cv(c->ws);
     const auto j = ops(form);
     const PackJob W = place_job(j[0], cv, form), X = place_job(j[1], cv, form);
@@ -2162,12 +2182,10 @@ mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const ui
   } else {
     // plain and fp64 limb forms: open, then im2col of eps, g_0 and a_1 into
     // row-major K x N matrices
-    const size_t kn = (size_t)(K * N);
     const bool fp = form == MPC_FORM_FP64LIMB;
     if (fp && 2 * K >= kFp64MaxK) return MPC_E_UNSUPPORTED;
     if (fp) CHK(fp64_ready(c));
-    CHK(ensure_ws(c, kAlign + 2 * align_up(nx * 8) + align_up(nw * 8) + 3 * align_up(kn * 8) +
-                         (fp ? fp64_ws(M, N, 2 * K) : 0)));
+    CHK(ensure_ws(c, opened + (fp ? fp64_ws(M, N, 2 * K) : 0)));
     Carve cv(c->ws);
     u64* eps = cv.take<u64>(nx);
     u64* g = cv.take<u64>(nx);
@@ -2220,13 +2238,15 @@ mpc_status mpc_ring_gemm(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const uint
   Form form = resolve_form(want, M, N, K, K);
   CHK(check_limb_k(form, K));
   const Epilogue ep = make_ep(nullptr, +1, 0, C, rowmajor_view(N));
-  if (packs(form)) {
-    JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
-    set_mode(ja, kModeCopy, {A});
-    set_mode(jb, kModeCopy, {B});
-    CHK(ensure_packing_ws(c, &form, [&](Form f) {
+  JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
+  set_mode(ja, kModeCopy, {A});
+  set_mode(jb, kModeCopy, {B});
+  if (packs(form))
+    CHK(ensure_form_ws(c, &form, want == MPC_FORM_AUTO, [&](Form f) {
+      if (!packs(f)) return (size_t)0;
       return kAlign + job_bytes(ja, f) + job_bytes(jb, f) + (f == kFormResidue ? res_out_bytes(M, N, K, 0) : 0);
     }));
+  if (packs(form)) {
     Carve cv(c->ws);
     const PackJob PA = place_job(ja, cv, form), PB = place_job(jb, cv, form);
     CHK(issue_packed(c, form, cv, {PA, PB}, {limb_req(M, N, K, 0, PA.dst[0], nullptr, PB.dst[0], nullptr, ep)}));
@@ -2898,7 +2918,7 @@ mpc_status mpc_mp_dealer_triples(mpc_ctx* c, int P, mpc_triple_kind kind, uint64
   Form form = resolve_form(MPC_FORM_AUTO, M, N, K, K);
   // workspace: a = sum a_p, b = sum b_p, S = sum_{p<P-1} c_p, then the GEMM's packs
   JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
-  CHK(ensure_packing_ws(c, &form, [&](Form f) {
+  CHK(ensure_form_ws(c, &form, true, [&](Form f) {
     return kAlign + align_up(na * 8) + align_up(nb * 8) + align_up(nc * 8) + (packs(f) ? job_bytes(ja, f) + job_bytes(jb, f) : 0) +
            (f == kFormResidue ? res_out_bytes(M, N, K, 0) : 0);
   }));
@@ -2990,7 +3010,7 @@ mpc_status mpc_mp_beaver_matmul(mpc_ctx* c, int P, int64_t M, int64_t N, int64_t
   const hipStream_t st = c->s[0];
   // open eps (MxK) and delta (KxN) into the workspace, then party p's finish
   // z_p = c_p + [a_p + [p=0] eps | eps] @ [delta ; b_p]
-  CHK(ensure_packing_ws(c, &form, [&](Form f) {
+  CHK(ensure_form_ws(c, &form, want == MPC_FORM_AUTO, [&](Form f) {
     return kAlign + align_up(na * 8) + align_up(nb * 8) +
            (packs(f) ? (size_t)(P + 1) * (align_up(packed_bytes(M, K, f)) + align_up(packed_bytes(N, K, f))) : 0) +
            (f == kFormResidue ? (size_t)P * res_out_bytes(M, N, K, K) : 0);

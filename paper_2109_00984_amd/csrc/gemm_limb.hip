@@ -406,6 +406,8 @@ __device__ __forceinline__ void mfma_step(StepRegs<SA, SB> r, const StepOff& cur
 struct TilePos {
   int pi;
   i64 tm, tn;
+  int kbeg, kend;  // k-blocks
+  i64 shift;       // of the output: a slice's partial sums
 };
 
 // This workgroup's problem and its tile index inside that problem.
@@ -424,6 +426,17 @@ __device__ __forceinline__ TilePos tile_coords(const GemmView& v, int pi, i64 lo
   q.pi = pi;
   const i64 M = v.probs[pi].M, N = v.probs[pi].N;
   const i64 ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
+  q.kbeg = v.probs[pi].kb_begin;
+  q.kend = v.probs[pi].kb_end;
+  q.shift = 0;
+  const int ks = v.probs[pi].slices;
+  if (ks > 1) {
+    const int sl = (int)(local / (ntm * ntn)), steps = (q.kend - q.kbeg) / 2;
+    local -= sl * ntm * ntn;
+    q.kend = q.kbeg + 2 * (int)((i64)steps * (sl + 1) / ks);
+    q.kbeg += 2 * (int)((i64)steps * sl / ks);
+    q.shift = sl * v.probs[pi].pstride;
+  }
   const i64 gm = v.sched.group_m;  // 1..64, checked by the host
   const i64 per_group = gm * ntn;
   const i64 first_m = (local / per_group) * gm;
@@ -449,15 +462,17 @@ __device__ __forceinline__ TilePos tile_pos(const GemmView& v) {
 // layout: lane l, register e holds row 4*(l/16) + e and column l%16 of the
 // 16x16 block.
 template <int HA, int HB, int BM, int BN>
-__device__ __forceinline__ void store_tile(v4i (&acc)[HA][HB][8], cptr<LimbProblem> pp, i64 tm, i64 tn, int wr,
+__device__ __forceinline__ void store_tile(v4i (&acc)[HA][HB][8], cptr<LimbProblem> pp, const TilePos& tp, int wr,
                                            int wc, int lane) {
+  const i64 tm = tp.tm, tn = tp.tn;
 #pragma unroll
   for (int s = 0; s < 8; ++s)
 #pragma unroll
     for (int x = 0; x < HA; ++x)
 #pragma unroll
       for (int y = 0; y < HB; ++y) asm volatile("s_nop 3" : "+a"(acc[x][y][s]));
-  const Epilogue ep = pp->ep;
+  Epilogue ep = pp->ep;
+  ep.Out += tp.shift;
   // Three passes over this lane's outputs: combine the limb diagonals, load
   // every added term (the triple share, the previous K chunk's sum), then add,
   // truncate and store.  With no store between them the loads are in flight
@@ -544,7 +559,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_limb_gemm(GemmTables) {
 
   // k runs in steps of two 32-blocks; every segment holds an even number of
   // blocks, so a step never straddles two segments
-  const int kbeg = pp->kb_begin, nsteps = (pp->kb_end - pp->kb_begin) >> 1;
+  const int kbeg = tp.kbeg, nsteps = (tp.kend - tp.kbeg) >> 1;
   const int g = lane >> 4;
   const LaneOff lo{(unsigned)((g >> 1) * 8192 + (g & 1) * 512 + (lane & 15) * 16)};
   const SegSrc s0 = seg_src(pp->PA0, pp->PB0, pp->kb0, mb0, nb0, SA, SB);
@@ -588,7 +603,7 @@ __global__ void __launch_bounds__(kThreads, 1) k_limb_gemm(GemmTables) {
 #pragma unroll
         for (int s = 0; s < 8; ++s) acc[x][y][s] = v4i{0, 0, 0, 0};
   }
-  store_tile<S::HA, S::HB, S::BM, S::BN>(acc, pp, tm, tn, wr, wc, lane);
+  store_tile<S::HA, S::HB, S::BM, S::BN>(acc, pp, tp, wr, wc, lane);
 }
 
 
@@ -835,7 +850,7 @@ __device__ __forceinline__ void lds_tile(lds_u8* b0, lds_u8* b1, const GemmView&
   const int ho0 = (G::kOuterA ? wr : wc) * G::HO, hi0 = (G::kOuterA ? wc : wr) * G::HI;
 
   v4i acc[HA][HB][8];
-  const int kbeg = pp->kb_begin, nsteps = (pp->kb_end - pp->kb_begin) >> 1;
+  const int kbeg = tp.kbeg, nsteps = (tp.kend - tp.kbeg) >> 1;
   const int g = lane >> 4;
   const unsigned lane_off = (unsigned)((g >> 1) * 8192 + (g & 1) * 512 + (lane & 15) * 16);
   // inner loads: the wave's descriptor starts at the strip of its first half;
@@ -894,7 +909,7 @@ __device__ __forceinline__ void lds_tile(lds_u8* b0, lds_u8* b1, const GemmView&
 #pragma unroll
         for (int s = 0; s < 8; ++s) acc[x][y][s] = v4i{0, 0, 0, 0};
   }
-  store_tile<HA, HB, G::BM, G::BN>(acc, pp, tm, tn, wr, wc, lane);
+  store_tile<HA, HB, G::BM, G::BN>(acc, pp, tp, wr, wc, lane);
 }
 
 template <int HA, int HB, int WR, int WC>
@@ -1256,7 +1271,7 @@ __global__ void __launch_bounds__(64 * WR * WC, WR * WC == 4 ? 2 : 1)  // SGeo::
   const int xo = G::kOuterA ? wr : wc, xi = G::kOuterA ? wc : wr;  // the wave's outer / inner strip
 
   v4i acc[2][2][8];
-  const int kbeg = pp->kb_begin, nsteps = (pp->kb_end - pp->kb_begin) >> 1;
+  const int kbeg = tp.kbeg, nsteps = (tp.kend - tp.kbeg) >> 1;
   const int g = lane >> 4;
   const unsigned lane_lds = (unsigned)((g >> 1) * 1024 + (g & 1) * 512 + (lane & 15) * 16);
   const SCtx c{(unsigned)(xo * 2048) + lane_lds, (unsigned)(G::kIBase + xi * 2048) + lane_lds,
@@ -1308,7 +1323,7 @@ __global__ void __launch_bounds__(64 * WR * WC, WR * WC == 4 ? 2 : 1)  // SGeo::
 #pragma unroll
         for (int s = 0; s < 8; ++s) acc[x][y][s] = v4i{0, 0, 0, 0};
   }
-  store_tile<2, 2, G::BM, G::BN>(acc, pp, tm, tn, wr, wc, lane);
+  store_tile<2, 2, G::BM, G::BN>(acc, pp, tp, wr, wc, lane);
 }
 
 }  // namespace

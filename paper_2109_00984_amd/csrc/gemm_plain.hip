@@ -11,7 +11,7 @@
 // aL*bL goes into a 64-bit accumulator (v_mad_u64_u32); the cross terms only
 // matter modulo 2^32 and go into a 32-bit accumulator that is shifted in once
 // at the end.
-#include "internal.h"
+#include "packed.h"
 
 namespace mpc {
 namespace {
@@ -19,16 +19,6 @@ namespace {
 constexpr int BM = 128, BN = 64, BK = kPlainBK;
 constexpr int TM = 8, TN = 4;
 constexpr int kThreads = 256;
-
-__device__ __forceinline__ int find_problem(const int* __restrict__ start, int nprob, int t) {
-  int lo = 0, hi = nprob - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (start[mid] <= t) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
-}
 
 __device__ __forceinline__ u64 load_a(const PlainProblem& p, i64 m, i64 k) {
   if (m >= p.M) return 0;
@@ -60,7 +50,7 @@ __global__ void __launch_bounds__(kThreads, 2)
   __shared__ u64 Bs[2][BK][BN];
 
   const int t = blockIdx.x;
-  const int pi = find_problem(map.tile_start, map.nprob, t);
+  const int pi = find_problem((cptr<int>)(uintptr_t)map.tile_start, map.nprob, t);
   const PlainProblem p = probs[pi];
   const int local = t - map.tile_start[pi];
   const int ntn = (int)((p.N + BN - 1) / BN);
@@ -219,16 +209,13 @@ __device__ __forceinline__ void reduce_one(const u64* __restrict__ partial, int 
   ep.Out[off] = v;
 }
 
-__global__ void __launch_bounds__(kThreads)
-    k_splitk_reduce_grouped(const ReduceJob* __restrict__ jobs, const i64* __restrict__ chunk_start, int njobs) {
+__global__ void __launch_bounds__(kThreads) k_splitk_reduce_grouped(ReduceTables) {
+  const cptr<ReduceTables> t = (cptr<ReduceTables>)MPC_KERNARG_PTR();
+  const cptr<ReduceJob> jobs = t->jobs ? (cptr<ReduceJob>)(uintptr_t)t->jobs : t->ijobs;
+  const cptr<i64> chunk_start = t->jobs ? (cptr<i64>)(uintptr_t)t->chunk_start : t->ichunk_start;
   const i64 c = blockIdx.x;
-  int lo = 0, hi = njobs - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (chunk_start[mid] <= c) lo = mid;
-    else hi = mid - 1;
-  }
-  const ReduceJob& jb = jobs[lo];
+  const int lo = find_job(chunk_start, t->njobs, c);
+  const ReduceJob jb = jobs[lo];
   const i64 total = jb.M * jb.N;
   const i64 base = (c - chunk_start[lo]) * kReduceChunk;
   const i64 end = min(base + kReduceChunk, total);
@@ -237,26 +224,28 @@ __global__ void __launch_bounds__(kThreads)
 
 }  // namespace
 
-hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceJob* jobs, const i64* chunk_start, int njobs,
-                                        i64 total_chunks) {
+hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceTables& t, i64 total_chunks) {
   if (total_chunks <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_splitk_reduce_grouped, dim3((unsigned)total_chunks), dim3(kThreads), 0, s, jobs,
-                     chunk_start, njobs);
+  hipLaunchKernelGGL(k_splitk_reduce_grouped, dim3((unsigned)total_chunks), dim3(kThreads), 0, s, t);
   return hipGetLastError();
 }
 
 // Whole Beaver matmul of a small product in one launch.  A workgroup owns a
-// 4x4 block of outputs of both parties' shares; its 256 threads are those 16
-// outputs times 16 lanes of k (k = lane, lane + 16, ...).  Each thread forms
+// 4x4 block of outputs of both parties' shares; its 512 threads are those 16
+// outputs times 32 lanes of k (k = lane, lane + 32, ...): the launch is a chain
+// of dependent loads, 32 steps of k at the longest.  Measured in a captured
+// loop, with 16, 32 and 64 lanes: 64 x 64 x 256 7.0, 6.6 and 7.1 us, 64 x 64 x
+// 512 11.4, 10.2 and 11.1, 128 x 10 x 1024 20.6, 17.1 and 18.2 (the plain form's
+// open, GEMM and reduction 25 to 31, the limb form 19 to 20).  Each thread forms
 // the opened eps = x - a and delta = y - b of the elements it reads from the
 // shares themselves (an open pass and its workspace would cost more than the
 // product at this size), accumulates
 //   z_0 = eps b_0 + (a_0 + eps) delta,  z_1 = eps b_1 + a_1 delta
-// over its k, and the 16 partial sums of an output are added through LDS
+// over its k, and the 32 partial sums of an output are added through LDS
 // before c_p and the truncation.  Ring sums do not depend on their order.
-constexpr int kSmallSide = 4, kSmallOut = kSmallSide * kSmallSide, kSmallKl = kThreads / kSmallOut;
+constexpr int kSmallSide = 4, kSmallOut = kSmallSide * kSmallSide, kSmallKl = 32;
 
-__global__ void __launch_bounds__(kThreads) k_beaver_matmul_small(SmallMatmul s) {
+__global__ void __launch_bounds__(kSmallOut * kSmallKl) k_beaver_matmul_small(SmallMatmul s) {
   __shared__ u64 part[2][kSmallKl][kSmallOut];
   const int o = threadIdx.x % kSmallOut, kl = threadIdx.x / kSmallOut;
   const i64 ntn = (s.N + kSmallSide - 1) / kSmallSide;
@@ -302,7 +291,7 @@ int plain_tiles(i64 M, i64 N) { return (int)(((M + BM - 1) / BM) * ((N + BN - 1)
 hipError_t launch_beaver_matmul_small(hipStream_t s, const SmallMatmul& m) {
   const i64 tiles = ((m.M + kSmallSide - 1) / kSmallSide) * ((m.N + kSmallSide - 1) / kSmallSide);
   if (tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_beaver_matmul_small, dim3((unsigned)tiles), dim3(kThreads), 0, s, m);
+  hipLaunchKernelGGL(k_beaver_matmul_small, dim3((unsigned)tiles), dim3(kSmallOut * kSmallKl), 0, s, m);
   return hipGetLastError();
 }
 

@@ -163,6 +163,11 @@ struct LimbProblem {
   i64 nblocks;  // padded col blocks of the right operand
   Epilogue ep;
   int cls;      // tile class, read by the classes variant only
+  // Split-K: with slices > 1 the k range is cut into that many slices of whole
+  // k steps, each with a tile list of its own, slice after slice; slice s writes
+  // its raw sums pstride * s elements past ep.Out.
+  int slices;
+  i64 pstride;
 };
 
 // Largest number of concatenated k values one limb launch may cover: with all
@@ -249,10 +254,14 @@ struct SmallMatmul {
   u64 *z0, *z1;
   int trunc;
 };
-// Products of at most kSmallMatmulMacs ring multiply-accumulates per party
-// with k at most kSmallMatmulK (each thread then runs at most 64 steps of k)
-// take it.
-constexpr i64 kSmallMatmulMacs = (i64)1 << 18, kSmallMatmulK = 1024;
+// Products of at most kSmallMatmulMacs ring multiply-accumulates per party with
+// k at most kSmallMatmulK take it.  At 3 * 2^20 with k of 1024 it takes the limb
+// form's 20 us, at 2^21 with k of 128 to 512 10 us against 17 to 20; at 2^22.9
+// (200 x 200 x 200) 30 against 22, and at k of 2048 (2^21) 31 against 21.
+constexpr i64 kSmallMatmulMacs = (i64)3 << 20, kSmallMatmulK = 1024;
+inline bool small_matmul(i64 M, i64 N, i64 K) {
+  return K <= kSmallMatmulK && M * N <= kSmallMatmulMacs && M * N * K <= kSmallMatmulMacs;
+}
 hipError_t launch_beaver_matmul_small(hipStream_t s, const SmallMatmul& m);
 hipError_t launch_plain_gemm(hipStream_t s, const PlainProblem* probs, TileMap map,
                              int total_tiles);
@@ -270,8 +279,16 @@ struct ReduceJob {
   Epilogue ep;
 };
 constexpr i64 kReduceChunk = 256;  // one output per thread
-hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceJob* jobs, const i64* chunk_start, int njobs,
-                                        i64 total_chunks);
+// The tables travel as PackTables' do: device arrays, or in the arguments when `jobs` is null.
+constexpr int kInlineReduces = 4;
+struct ReduceTables {
+  const ReduceJob* jobs;
+  const i64* chunk_start;
+  int njobs;
+  ReduceJob ijobs[kInlineReduces];
+  i64 ichunk_start[kInlineReduces + 1];
+};
+hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceTables& t, i64 total_chunks);
 
 // Limb form (gemm_limb.hip).
 // The descriptor tables of one pack or GEMM launch travel either as device
