@@ -407,17 +407,87 @@ bool conv_direct(const mpc_conv1d_shape& s) {
          s.batch * conv_lout(s) <= (i64)1 << 30;
 }
 
-// Whether AUTO takes a product of the limb form to the residue form, which
+// Time of the residue GEMM's tiles: a round of workgroups over the compute
+// units takes a fixed part (first loads, epilogue) and one part per 64-wide k
+// step, as measured per tile shape on 4096 x 4096 outputs at k of 4096 and 8192.
+constexpr double kResFixedUs[kResTiles] = {5.8, 3.9, 3.9, 2.0}, kResStepUs[kResTiles] = {0.71, 0.82, 0.82, 0.48};
+constexpr int kPlanCUs = 256;
+double res_round_us(int v, i64 steps) { return kResFixedUs[v] + kResStepUs[v] * (double)steps; }
+i64 res_tiles(int v, i64 M, i64 N) {
+  int bm, bn;
+  res_tile_shape(v, &bm, &bn);
+  return (M + bm - 1) / bm * ((N + bn - 1) / bn);
+}
+// `units` equal GEMMs (one modulus of one product each) of M x N over `steps`
+// k steps: the first `first` of them in tiles of shape v0, the rest, which
+// would leave most of a round idle, in shape v1.
+struct ResPlan {
+  int v0 = kRes128x128, v1 = kRes128x128;
+  i64 first = 0;
+  double us = 0;
+};
+ResPlan res_plan(i64 M, i64 N, i64 steps, i64 units) {
+  auto time = [&](int v, i64 n) {
+    const double slots = (double)kPlanCUs * res_tile_per_cu(v);
+    return n ? std::ceil((double)(n * res_tiles(v, M, N)) / slots) * res_round_us(v, steps) : 0.0;
+  };
+  ResPlan best;
+  best.us = -1;
+  for (int v0 = 0; v0 < kResTiles; ++v0) {
+    const i64 slots = (i64)kPlanCUs * res_tile_per_cu(v0), per = res_tiles(v0, M, N);
+    // whole rounds of v0, then v1; or v0 alone
+    for (i64 first : {units, units * per / slots * slots / per})
+      for (int v1 = 0; v1 < kResTiles; ++v1) {
+        const double us = time(v0, first) + time(v1, units - first) + (first && first < units ? 4.0 : 0.0);
+        if (best.us < 0 || us < best.us) best = ResPlan{v0, v1, first, us};
+      }
+  }
+  return best;
+}
+// One of many GEMMs in a launch: the shape that wastes least.
+int res_tile_of(i64 M, i64 N, i64 steps, double* us) {
+  int pick = 0;
+  double best = -1;
+  for (int v = 0; v < kResTiles; ++v) {
+    const double t = (double)res_tiles(v, M, N) * res_round_us(v, steps) / ((double)kPlanCUs * res_tile_per_cu(v));
+    if (best < 0 || t < best) {
+      best = t;
+      pick = v;
+    }
+  }
+  if (us) *us = best;
+  return pick;
+}
+
+// What a product gains, in us, by the residue form over the limb form: it
 // halves the int8 work (18 products against 36) and writes 2.25 times the
-// packed bytes (18 a packed element against 8): it pays where each packed
-// element is used by many outputs and the sums are long.  reuse = M N / (M + N)
-// outputs per operand element; K is the summed k.  Beaver matmuls, limb against
-// residue: 1024 x 1024 x 1024 125 / 153 us, 512 x 2048 x 4096 490 / 490,
-// 1024 x 2048 x 1024 227 / 246, 1024 x 2048 x 2048 453 / 396, 2048 x 2048 x 1024
-// 434 / 411, 2048^3 841 / 692, 4096^3 6540 / 4480.
-bool residue_pays(i64 M, i64 N, i64 K) {
-  const double reuse = (double)M * (double)N / (double)(M + N);
-  return reuse >= 512 && reuse * (double)K >= 2.5e6;
+// packed bytes (18 a packed element against 8).  `gemms` products of M x N over
+// K summed k, each operand packed `outs` times over K / segs; the difference
+// of the two forms' times, in us: limb work at 3.1 PMAC-op/s, packed bytes at
+// 5.0 TB/s, the combine's 34 bytes an output at 4.4, the residue form's further
+// launches 6 us, and 8 % against the model's own error.  Measured, Beaver
+// matmuls, limb against residue: 512 x 2048 x 2048 244 / 261 us, 512 x 2048 x
+// 4096 491 / 471, 1024 x 2048 x 1024 222 / 225, 1024 x 2048 x 2048 453 / 393,
+// 2048 x 2048 x 1024 441 / 410, 2048^3 859 / 678, 777 x 1500 x 3001 452 / 472;
+// ring GEMMs 2048 x 2048 x 1024 114 / 119, 2048 x 2048 x 4096 435 / 376.
+// grouped: many products in one call, no rounding up to rounds.
+double residue_gain_us(i64 M, i64 N, i64 K, int gemms, int outs, int segs, bool grouped) {
+  if (K < 256 || std::min(M, N) < 64) return -1;
+  const double m64 = (double)((M + 63) / 64 * 64), n64 = (double)((N + 63) / 64 * 64);
+  const i64 steps = (K + 63) / 64;
+  const double limb = gemms * 72.0 * m64 * n64 * (double)K / 3.1e9;
+  double gemm;
+  if (grouped) {
+    res_tile_of(M, N, steps, &gemm);
+    gemm *= gemms * kRes;
+  } else {
+    gemm = res_plan(M, N, steps, (i64)gemms * kRes).us;
+  }
+  // rows that do not start on 128-byte lines slow its packing more
+  const bool aligned = K / segs % 16 == 0 && N % 16 == 0;
+  const double packed = (double)(M + N) * (double)(K / segs) * outs * ((kRes - 8.0) / 5.0e6 + (aligned ? 0.0 : 2.0e-6));
+  const double res = gemm + packed + gemms * 34.0 * (double)M * (double)N / 4.4e6 + (grouped ? 0.0 : 6.0);
+  return limb - 1.08 * res;
 }
 // A convolution packed without im2col writes its activation once, not once per
 // tap, so only its k (against the combine, 18 bytes an output) and its whole
@@ -425,24 +495,30 @@ bool residue_pays(i64 M, i64 N, i64 K) {
 // 250 -> 250 channels, 7 taps, 771 long 424 / 281 us; 512 -> 512, 3 taps, 398
 // long 334 / 268; 64 -> 128, 5 taps, 496 long 59 / 81; 128 -> 128, 9 taps, 992
 // long: batch 2 79 / 94, batch 4 113 / 111, batch 8 201 / 157.
-bool residue_pays_conv(const mpc_conv1d_shape& s, i64 N, i64 K) {
-  if (!conv_direct(s)) return residue_pays(s.cout, N, K);
+bool residue_pays_conv(const mpc_conv1d_shape& s, i64 N, i64 K, int gemms, int outs, int segs) {
+  if (!conv_direct(s)) return residue_gain_us(s.cout, N, K, gemms, outs, segs, false) > 0;
   return s.cout >= 128 && K >= 1536 && (double)s.cout * (double)N * (double)K >= 1.3e9;
 }
-Form packing_form(i64 M, i64 N, i64 K) { return residue_pays(M, N, K) ? kFormResidue : MPC_FORM_LIMB8; }
+// The packing form of a Beaver matmul (P parties) over K k.
+Form packing_form(i64 M, i64 N, i64 K, int P = 2) {
+  return residue_gain_us(M, N, 2 * K, P, P + 1, 2, false) > 0 ? kFormResidue : MPC_FORM_LIMB8;
+}
 
-// AUTO: a matrix-core form, unless the limb form cannot address the k segments
-// (each kseg long; K is the total) or they fill less than a quarter of its
-// 64-wide k step.  The plain form's launches cost more than a small product
+// AUTO: a matrix-core form, unless the limb form cannot address the K segments
+// or they fill less than a quarter of its 64-wide k step.  The plain form's launches cost more than a small product
 // (ring GEMM in a captured loop, plain against limb: 64 x 32 x 128 17.5 / 10.8
 // us, 200 x 100 x 50 28.6 / 10.4, 4 x 4 x 8192 34 / 19, 512 x 512 x 16 10.8 /
 // 10.9, 1024 x 1024 x 4 11.6 / 12.2; among three parties 23.8 / 18.6, 33.0 /
 // 17.6, 94 / 36, 24.3 / 18.9, 26.0 / 35.4).
 constexpr i64 kLimbMinSegK = 16;
-Form resolve_form(Form f, i64 M, i64 N, i64 K, i64 kseg, const mpc_conv1d_shape* conv = nullptr) {
+// parties: of a Beaver product over K k, or 0 for one product of public or
+// dealt operands.
+Form resolve_form(Form f, i64 M, i64 N, i64 K, int parties, const mpc_conv1d_shape* conv = nullptr) {
   if (f != MPC_FORM_AUTO) return f;
-  if (kseg > kLimbMaxSegK || kseg < kLimbMinSegK) return MPC_FORM_PLAIN;
-  return conv ? (residue_pays_conv(*conv, N, K) ? kFormResidue : MPC_FORM_LIMB8) : packing_form(M, N, K);
+  if (K > kLimbMaxSegK || K < kLimbMinSegK) return MPC_FORM_PLAIN;
+  const int gemms = parties ? parties : 1, outs = parties ? parties + 1 : 1, segs = parties ? 2 : 1;
+  const bool res = conv ? residue_pays_conv(*conv, N, segs * K, gemms, outs, segs) : residue_gain_us(M, N, segs * K, gemms, outs, segs, false) > 0;
+  return res ? kFormResidue : MPC_FORM_LIMB8;
 }
 bool packs(Form f) { return f == MPC_FORM_LIMB8 || f == kFormResidue; }
 
@@ -1149,46 +1225,29 @@ size_t res_out_bytes(i64 M, i64 N, i64 K0, i64 K1) {
   return align_up(res_chunks(K0, K1) * (size_t)kRes * (size_t)res_plane(M, N));
 }
 
-// Workgroup tile of a residue launch: the one whose rounds over the compute
-// units take least, a round being a fixed part (first loads, epilogue) and one
-// part per 64-wide k step, both as measured on 4096 x 4096 outputs.
-int res_tile_for(const mpc_ctx* c, const std::vector<LimbReq>& reqs) {
-  static const double fixed_us[kResTiles] = {5.8, 3.9, 3.9, 2.0}, step_us[kResTiles] = {0.71, 0.82, 0.82, 0.48};
-  double best = 0;
-  int pick = kRes128x128;
-  for (int v = 0; v < kResTiles; ++v) {
-    int bm, bn;
-    res_tile_shape(v, &bm, &bn);
-    double steps = 0, tiles = 0;
-    for (const LimbReq& r : reqs) {
-      const double n = (double)kRes * (double)((r.M + bm - 1) / bm) * (double)((r.N + bn - 1) / bn);
-      tiles += n;
-      steps += n * (double)(res_kblocks(r.K0) + res_kblocks(r.K1));
-    }
-    if (tiles == 0) continue;
-    const double cost = std::ceil(tiles / ((double)c->num_cu * res_tile_per_cu(v))) * (fixed_us[v] + step_us[v] * steps / tiles);
-    if (best == 0 || cost < best) {
-      best = cost;
-      pick = v;
-    }
-  }
-  return pick;
-}
-
 // The residue form of issue_limb: the pack launches, one GEMM launch over the
 // tiles of every product, modulus and chunk of k, one combine launch with the
 // products' epilogues.  `cv` provides res_out_bytes per product.
 mpc_status issue_residue(mpc_ctx* c, Carve& cv, const std::vector<PackJob>& jobs, const std::vector<LimbReq>& reqs) {
   const hipStream_t st = c->s[0];
   PackLaunch pk(jobs);
-  const int tile = res_tile_for(c, reqs);
-  int bm, bn;
-  res_tile_shape(tile, &bm, &bn);
-  std::vector<ResProblem> probs;
+  // one launch per tile shape in use
+  struct Launch {
+    std::vector<ResProblem> probs;
+    std::vector<int> tstart{0};
+    size_t op = 0, ots = 0;
+  };
+  Launch launches[kResTiles];
   std::vector<ResOut> outs;
-  std::vector<int> tstart{0};
   std::vector<i64> ustart{0};
   double macs = 0;
+  // the products of one call, when they are all alike, share whole rounds
+  bool alike = true;
+  for (const LimbReq& r : reqs) alike = alike && r.M == reqs[0].M && r.N == reqs[0].N && r.K0 == reqs[0].K0 && r.K1 == reqs[0].K1;
+  const i64 kb_all = res_kblocks(reqs[0].K0) + res_kblocks(reqs[0].K1), nch0 = (i64)res_chunks(reqs[0].K0, reqs[0].K1);
+  const i64 nunits = (i64)reqs.size() * nch0 * kRes;
+  const ResPlan plan = res_plan(reqs[0].M, reqs[0].N, (kb_all + nch0 - 1) / nch0, nunits);
+  i64 unit = 0;
   for (const LimbReq& r : reqs) {
     // one segment, or two of the same length
     if (r.K1 && r.K1 != r.K0) return MPC_E_INVAL;
@@ -1218,51 +1277,78 @@ mpc_status issue_residue(mpc_ctx* c, Carve& cv, const std::vector<PackJob>& jobs
       // chunks of equal length, to a block
       p.kb_begin = (int)((i64)(kb0 + kb1) * ch / nch);
       p.kb_end = (int)((i64)(kb0 + kb1) * (ch + 1) / nch);
-      p.ntm = (int)((r.M + bm - 1) / bm);
-      p.ntn = (int)((r.N + bn - 1) / bn);
       p.n64 = o.n64;
       p.R = R + ch * o.pc;
       p.pr = o.pr;
-      probs.push_back(p);
-      tstart.push_back(tstart.back() + kRes * p.ntm * p.ntn);
+      auto put = [&](int v, int m0, int nm) {
+        if (!nm) return;
+        int bm, bn;
+        res_tile_shape(v, &bm, &bn);
+        p.ntm = (int)((r.M + bm - 1) / bm);
+        p.ntn = (int)((r.N + bn - 1) / bn);
+        p.m0 = m0;
+        p.nm = nm;
+        launches[v].probs.push_back(p);
+        launches[v].tstart.push_back(launches[v].tstart.back() + nm * p.ntm * p.ntn);
+      };
+      if (alike) {
+        const int nm = (int)std::clamp<i64>(plan.first - unit, 0, kRes);
+        put(plan.v0, 0, nm);
+        put(plan.v1, nm, kRes - nm);
+        unit += kRes;
+      } else {
+        put(res_tile_of(r.M, r.N, p.kb_end - p.kb_begin, nullptr), 0, kRes);
+      }
     }
     macs += (double)r.M * (double)r.N * (double)(r.K0 + r.K1);
   }
-  // Tiles of one length run in a persistent launch, whose workgroups fetch the
-  // next tile's first steps during their epilogue; of uneven ones the hardware
-  // hands each workgroup one.
-  bool even = true;
-  for (const ResProblem& p : probs) even = even && p.kb_end - p.kb_begin == probs[0].kb_end - probs[0].kb_begin;
-  const int grid = even ? std::min(tstart.back(), res_tile_per_cu(tile) * c->num_cu) : tstart.back();
-  const bool inl = pk.fits_inline() && probs.size() <= (size_t)kResInline && outs.size() <= (size_t)kResInline;
-  ResGemmTables gt{};
+  bool inl = pk.fits_inline() && outs.size() <= (size_t)kResInline;
+  for (const Launch& l : launches) inl = inl && l.probs.size() <= (size_t)kResInline;
   ResOutTables ot{};
-  gt.nprob = (int)probs.size();
   ot.nout = (int)outs.size();
   uint8_t* dev = nullptr;
   if (inl) {
-    std::copy(probs.begin(), probs.end(), gt.iprobs);
-    std::copy(tstart.begin(), tstart.end(), gt.itile_start);
     std::copy(outs.begin(), outs.end(), ot.iouts);
     std::copy(ustart.begin(), ustart.end(), ot.iunit_start);
   } else {
     Blob blob;
     pk.add(blob);
-    const size_t op = blob.add(probs.data(), probs.size()), ots = blob.add(tstart.data(), tstart.size());
+    for (Launch& l : launches) {
+      l.op = blob.add(l.probs.data(), l.probs.size());
+      l.ots = blob.add(l.tstart.data(), l.tstart.size());
+    }
     const size_t oo = blob.add(outs.data(), outs.size()), ous = blob.add(ustart.data(), ustart.size());
     CHK(upload(c, blob, &dev));
-    gt.probs = (const ResProblem*)(dev + op);
-    gt.tile_start = (const int*)(dev + ots);
     ot.outs = (const ResOut*)(dev + oo);
     ot.unit_start = (const i64*)(dev + ous);
   }
   CHK(pk.issue(c, dev, launch_res_pack));
   LaunchTimer tm(c, MPC_FORM_LIMB8, macs);
   CHK(tm.start());
-  CHK(hip_status(launch_res_gemm(st, gt, tstart.back(), tile, grid, reqs[0].cv.ksz > 0)));
+  for (int v = 0; v < kResTiles; ++v) {
+    const Launch& l = launches[v];
+    if (l.probs.empty()) continue;
+    ResGemmTables gt{};
+    gt.nprob = (int)l.probs.size();
+    if (inl) {
+      std::copy(l.probs.begin(), l.probs.end(), gt.iprobs);
+      std::copy(l.tstart.begin(), l.tstart.end(), gt.itile_start);
+    } else {
+      gt.probs = (const ResProblem*)(dev + l.op);
+      gt.tile_start = (const int*)(dev + l.ots);
+    }
+    // Tiles of one length run in a persistent launch, whose workgroups fetch
+    // the next tile's first steps during their epilogue; of uneven ones the
+    // hardware hands each workgroup one.
+    bool even = true;
+    for (const ResProblem& p : l.probs) even = even && p.kb_end - p.kb_begin == l.probs[0].kb_end - l.probs[0].kb_begin;
+    const int tiles = l.tstart.back();
+    CHK(hip_status(launch_res_gemm(st, gt, tiles, v, even ? std::min(tiles, res_tile_per_cu(v) * c->num_cu) : tiles, reqs[0].cv.ksz > 0)));
+    c->stats.launches++;
+  }
   CHK(tm.stop());
   CHK(hip_status(launch_res_combine(st, ot, ustart.back())));
-  c->stats.launches += 2;
+  c->stats.launches++;
   c->stats.gemm_problems += reqs.size();
   return MPC_OK;
 }
@@ -1575,7 +1661,7 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
     for (int j = 0; j < i; ++j)
       if (overlap(bufs[i], ns[i], bufs[j], ns[j])) return MPC_E_ALIAS;
 
-  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, K, kind == MPC_TRIPLE_CONV1D ? &cs : nullptr);
+  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, 0, kind == MPC_TRIPLE_CONV1D ? &cs : nullptr);
   const Epilogue ep = make_ep(t->c0, -1, 0, t->c1, view);
   // the left factor is a (matmul) or the weight b (conv); the right one b or im2col(a)
   const u64 *L0 = kind == MPC_TRIPLE_MATMUL ? t->a0 : t->b0, *L1 = kind == MPC_TRIPLE_MATMUL ? t->a1 : t->b1;
@@ -1874,9 +1960,21 @@ void matmul_packed(const MatmulPlan& m, Carve& cv, int trunc, Form form, std::ve
                                     rowmajor_view(m.N))));
 }
 
+// A group's products: each in the form that suits it, if the residue form gains
+// enough on them together to be worth its own launches, whose tails leave the
+// chip part idle (a 256-problem batch with one such product, a gain of some 30
+// us by the model, took 40 us longer).
+constexpr double kGroupGainUs = 100;
 std::vector<Form> packing_forms(const std::vector<MatmulPlan>& plans) {
+  if (plans.size() == 1) return {packing_form(plans[0].M, plans[0].N, plans[0].K)};
   std::vector<Form> f;
-  for (const MatmulPlan& m : plans) f.push_back(packing_form(m.M, m.N, 2 * m.K));
+  double gain = 0;
+  for (const MatmulPlan& m : plans) {
+    const double g = residue_gain_us(m.M, m.N, 2 * m.K, 2, 3, 2, true);
+    gain += std::max(g, 0.0);
+    f.push_back(g > 0 ? kFormResidue : MPC_FORM_LIMB8);
+  }
+  if (gain < kGroupGainUs) f.assign(plans.size(), MPC_FORM_LIMB8);
   return f;
 }
 
@@ -1960,7 +2058,7 @@ mpc_status mpc_beaver_matmul(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const 
   MatmulPlan m{M, N, K, x0, x1, y0, y1, *t, z0, z1};
   CHK(validate_matmul(m));
   const bool automatic = want == MPC_FORM_AUTO;
-  const Form form = automatic && small_matmul(M, N, K) ? MPC_FORM_PLAIN : resolve_form(want, M, N, 2 * K, K);
+  const Form form = automatic && small_matmul(M, N, K) ? MPC_FORM_PLAIN : resolve_form(want, M, N, K, 2);
   CHK(check_limb_k(form, K));
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
@@ -2047,7 +2145,7 @@ mpc_status mpc_beaver_matmul_prepacked(mpc_ctx* c, int64_t M, int64_t N, int64_t
   CHK(check_limb_k(MPC_FORM_LIMB8, K));
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
-  CHK(run_matmuls(c, {m}, trunc_bits, packing_form(M, N, 2 * K)));
+  CHK(run_matmuls(c, {m}, trunc_bits, packing_form(M, N, K)));
   return end_call(c);
 }
 
@@ -2148,7 +2246,7 @@ mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const ui
   // transposed orientation: z_p[b][o][l] is element (o, b*Lout + l) of
   //   c_p + Wm(b_p) @ im2col(eps) + Wm(delta) @ im2col(g_p),  g_0 = a_0 + eps, g_1 = a_1
   const i64 M = s.cout, N = s.batch * lout, K = s.cin * s.ksize;
-  Form form = resolve_form(want, M, N, 2 * K, K, &s);
+  Form form = resolve_form(want, M, N, K, 2, &s);
   CHK(check_limb_k(form, K));
   const OutView view{lout, std::max<i64>(lout, 1), s.cout * lout};
   // delta, b0, b1 (weights); im2col of eps, g0, a1 (activations), or in the
@@ -2235,7 +2333,7 @@ mpc_status mpc_ring_gemm(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const uint
     return MPC_E_ALIAS;
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
-  Form form = resolve_form(want, M, N, K, K);
+  Form form = resolve_form(want, M, N, K, 0);
   CHK(check_limb_k(form, K));
   const Epilogue ep = make_ep(nullptr, +1, 0, C, rowmajor_view(N));
   JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
@@ -2915,7 +3013,7 @@ mpc_status mpc_mp_dealer_triples(mpc_ctx* c, int P, mpc_triple_kind kind, uint64
   CHK(mp_alias(a, P, na, {{&bi, nb}, {&ci, nc}}));
   CHK(mp_alias(b, P, nb, {{&ci, nc}}));
   if (!na && !nb && !nc) return MPC_OK;
-  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, K);
+  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, 0);
   // workspace: a = sum a_p, b = sum b_p, S = sum_{p<P-1} c_p, then the GEMM's packs
   JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
   CHK(ensure_form_ws(c, &form, true, [&](Form f) {
@@ -3005,7 +3103,7 @@ mpc_status mpc_mp_beaver_matmul(mpc_ctx* c, int P, int64_t M, int64_t N, int64_t
   CHK(mp_alias(zo, P, nc, {{&xi, na}, {&yi, nb}, {&ai, na}, {&bi, nb}, {&ci, nc}}));
   if (!nc) return MPC_OK;
   CHK(set_device(c));
-  Form form = resolve_form(want, M, N, 2 * K, K);
+  Form form = resolve_form(want, M, N, K, P);
   CHK(check_limb_k(form, K));
   const hipStream_t st = c->s[0];
   // open eps (MxK) and delta (KxN) into the workspace, then party p's finish

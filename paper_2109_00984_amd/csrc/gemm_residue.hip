@@ -82,6 +82,11 @@ constexpr u32 bal(u64 r, u64 m) { return (u32)((r > (m - 1) / 2 ? r - m : r) & 0
 struct ResConst {
   int wl[2], wr[2], neg_m, fold;  // fold: 256 mod m where the epilogue folds the high bits down, else 0
   float inv;
+  // The packing's byte sums start from the bits of the float `bias`, a multiple
+  // of 256 m next to 1.5 * 2^23, and so come out as the bits of bias + t: their
+  // quotient needs no conversion, and the bias drops out of the low byte.
+  int bias;
+  float back;  // 1.5 * 2^23 - bias / m
 };
 constexpr ResConst res_const(int i) {
   ResConst c{};
@@ -99,6 +104,9 @@ constexpr ResConst res_const(int i) {
   c.neg_m = -(int)m;
   c.fold = m >= 216 && m < 256 ? (int)(256 - m) : 0;
   c.inv = (float)(1.0 / (double)m);
+  const u64 step = 256 * m, bias = (((u64)3 << 22) + step / 2) / step * step;  // t below 2^18 keeps it in [2^23, 2^24)
+  c.bias = (int)(0x4b000000 + (u32)(bias - ((u64)1 << 23)));
+  c.back = (float)(12582912.0 - (double)(bias / m));
   return c;
 }
 struct ResConsts {
@@ -192,19 +200,20 @@ __device__ __forceinline__ void write_residues(uint8_t* dst, i64 plane, const u6
     }
     *(gv4i*)dst = w;
   }
+  ResConst k = g_res.c[1];
 #pragma unroll 1
   for (int i = 1; i < kRes; ++i) {
-    const int w0 = RIGHT ? g_res.c[i].wr[0] : g_res.c[i].wl[0], w1 = RIGHT ? g_res.c[i].wr[1] : g_res.c[i].wl[1];
-    const int neg_m = g_res.c[i].neg_m;
-    const float inv = g_res.c[i].inv;
+    const int w0 = RIGHT ? k.wr[0] : k.wl[0], w1 = RIGHT ? k.wr[1] : k.wl[1], neg_m = k.neg_m, bias = k.bias;
+    const float inv = k.inv, back = k.back;
+    k = g_res.c[i + 1 < kRes ? i + 1 : i];  // the next modulus' constants arrive behind this one's work
     v4i w;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       u32 r[4];
 #pragma unroll
       for (int b = 0; b < 4; ++b) {
-        const int t = __builtin_amdgcn_sdot4(hi[4 * x + b], w1, __builtin_amdgcn_sdot4(lo[4 * x + b], w0, 0, false), false);
-        r[b] = reduce(t, inv, neg_m);
+        const int t = __builtin_amdgcn_sdot4(hi[4 * x + b], w1, __builtin_amdgcn_sdot4(lo[4 * x + b], w0, bias, false), false);
+        r[b] = (u32)(__mul24(__float_as_int(__builtin_fmaf(__int_as_float(t), inv, back)), neg_m) + t);
       }
       w[x] = (int)low_bytes(r[0], r[1], r[2], r[3]);
     }
@@ -532,7 +541,7 @@ __device__ __forceinline__ ResPos res_pos(const ResView& tv, int idx) {
   const cptr<ResProblem> pp = tv.probs + q.pi;
   // modulus, then a grouped raster
   const int local = t - tv.tile_start[q.pi], ntm = pp->ntm, ntn = pp->ntn, per = ntm * ntn;
-  q.mi = local / per;
+  q.mi = pp->m0 + local / per;
   const int in_mod = local % per, first_m = in_mod / (kResGroupM * ntn) * kResGroupM;
   const int gsize = min(ntm - first_m, kResGroupM), in_group = in_mod % (kResGroupM * ntn);
   q.tm = first_m + in_group % gsize;

@@ -386,6 +386,7 @@ struct ResProblem {
   i64 pa, pb;              // plane strides of the operands
   int kbs, kb_begin, kb_end;
   int ntm, ntn;            // output tiles
+  int m0, nm;              // the moduli of this entry: [m0, m0 + nm)
   int n64;                 // units per row of units
   uint8_t* R;
   i64 pr;                  // plane stride of R
@@ -402,7 +403,7 @@ struct ResOut {
 constexpr int kResInline = 4;
 struct ResGemmTables {
   const ResProblem* probs;
-  const int* tile_start;   // nprob + 1 prefix sums of kRes * ntm * ntn
+  const int* tile_start;   // nprob + 1 prefix sums of nm * ntm * ntn
   int nprob, tiles;
   ResProblem iprobs[kResInline];
   int itile_start[kResInline + 1];

@@ -43,17 +43,17 @@ def same(a, b):
 
 @pytest.mark.parametrize("kind", ["uniform", "edge"])
 def test_ring_gemm_matches_oracle(m, c, kind):
-    M, N, K = 1025, 1030, 4929
+    M, N, K = 2500, 2305, 4161
     say(f"residue ring GEMM {M}x{N}x{K} {kind}")
     A, B = rnd(M + K, (M, K), kind), rnd(N + K, (K, N), kind)
-    rows, cols = np.r_[0:1025:97, 1008:1025], np.r_[0:1030:61, 1013:1030]
+    rows, cols = np.r_[0:2500:97, 2483:2500], np.r_[0:2305:61, 2288:2305]
     r, q = (v.ravel() for v in np.meshgrid(rows, cols))
     got = host(c, c.ring_gemm(dev(A), dev(B)))
     assert np.array_equal(got[r, q], oracle.ring_gemm_at(A, B, r, q))
 
 
-@pytest.mark.parametrize("M,N,K", [(1024, 1024, 4896), (1039, 1089, 4928), (1281, 1537, 4097), (3000, 700, 8191), (1024, 1024, 11008),
-                                   (1024, 1024, 11072), (1024, 1024, 11073), (1030, 1100, 22144), (1030, 1100, 22145)])
+@pytest.mark.parametrize("M,N,K", [(2048, 2048, 4096), (3000, 1700, 8191), (2500, 2305, 4161), (2048, 2048, 11008), (2048, 2048, 11072),
+                                   (2048, 2050, 11073), (2048, 2048, 22144), (2050, 2100, 22145)])
 @pytest.mark.parametrize("kind", ["uniform", "top"])
 def test_ring_gemm_matches_plain(m, c, M, N, K, kind):
     say(f"residue ring GEMM {M}x{N}x{K} {kind}")
@@ -61,7 +61,7 @@ def test_ring_gemm_matches_plain(m, c, M, N, K, kind):
     assert torch.equal(c.ring_gemm(A, B), c.ring_gemm(A, B, "plain"))
 
 
-@pytest.mark.parametrize("M,N,K,trunc", [(1025, 1300, 2200, 16), (1024, 1024, 2464, 0), (2050, 1050, 1900, 63)])
+@pytest.mark.parametrize("M,N,K,trunc", [(2048, 2048, 2048, 16), (1024, 1024, 4112, 0), (2300, 2304, 2512, 63), (3000, 2500, 3001, 16)])
 def test_beaver_matmul_matches_plain(m, c, M, N, K, trunc):
     say(f"residue Beaver matmul {M}x{N}x{K} trunc {trunc}")
     tag = M + 7 * N + 11 * K
@@ -82,7 +82,7 @@ def test_mixed_group_and_graph_replay(m):
     streams = (torch.cuda.Stream(), torch.cuda.Stream())
     c = m.Context(device=0, seed=SEED, streams=streams)
     with torch.cuda.stream(streams[0]):
-        shapes = [(300, 220, 500), (1040, 1030, 2500), (17, 200, 300), (1500, 1100, 3000), (40, 600, 64), (1025, 1281, 2304)]
+        shapes = [(300, 220, 500), (2040, 1040, 2512), (17, 200, 300), (1500, 2104, 3003), (40, 600, 64), (1825, 2281, 2304)]
         probs = []
         for i, (M, N, K) in enumerate(shapes):
             x, y = c.share(dev(rnd(i, (M, K))), 0, 2 * i), c.share(dev(rnd(50 + i, (K, N))), 1, 2 * i + 1)
@@ -108,7 +108,7 @@ def test_small_workspace_falls_back(m):
     """Where the workspace may not grow (under capture), a product that fits it in the limb form still runs."""
     streams = (torch.cuda.Stream(), torch.cuda.Stream())
     c, d = (m.Context(device=0, seed=SEED, streams=streams) for _ in range(2))
-    M, N, K = 1040, 1060, 2500
+    M, N, K = 2048, 2048, 2048
     with torch.cuda.stream(streams[0]):
         x, y = c.share(dev(rnd(1, (M, K))), 0, 1), c.share(dev(rnd(2, (K, N))), 1, 2)
         t = c.dealer(m.TRIPLE_MATMUL, DSEED, 3, (M, N, K))
@@ -144,7 +144,7 @@ def test_conv_matches_plain(m, c, B, cin, L, cout, k, s):
 
 @pytest.mark.parametrize("P", [2, 3, 5])
 def test_multiparty_matches_plain(m, c, P):
-    M, N, K = 1030, 1100, 2400
+    M, N, K = 2060, 2100, 2400
     x, y = c.mp_share(dev(rnd(1, (M, K))), P, 0, 1), c.mp_share(dev(rnd(2, (K, N))), P, 1, 2)
     t = c.mp_dealer(P, m.TRIPLE_MATMUL, DSEED, 4, (M, N, K))
     a, b = c.mp_beaver_matmul(x, y, t), c.mp_beaver_matmul(x, y, t, "plain")
