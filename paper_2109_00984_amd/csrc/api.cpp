@@ -1031,7 +1031,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
 
   // K pieces per request.  The int32 bound needs kbt / kLimbMaxKBlocks chunks,
   // run as consecutive launches that add into the output.  When the whole
-  // launch has fewer tiles than compute units, k is instead cut into slices
+  // launch fills at most half of the compute units, k is instead cut into slices
   // (at least that many) that run side by side in one launch, each writing
   // its raw sum to a partial buffer; a reduction adds them and applies the
   // epilogue (split-K).
@@ -1065,7 +1065,13 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
   }
   size_t part_bytes = 0;
   if (!no_alloc && tiles_all > 0 && tiles_all < c->num_cu) {
-    const i64 want = (2 * (i64)c->num_cu + tiles_all - 1) / tiles_all;
+    // As many slices as give every unit one workgroup, not two: a second
+    // workgroup on some units makes the launch as long as they take, and every
+    // slice has its own first loads, epilogue and partial sums (Beaver matmuls
+    // in a captured loop, two workgroups a unit against one: 128 x 1024 x 784
+    // 36.5 / 33.3 us, 1 x 1000 x 4000 68 / 63, 250 x 771 x 1750 76 / 64,
+    // 600 x 600 x 2000 121 / 108, 64 x 512 x 2048 33.1 / 33.7).
+    const i64 want = c->num_cu / tiles_all;
     for (size_t q = 0; q < nreq; ++q) {
       const i64 steps = (limb_kblocks(reqs[q].K0) + limb_kblocks(reqs[q].K1)) / 2;
       const i64 sl = std::max<i64>(nchunks[q], std::min<i64>(want, steps / kLimbMinSliceSteps));
