@@ -412,45 +412,45 @@ struct TilePos {
 
 // This workgroup's problem and its tile index inside that problem.
 template <int PER_CU>
-__device__ __forceinline__ void tile_of(const GemmView& v, int& pi, i64& local) {
+__device__ __forceinline__ void tile_of(const GemmView& v, int& pi, unsigned& local) {
   const int b = blockIdx.x;
   const int t = v.sched.xcd_remap ? remap_tile(b, gridDim.x, kXcdCUs * PER_CU) : b;
   pi = find_problem(v.tile_start, v.nprob, t);
-  local = t - v.tile_start[pi];
+  local = (unsigned)(t - v.tile_start[pi]);
 }
 
-// Tile coordinates of tile `local` of problem pi for a BM x BN tile.
+// Tile coordinates of tile `local` of problem pi for a BM x BN tile.  In 32
+// bits (a launch's tile count is an int): a 64-bit division costs as much as
+// several k steps of a wave's other scalar work, per tile.
 template <int BM, int BN>
-__device__ __forceinline__ TilePos tile_coords(const GemmView& v, int pi, i64 local) {
+__device__ __forceinline__ TilePos tile_coords(const GemmView& v, int pi, unsigned local) {
   TilePos q;
   q.pi = pi;
-  const i64 M = v.probs[pi].M, N = v.probs[pi].N;
-  const i64 ntm = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
+  const unsigned ntm = (unsigned)((v.probs[pi].M + BM - 1) / BM), ntn = (unsigned)((v.probs[pi].N + BN - 1) / BN);
   q.kbeg = v.probs[pi].kb_begin;
   q.kend = v.probs[pi].kb_end;
   q.shift = 0;
   const int ks = v.probs[pi].slices;
   if (ks > 1) {
-    const int sl = (int)(local / (ntm * ntn)), steps = (q.kend - q.kbeg) / 2;
-    local -= sl * ntm * ntn;
-    q.kend = q.kbeg + 2 * (int)((i64)steps * (sl + 1) / ks);
-    q.kbeg += 2 * (int)((i64)steps * sl / ks);
-    q.shift = sl * v.probs[pi].pstride;
+    const unsigned per = ntm * ntn, sl = local / per;
+    const int steps = (q.kend - q.kbeg) / 2;
+    local -= sl * per;
+    q.kend = q.kbeg + 2 * (int)((unsigned)steps * (sl + 1) / (unsigned)ks);
+    q.kbeg += 2 * (int)((unsigned)steps * sl / (unsigned)ks);
+    q.shift = (i64)sl * v.probs[pi].pstride;
   }
-  const i64 gm = v.sched.group_m;  // 1..64, checked by the host
-  const i64 per_group = gm * ntn;
-  const i64 first_m = (local / per_group) * gm;
-  const i64 gsize = min(ntm - first_m, gm);
-  const i64 in_group = local % per_group;
-  q.tm = first_m + in_group % gsize;
-  q.tn = in_group / gsize;
+  const unsigned gm = min((unsigned)v.sched.group_m, ntm);  // group_m: 1..64, checked by the host
+  const unsigned per_group = gm * ntn, group = local / per_group, in_group = local - group * per_group;
+  const unsigned first_m = group * gm, gsize = min(ntm - first_m, gm), col = in_group / gsize;
+  q.tm = first_m + (in_group - col * gsize);
+  q.tn = col;
   return q;
 }
 
 template <int BM, int BN, int PER_CU>
 __device__ __forceinline__ TilePos tile_pos(const GemmView& v) {
   int pi;
-  i64 local;
+  unsigned local;
   tile_of<PER_CU>(v, pi, local);
   return tile_coords<BM, BN>(v, pi, local);
 }
@@ -485,7 +485,8 @@ __device__ __forceinline__ void store_tile(v4i (&acc)[HA][HB][8], cptr<LimbProbl
   for (int y = 0; y < HB; ++y) {
     const i64 n = tn * BN + wc * 16 * HB + y * 16 + (lane & 15);
     const bool n_ok = n < pp->N;
-    const i64 coff = (n / ep.view.n_div) * ep.view.ld_q + (n % ep.view.n_div);
+    // (row-major outputs have no ld_q, and need no 64-bit division per column)
+    const i64 coff = ep.view.ld_q ? (n / ep.view.n_div) * ep.view.ld_q + (n % ep.view.n_div) : n;
 #pragma unroll
     for (int x = 0; x < HA; ++x)
 #pragma unroll
@@ -940,7 +941,7 @@ __global__ void __launch_bounds__(256, 2) k_limb_gemm_classes(GemmTables) {
   __shared__ v4i stage[2][kClassBuf / 16];
   const GemmView tv = gemm_view();
   int pi;
-  i64 local;
+  unsigned local;
   tile_of<2>(tv, pi, local);
   lds_u8* b0 = (lds_u8*)&stage[0][0];
   lds_u8* b1 = (lds_u8*)&stage[1][0];
@@ -1022,7 +1023,7 @@ __global__ void __launch_bounds__(256, 2) k_limb_gemm_persist(GemmTables) {
       continue;
     }
     const int pi = find_problem(tv.tile_start, tv.nprob, t);
-    const i64 local = t - tv.tile_start[pi];
+    const unsigned local = (unsigned)(t - tv.tile_start[pi]);
     const int cls = tv.probs[pi].cls;
     if (cls == 1)
       lds_tile<GClass1>(b0, b1, tv, tile_coords<GClass1::BM, GClass1::BN>(tv, pi, local));
