@@ -465,7 +465,7 @@ int res_tile_of(i64 M, i64 N, i64 steps, double* us) {
 // K summed k, each operand packed `outs` times over K / segs; the difference
 // of the two forms' times, in us: limb work at 3.1 PMAC-op/s, packed bytes at
 // 5.0 TB/s, the combine's 34 bytes an output at 4.4, the residue form's further
-// launches 6 us, and 8 % against the model's own error.  Measured, Beaver
+// launches 6 us, and 4 % against the model's own error.  Measured, Beaver
 // matmuls, limb against residue: 512 x 2048 x 2048 244 / 261 us, 512 x 2048 x
 // 4096 491 / 471, 1024 x 2048 x 1024 222 / 225, 1024 x 2048 x 2048 453 / 393,
 // 2048 x 2048 x 1024 441 / 410, 2048^3 859 / 678, 777 x 1500 x 3001 452 / 472;
@@ -487,7 +487,7 @@ double residue_gain_us(i64 M, i64 N, i64 K, int gemms, int outs, int segs, bool 
   const bool aligned = K / segs % 16 == 0 && N % 16 == 0;
   const double packed = (double)(M + N) * (double)(K / segs) * outs * ((kRes - 8.0) / 5.0e6 + (aligned ? 0.0 : 2.0e-6));
   const double res = gemm + packed + gemms * 34.0 * (double)M * (double)N / 4.4e6 + (grouped ? 0.0 : 6.0);
-  return limb - 1.08 * res;
+  return limb - 1.04 * res;
 }
 // A convolution packed without im2col writes its activation once, not once per
 // tap, so only its k (against the combine, 18 bytes an output) and its whole

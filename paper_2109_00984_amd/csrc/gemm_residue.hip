@@ -756,22 +756,32 @@ struct ResOutView {
 };
 
 // Bound by HBM: 18 bytes of residues, 8 of the added term and 8 stored an
-// output (two shares of 4096 x 4096: 0.26 ms, 4.3 TB/s).
-// One lane combines 16 outputs (its part of one unit of 16 rows x 64 columns):
-// 18 loads of 16 bytes a chunk, all in flight before the first is used.
+// output (two shares of 4096 x 4096: 0.23 ms, 4.9 TB/s).
+// One wave combines one unit of 16 rows x 64 columns: 18 loads of 16 bytes a
+// lane and chunk, all in flight before the first is used.  The residues come in
+// the GEMM's lane order (a lane holds 4 x 4 columns of one row); the outputs turn
+// through LDS so that the added term and the stores run along rows, 512
+// contiguous bytes an access (without, 16 rows of 8-byte pieces each: 0.28 ms).
+constexpr int kCombPad = 66;
 __global__ void __launch_bounds__(256) k_res_combine(ResOutTables) {
+  __shared__ u64 turn[4][16 * kCombPad];
   const cptr<ResOutTables> tp = (cptr<ResOutTables>)MPC_KERNARG_PTR();
   const cptr<ResOut> outs = tp->outs ? (cptr<ResOut>)(uintptr_t)tp->outs : tp->iouts;
   const cptr<i64> us = tp->outs ? (cptr<i64>)(uintptr_t)tp->unit_start : tp->iunit_start;
   const int nout = tp->nout;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const i64 un = (i64)blockIdx.x * 4 + wave;
-  if (un >= us[nout]) return;
+  if (un >= us[nout]) return;  // whole wave leaves; only wave-level sync below
   const int oi = find_job(us, nout, un);
   const cptr<ResOut> o = outs + oi;
   const i64 local = un - us[oi], real64 = (o->N + 63) / 64;
   const i64 ur = local / real64, uc = local % real64;
   const uint8_t* R = o->R + (ur * o->n64 + uc) * kResBlockBytes + lane * 16;
+  // after the turn: this lane's column, row by row; lanes past the edge read the first element
+  const Epilogue ep = o->ep;
+  const i64 m0 = ur * 16, n = uc * 64 + lane, M = o->M;
+  const bool n_ok = n < o->N;
+  const i64 coff = ep.view.ld_q ? n / ep.view.n_div * ep.view.ld_q + n % ep.view.n_div : n;
   u64 z[16];
 #pragma unroll
   for (int k = 0; k < 16; ++k) z[k] = 0;
@@ -798,28 +808,24 @@ __global__ void __launch_bounds__(256) k_res_combine(ResOutTables) {
       for (int e = 0; e < 4; ++e) z[4 * y + e] += combine_one(c[e]);
     }
   }
-  // the shared epilogue: added term, truncation, store (loads before stores)
-  const Epilogue ep = o->ep;
-  const i64 m = ur * 16 + (lane & 15), M = o->M, N = o->N;
-  i64 off[16];
-  bool ok[16];
+  u64* t = turn[wave];
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const i64 n = uc * 64 + (k >> 2) * 16 + (lane >> 4) * 4 + (k & 3);
-    ok[k] = m < M && n < N;
-    off[k] = ok[k] ? m * ep.view.ld_m + (ep.view.ld_q ? n / ep.view.n_div * ep.view.ld_q + n % ep.view.n_div : n) : 0;
-  }
+  for (int k = 0; k < 16; ++k) t[(lane & 15) * kCombPad + (k >> 2) * 16 + (lane >> 4) * 4 + (k & 3)] = z[k];
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) z[k] = t[k * kCombPad + lane];
+  // the shared epilogue: added term, truncation, store (loads before stores)
   if (ep.Cadd) {
     const u64 neg = ep.csign < 0 ? ~(u64)0 : 0;  // -c as (c ^ ~0) + 1
     u64 cv[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) cv[k] = ep.Cadd[off[k]];
+    for (int k = 0; k < 16; ++k) cv[k] = ep.Cadd[n_ok && m0 + k < M ? (m0 + k) * ep.view.ld_m + coff : 0];
 #pragma unroll
     for (int k = 0; k < 16; ++k) z[k] += (cv[k] ^ neg) + (neg & 1);
   }
 #pragma unroll
   for (int k = 0; k < 16; ++k)
-    if (ok[k]) ep.Out[off[k]] = ep.trunc_bits ? (u64)((i64)z[k] >> ep.trunc_bits) : z[k];
+    if (n_ok && m0 + k < M) ep.Out[(m0 + k) * ep.view.ld_m + coff] = ep.trunc_bits ? (u64)((i64)z[k] >> ep.trunc_bits) : z[k];
 }
 
 }  // namespace
