@@ -985,8 +985,7 @@ struct PackLaunch {
     else if (l.mode == kModeOpenLeft2) set = kPackMatmulPre;
     else if (l.mode == kModePrgSum2) set = kPackDeal;
     else if (l.mode == kModePrgSum2A) set = kPackDealPre;
-    else if (jobs.size() == 2) set = kPackRing;
-    else set = kPackParty;
+    else set = kPackRing;
   }
   bool fits_inline() const { return jobs.size() <= (size_t)kInlineJobs; }
   void add(Blob& blob) {
@@ -3112,43 +3111,41 @@ mpc_status mpc_mp_beaver_matmul(mpc_ctx* c, int P, int64_t M, int64_t N, int64_t
   Form form = resolve_form(want, M, N, K, P);
   CHK(check_limb_k(form, K));
   const hipStream_t st = c->s[0];
-  // open eps (MxK) and delta (KxN) into the workspace, then party p's finish
-  // z_p = c_p + [a_p + [p=0] eps | eps] @ [delta ; b_p]
+  // party p's finish z_p = c_p + [a_p + [p=0] eps | eps] @ [delta ; b_p]; the
+  // packing forms open eps (MxK) and delta (KxN) while they pack, the plain
+  // form into the workspace
   CHK(ensure_form_ws(c, &form, want == MPC_FORM_AUTO, [&](Form f) {
-    return kAlign + align_up(na * 8) + align_up(nb * 8) +
-           (packs(f) ? (size_t)(P + 1) * (align_up(packed_bytes(M, K, f)) + align_up(packed_bytes(N, K, f))) : 0) +
+    return kAlign + (packs(f) ? (size_t)(P + 1) * (align_up(packed_bytes(M, K, f)) + align_up(packed_bytes(N, K, f)))
+                              : align_up(na * 8) + align_up(nb * 8)) +
            (f == kFormResidue ? (size_t)P * res_out_bytes(M, N, K, K) : 0);
   }));
   Carve cv(c->ws);
-  u64* eps = cv.take<u64>(na);
-  u64* del = cv.take<u64>(nb);
-  CHK(hip_status(launch_mp_open(st, xi, ai, P, na, eps)));
-  CHK(hip_status(launch_mp_open(st, yi, bi, P, nb, del)));
-  c->stats.launches += 2;
   if (packs(form)) {
-    std::vector<PackJob> jobs;
-    JobSpec je = left_job(M, K, K), jd = right_job(K, N, N);
-    set_mode(je, kModeCopy, {eps});
-    set_mode(jd, kModeCopy, {del});
-    jobs.push_back(place_job(je, cv, form));
-    jobs.push_back(place_job(jd, cv, form));
-    std::vector<const uint8_t*> pa(P), pb(P);
-    for (int p = 0; p < P; ++p) {
-      JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
-      if (p == 0) set_mode(ja, kModeSum2, {ai.p[0], eps});
-      else set_mode(ja, kModeCopy, {ai.p[p]});
-      set_mode(jb, kModeCopy, {bi.p[p]});
-      jobs.push_back(place_job(ja, cv, form));
-      pa[p] = jobs.back().dst[0];
-      jobs.push_back(place_job(jb, cv, form));
-      pb[p] = jobs.back().dst[0];
+    PartyPackTables pt{};
+    const JobSpec spec[2] = {left_job(M, K, K), right_job(K, N, N)};
+    for (int side = 0; side < 2; ++side) {
+      PartyPack& s = pt.side[side];
+      s.job = place_job(spec[side], cv, form, 0);
+      s.P = P;
+      for (int p = 0; p < P; ++p) {
+        s.x[p] = side ? yi.p[p] : xi.p[p];
+        s.a[p] = side ? bi.p[p] : ai.p[p];
+      }
+      for (int p = 0; p <= P; ++p) s.dst[p] = cv.take<uint8_t>(job_out_bytes(spec[side], form));
     }
+    CHK(hip_status(form == kFormResidue ? launch_res_pack_party(st, pt) : launch_pack_party(st, pt)));
+    c->stats.launches++;
     std::vector<LimbReq> reqs;
     for (int p = 0; p < P; ++p)
-      reqs.push_back(limb_req(M, N, K, K, pa[p], jobs[0].dst[0], jobs[1].dst[0], pb[p],
+      reqs.push_back(limb_req(M, N, K, K, pt.side[0].dst[p], pt.side[0].dst[P], pt.side[1].dst[P], pt.side[1].dst[p],
                               make_ep(ci.p[p], +1, 0, zo.p[p], rowmajor_view(N))));
-    CHK(issue_packed(c, form, cv, jobs, reqs));
+    CHK(issue_packed(c, form, cv, {}, reqs));
   } else {
+    u64* eps = cv.take<u64>(na);
+    u64* del = cv.take<u64>(nb);
+    CHK(hip_status(launch_mp_open(st, xi, ai, P, na, eps)));
+    CHK(hip_status(launch_mp_open(st, yi, bi, P, nb, del)));
+    c->stats.launches += 2;
     std::vector<PlainProblem> probs;
     for (int p = 0; p < P; ++p)
       probs.push_back(plain_problem(M, N, K, K, ai.p[p], p == 0 ? eps : nullptr, K, eps, K, del, nullptr, N,

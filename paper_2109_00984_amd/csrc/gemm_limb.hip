@@ -120,6 +120,16 @@ __device__ __forceinline__ void pack_offsets(const PackJob& jb, i64 rb, i64 kb, 
   }
 }
 
+// A wave's 32x32 block from load layout (32 lanes along a row) to packed order.
+__device__ __forceinline__ void turn_rows(u64 (&w)[16], u64* t, int lane) {
+#pragma unroll
+  for (int q = 0; q < 16; ++q) t[(2 * q + (lane >> 5)) * kTPad + (lane & 31)] = w[q];
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int q = 0; q < 16; ++q) w[q] = t[(lane & 31) * kTPad + (lane >> 5) * 16 + q];
+  __builtin_amdgcn_wave_barrier();
+}
+
 // One wave packs one 32x32 block of every output of a job; all loads of a
 // lane are issued before any is used.  Right operands (COL, IM2COL) are read
 // in the packed lane order directly: for each k the 32 lanes of a half-wave
@@ -172,15 +182,7 @@ __device__ __forceinline__ void pack_block(const PackJob& jb, i64 local, u64* ti
     u64 w[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) w[q] = Md::out(o, v[q]);
-    if (KIND == kPackRow) {
-      u64* t = tile;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) t[(2 * q + (lane >> 5)) * kTPad + (lane & 31)] = w[q];
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int q = 0; q < 16; ++q) w[q] = t[(lane & 31) * kTPad + (lane >> 5) * 16 + q];
-      __builtin_amdgcn_wave_barrier();
-    }
+    if (KIND == kPackRow) turn_rows(w, tile, lane);
     write_limbs(jb.dst[o] + boff, lane, w);
   }
 }
@@ -204,6 +206,30 @@ __global__ void __launch_bounds__(kPackThreads) k_pack(PackTables, PackPairs<KM.
   const int pair = km(jb.kind, jb.mode);
   ((pair == KM ? pack_block<KM / 16, KM % 16>(jb, unit - start[ji], tile[wave], lane) : (void)0), ...);
 }
+
+template <int KIND>
+__device__ __forceinline__ void party_pack_block(cptr<PartyPack> s, i64 local, u64* tile, int lane) {
+  const PackJob jb = s->job;
+  const i64 rb = KIND == kPackRow ? local / jb.kblocks : local % jb.rreal;
+  const i64 kb = KIND == kPackRow ? local % jb.kblocks : local / jb.rreal;
+  const size_t boff = (size_t)(rb * jb.kblocks + kb) << 13;
+  i64 off[16];
+  bool ok[16];
+  pack_offsets<KIND>(jb, rb, kb, lane, off, ok);
+  party_block<KIND == kPackRow>(s, off, ok, (rb + 1) * 32 <= jb.rows && (kb + 1) * 32 <= jb.K, [&](uint8_t* dst, u64 (&w)[16]) {
+    if (KIND == kPackRow) turn_rows(w, tile, lane);
+    write_limbs(dst + boff, lane, w);
+  });
+}
+__global__ void __launch_bounds__(kPackThreads) k_pack_party(PartyPackTables) {
+  const cptr<PartyPackTables> t = (cptr<PartyPackTables>)MPC_KERNARG_PTR();
+  __shared__ u64 tile[4][32 * kTPad];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const i64 unit = (i64)blockIdx.x * 4 + wave, n0 = t->side[0].job.units;
+  if (unit < n0) party_pack_block<kPackRow>(&t->side[0], unit, tile[wave], lane);
+  else if (unit < n0 + t->side[1].job.units) party_pack_block<kPackCol>(&t->side[1], unit - n0, tile[wave], lane);
+}
+
 template <int... KM>
 hipError_t launch_pack_set(hipStream_t s, const PackTables& t, i64 units, PackPairs<KM...> pairs) {
   hipLaunchKernelGGL((k_pack<KM...>), dim3((unsigned)((units + 3) / 4)), dim3(kPackThreads), 0, s, t, pairs);
@@ -1364,9 +1390,16 @@ hipError_t launch_pack(hipStream_t s, const PackTables& t, i64 total_units, Pack
     case kPackDealPre: return launch_pack_set(s, t, total_units, SetPairs<kPackDealPre>::T{});
     case kPackDealConv: return launch_pack_set(s, t, total_units, SetPairs<kPackDealConv>::T{});
     case kPackRing: return launch_pack_set(s, t, total_units, SetPairs<kPackRing>::T{});
-    case kPackParty: return launch_pack_set(s, t, total_units, SetPairs<kPackParty>::T{});
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_pack_party(hipStream_t s, const PartyPackTables& t) {
+  const i64 units = t.side[0].job.units + t.side[1].job.units;
+  if (units <= 0) return hipSuccess;
+  if (t.side[0].P > kMaxParties || t.side[1].P > kMaxParties) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_pack_party, dim3((unsigned)((units + 3) / 4)), dim3(kPackThreads), 0, s, t);
+  return hipGetLastError();
 }
 
 int limb_persist_grid(int total_tiles, int num_cu) {

@@ -221,6 +221,16 @@ __device__ __forceinline__ void write_residues(uint8_t* dst, i64 plane, const u6
   }
 }
 
+// A wave's 16 x 64 block from load layout (64 lanes along a row) to packed order.
+__device__ __forceinline__ void res_turn_rows(u64 (&w)[16], u64* t, int lane) {
+#pragma unroll
+  for (int q = 0; q < 16; ++q) t[q * kResTPad + lane] = w[q];
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int q = 0; q < 16; ++q) w[q] = t[(lane & 15) * kResTPad + (lane >> 4) * 16 + q];
+  __builtin_amdgcn_wave_barrier();
+}
+
 // Bound by HBM: 32 bytes read and 54 written per element of a Beaver operand
 // (4096 x 4096: 0.29 ms, 5.0 TB/s; a copy of 2 GiB reaches 4.9).
 // One wave packs one 16 x 64 block of every output of a job; all loads of a
@@ -304,15 +314,7 @@ __device__ __forceinline__ void res_pack_block(const PackJob& jb, i64 local, u64
     u64 w[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) w[q] = Md::out(o, v[q]);
-    if constexpr (KIND == kPackRow) {
-      u64* t = tile;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) t[q * kResTPad + lane] = w[q];
-      __builtin_amdgcn_wave_barrier();
-#pragma unroll
-      for (int q = 0; q < 16; ++q) w[q] = t[(lane & 15) * kResTPad + (lane >> 4) * 16 + q];
-      __builtin_amdgcn_wave_barrier();
-    }
+    if constexpr (KIND == kPackRow) res_turn_rows(w, tile, lane);
     if constexpr (KIND == kPackConvRow) {
       u64* t = tiles;
 #pragma unroll
@@ -346,6 +348,31 @@ __global__ void __launch_bounds__(kPackThreads) k_res_pack(PackTables, PackPairs
   const int pair = km(jb.kind, jb.mode);
   ((pair == KM ? res_pack_block<KM / 16, KM % 16>(jb, unit - start[ji], tiles, wave, lane) : (void)0), ...);
 }
+
+template <int KIND>
+__device__ __forceinline__ void res_party_block(cptr<PartyPack> s, i64 local, u64* tile, int lane) {
+  const PackJob jb = s->job;
+  const i64 rb = KIND == kPackRow ? local / jb.kblocks : local % jb.rreal;
+  const i64 kb = KIND == kPackRow ? local % jb.kblocks : local / jb.rreal;
+  const i64 plane = jb.rblocks * jb.kblocks * kResBlockBytes;
+  const size_t boff = (size_t)(rb * jb.kblocks + kb) * kResBlockBytes + (size_t)lane * 16;
+  i64 off[16];
+  bool ok[16];
+  res_offsets<KIND>(jb, rb, kb, lane, off, ok);
+  party_block<KIND == kPackRow>(s, off, ok, (rb + 1) * 16 <= jb.rows && (kb + 1) * 64 <= jb.K, [&](uint8_t* dst, u64 (&w)[16]) {
+    if constexpr (KIND == kPackRow) res_turn_rows(w, tile, lane);
+    write_residues<KIND != kPackRow>(dst + boff, plane, w);
+  });
+}
+__global__ void __launch_bounds__(kPackThreads) k_res_pack_party(PartyPackTables) {
+  const cptr<PartyPackTables> t = (cptr<PartyPackTables>)MPC_KERNARG_PTR();
+  __shared__ u64 tile[4][16 * kResTPad];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const i64 unit = (i64)blockIdx.x * 4 + wave, n0 = t->side[0].job.units;
+  if (unit < n0) res_party_block<kPackRow>(&t->side[0], unit, tile[wave], lane);
+  else if (unit < n0 + t->side[1].job.units) res_party_block<kPackCol>(&t->side[1], unit - n0, tile[wave], lane);
+}
+
 template <int... KM>
 hipError_t launch_res_pack_set(hipStream_t s, const PackTables& t, i64 units, PackPairs<KM...> pairs) {
   hipLaunchKernelGGL((k_res_pack<KM...>), dim3((unsigned)((units + 3) / 4)), dim3(kPackThreads), 0, s, t, pairs);
@@ -849,9 +876,16 @@ hipError_t launch_res_pack(hipStream_t s, const PackTables& t, i64 total_units, 
     case kPackDealConv: return launch_res_pack_set(s, t, total_units, SetPairs<kPackDealConv>::T{});
     case kPackDealConvDirect: return launch_res_pack_set(s, t, total_units, SetPairs<kPackDealConvDirect>::T{});
     case kPackRing: return launch_res_pack_set(s, t, total_units, SetPairs<kPackRing>::T{});
-    case kPackParty: return launch_res_pack_set(s, t, total_units, SetPairs<kPackParty>::T{});
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_res_pack_party(hipStream_t s, const PartyPackTables& t) {
+  const i64 units = t.side[0].job.units + t.side[1].job.units;
+  if (units <= 0) return hipSuccess;
+  if (t.side[0].P > kMaxParties || t.side[1].P > kMaxParties) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_res_pack_party, dim3((unsigned)((units + 3) / 4)), dim3(kPackThreads), 0, s, t);
+  return hipGetLastError();
 }
 
 int res_tile_per_cu(int tile) {

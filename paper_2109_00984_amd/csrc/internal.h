@@ -296,7 +296,7 @@ hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceTables& t, i6
 // arguments: then no upload (no copy on the stream, no host staging) precedes
 // the launch.  The kernels read whichever the host filled through the
 // kernel-argument segment, as constant memory.
-constexpr int kInlineJobs = 12, kInlineProbs = 4;
+constexpr int kInlineJobs = 4, kInlineProbs = 4;
 // Jobs of one pack launch: `jobs`/`block_start` (device; njobs+1 prefix sums
 // of their units), or when `jobs` is null the first njobs entries of
 // ijobs/ibstart.
@@ -311,9 +311,24 @@ struct PackTables {
 // operands in one launch, a kernel per set.
 enum PackSet : int {
   kPackMatmul, kPackMatmulPre, kPackConv, kPackConvDirect, kPackDeal, kPackDealPre, kPackDealConv, kPackDealConvDirect,
-  kPackRing, kPackParty, kPackSets
+  kPackRing, kPackSets
 };
 hipError_t launch_pack(hipStream_t s, const PackTables& t, i64 total_units, PackSet set);
+// The open and pack of a Beaver matmul among P parties, both operands in one
+// launch: side 0 (ROW) x, a -> party p's a_p (a_0 + eps for party 0) and eps;
+// side 1 (COL) y, b -> b_p and delta.
+constexpr int kMaxParties = 16;
+struct PartyPack {
+  PackJob job;  // geometry only
+  int P;
+  const u64 *x[kMaxParties], *a[kMaxParties];
+  uint8_t* dst[kMaxParties + 1];  // the parties' operands, then at [P] the opened value
+};
+struct PartyPackTables {
+  PartyPack side[2];
+};
+hipError_t launch_pack_party(hipStream_t s, const PartyPackTables& t);
+hipError_t launch_res_pack_party(hipStream_t s, const PartyPackTables& t);
 // Tile shapes of the limb GEMM (workgroup output tile) and the tile order.
 // Variants 3..8 stage the outer operand through LDS (k_limb_gemm_lds); 6, 7
 // and 8 run eight waves per workgroup (two per SIMD): 6 and 7 with 16x64 and
@@ -457,7 +472,6 @@ hipError_t launch_relu(hipStream_t s, size_t n, const u64* x0, const u64* x1, u6
                        const TriplePtrs& m, u64* z0, u64* z1);
 
 // ---------------------------------------------------------------- more than two parties
-constexpr int kMaxParties = 16;
 struct MpOut {
   u64* p[kMaxParties];
 };
