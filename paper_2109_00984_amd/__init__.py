@@ -27,6 +27,9 @@ if not os.path.exists(LIB_PATH):
     raise ImportError(f"{LIB_PATH} is not built; run paper_2109_00984_amd/build.py "
                       "(or __graft_entry__.build())")
 _lib = ctypes.CDLL(LIB_PATH)
+# the same calls' checks, allocations and marshalling in native code, for the
+# small products whose time they are; it answers None where the Python code below is to run
+from . import _binding  # noqa: E402
 
 VP = ctypes.c_void_p
 I64 = ctypes.c_int64
@@ -293,6 +296,7 @@ class Context:
                                    VP(streams[1].cuda_stream), seed, ctypes.byref(h)),
                "mpc_ctx_create")
         self._h = h
+        self._at, self._index = h.value, device  # for the native calls
         self._graphs = set()
 
     def close(self):
@@ -300,7 +304,7 @@ class Context:
             for g in list(self._graphs):
                 g.destroy()
             _check(_lib.mpc_ctx_destroy(self._h), "mpc_ctx_destroy")
-            self._h = None
+            self._h, self._at = None, 0
 
     def __del__(self):
         try:
@@ -372,6 +376,10 @@ class Context:
         _check(_lib.mpc_reserve(self._h, int(nbytes)), "mpc_reserve")
 
     def share(self, x, src, tag, out=None):
+        r = _binding.share(self._at, self._index, x, src, tag, *((None, None) if out is None else (out.s0, out.s1)))
+        if r is not None:
+            _check(r[0], "mpc_share")
+            return SharedPair(r[1], r[2])
         self._check_t(x)
         s0, s1 = (self.empty(x.shape), self.empty(x.shape)) if out is None else (out.s0, out.s1)
         self._check_t(s0, s1, n=x.numel())
@@ -380,6 +388,10 @@ class Context:
         return SharedPair(s0, s1)
 
     def reveal(self, x, out=None):
+        r = _binding.reveal(self._at, self._index, x.s0, x.s1, out)
+        if r is not None:
+            _check(r[0], "mpc_reveal")
+            return r[1]
         self._check_t(x.s0, x.s1, out, n=x.s0.numel())
         out = self.empty(x.shape) if out is None else out
         _check(_lib.mpc_reveal(self._h, _ptr(x.s0), _ptr(x.s1), x.s0.numel(), _ptr(out)),
@@ -677,6 +689,12 @@ class Context:
     # -------------------------------------------------------------- Beaver
     def beaver_mul(self, x, y, t, trunc_bits=0, out=None):
         """y=None selects the square with a Beaver pair (t.a, t.b = a^2)."""
+        r = _binding.beaver_mul(self._at, self._index, x.s0, x.s1, *((None, None) if y is None else (y.s0, y.s1)),
+                                t.a0, t.a1, t.b0, t.b1, t.c0, t.c1, trunc_bits,
+                                *((None, None) if out is None else (out.s0, out.s1)))
+        if r is not None:
+            _check(r[0], "mpc_beaver_mul")
+            return SharedPair(r[1], r[2]) if out is None else out
         n = x.s0.numel()
         z = out if out is not None else SharedPair(self.empty(x.shape), self.empty(x.shape))
         self._check_t(x.s0, x.s1, z.s0, z.s1, *((y.s0, y.s1) if y is not None else ()), n=n)
@@ -689,6 +707,11 @@ class Context:
         return z
 
     def beaver_matmul(self, x, y, t, trunc_bits=0, form="auto", out=None):
+        r = _binding.beaver_matmul(self._at, self._index, x.s0, x.s1, y.s0, y.s1, t.a0, t.a1, t.b0, t.b1, t.c0, t.c1,
+                                   trunc_bits, FORMS.get(form), *((None, None) if out is None else (out.s0, out.s1)))
+        if r is not None:
+            _check(r[0], "mpc_beaver_matmul")
+            return SharedPair(r[1], r[2]) if out is None else out
         M, K = x.s0.shape
         K2, N = y.s0.shape
         if K != K2:

@@ -8,6 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libmpc.so")
+BINDING = os.path.join(HERE, "_binding.so")
 BUILD = os.path.join(ROOT, "_build")
 SOURCES = ["api.cpp", "elementwise.hip", "gemm_plain.hip", "gemm_limb.hip", "gemm_residue.hip", "gemm_fp64.hip",
            "multiparty.hip", "binary.hip"]
@@ -28,6 +29,25 @@ def _compile(src, verbose):
     return obj
 
 
+def _build_binding(verbose):
+    """The native part of the Python binding (host code over PyTorch's C++ API and libmpc.so)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    tmp = BINDING + ".tmp"
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+           *[f for d in cpp_extension.include_paths() for f in ("-isystem", d)], os.path.join(CSRC, "binding.cpp"), "-o", tmp,
+           "-L", HERE, "-l:libmpc.so", "-L", lib, "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(tmp, BINDING)
+
+
 def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
@@ -41,6 +61,7 @@ def build(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(tmp, OUT)
+    _build_binding(verbose)
     # the arithmetic-ceiling microbenchmark (a standalone program)
     cmd = ["hipcc", *[f for f in FLAGS if f != "-fPIC"], os.path.join(CSRC, "ceilings.hip"), "-o",
            os.path.join(HERE, "ceilings")]

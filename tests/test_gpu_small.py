@@ -88,3 +88,53 @@ def test_auto_without_workspace(m):
             c.sync()
             assert np.array_equal(out.cpu().numpy().view(np.uint64), oracle.ring_gemm(A, B))
     c.close()
+
+
+class _Sub(torch.Tensor):
+    pass
+
+
+def test_native_calls_match_python(m, c, monkeypatch):
+    """The native call of every entry point it has, with and without given outputs, equals the Python code's call (which
+    runs when the native one answers None, as for a tensor subclass), and what that refuses stays refused."""
+    M, N, K = 37, 21, 50
+    X, Y = dev(rnd(1, (M, K))), dev(rnd(2, (K, N)))
+    t, tm = c.dealer(m.TRIPLE_MATMUL, DSEED, 1, (M, N, K)), c.dealer(m.TRIPLE_MUL, DSEED, 2, (M * K,))
+    sq = c.dealer(m.TRIPLE_SQUARE, DSEED, 3, (M * K,))
+
+    def calls(out):
+        new = lambda *s: m.SharedPair(c.empty(s), c.empty(s)) if out else None  # noqa: E731
+        x, y = c.share(X, 0, 2**63 + 5, out=new(M, K)), c.share(Y, 1, 2, out=new(K, N))
+        w = c.share(X, 1, 9)
+        z = [c.beaver_matmul(x, y, t, 16, f, out=new(M, N)) for f in ("auto", "plain", "limb8")]
+        z += [c.beaver_mul(x, w, tm, 16, out=new(M, K)), c.beaver_mul(x, None, sq, 0, out=new(M, K)), c.beaver_mul(x, None, tm, 3)]
+        return [x.s0, x.s1] + [s for p in z for s in p] + [c.reveal(p, out=c.empty(p.shape) if out else None) for p in z]
+
+    native = [calls(False), calls(True)]
+
+    class Off:
+        def __getattr__(self, name):
+            return lambda *a: None
+    with monkeypatch.context() as mp:
+        mp.setattr(m, "_binding", Off())
+        want = calls(False)
+    for got in native:
+        assert all(torch.equal(g, w) and g.shape == w.shape for g, w in zip(got, want))
+    x, y = c.share(X, 0, 1), c.share(Y, 1, 2)
+    ref = c.beaver_matmul(x, y, t, 16)
+    sub = m.SharedPair(x.s0.as_subclass(_Sub), x.s1)
+    z = c.beaver_matmul(sub, y, t, 16)
+    assert torch.equal(z.s0, ref.s0) and torch.equal(z.s1, ref.s1)
+    bad = [lambda: c.beaver_matmul(m.SharedPair(x.s0.t(), x.s1.t()), y, t), lambda: c.beaver_matmul(y, x, t),
+           lambda: c.beaver_matmul(m.SharedPair(x.s0.to(torch.int32), x.s1), y, t), lambda: c.beaver_matmul(x, y, c.dealer(m.TRIPLE_MUL, DSEED, 4, (700,))),
+           lambda: c.beaver_matmul(m.SharedPair(x.s0[:-1], x.s1), y, t), lambda: c.beaver_matmul(m.SharedPair(x.s0.cpu(), x.s1), y, t),
+           lambda: c.beaver_mul(x, y, tm), lambda: c.beaver_mul(x, x, sq), lambda: c.reveal(m.SharedPair(x.s0, y.s0)),
+           lambda: c.share(X.to(torch.float64), 0, 1), lambda: c.share(X, 0, 1, out=y),
+           lambda: c.beaver_matmul(x, y, t, out=m.SharedPair(c.empty((M, N + 1)), c.empty((M, N))))]
+    for f in bad:
+        with pytest.raises(ValueError):
+            f()
+    with pytest.raises(m.MPCError):
+        c.beaver_matmul(x, y, t, 64)
+    with pytest.raises(m.MPCError):
+        c.share(X, 2, 1)
