@@ -955,9 +955,11 @@ std::vector<Region> limb_regions(const LimbReq& r, const TileSched& ts) {
 // The pack launches of one call: its jobs, ordered by kind and mode (the waves
 // of one workgroup then mostly run the same code), with the prefix sums of
 // their units, and the kernel for the kinds and modes among them.  One launch
-// where the tables fit the kernel arguments; a launch per kind where they do
-// not, so that a wave looks its job up in half the list (with one launch a
-// batch of some hundred products took 0.4 to 0.9 % longer).
+// where the tables fit the kernel arguments.  A group's jobs, which do not, run
+// in a launch per side: a wave looks its job up in half the list, and the right
+// side's kernel needs no LDS, which leaves more room beside another stream's
+// GEMM (three batches of 33 products on three streams, a batch: 586 us, 596 in
+// a kernel of both sides).
 struct PackLaunch {
   std::vector<PackJob> jobs;
   std::vector<size_t> first;               // first job of every launch, and the end
@@ -987,6 +989,11 @@ struct PackLaunch {
     else if (l.mode == kModePrgSum2A) set = kPackDealPre;
     else set = kPackRing;
   }
+  PackSet set_of(size_t L) const {
+    if (starts.size() > 1 && set == kPackMatmul) return L ? kPackMatmulRight : kPackMatmulLeft;
+    if (starts.size() > 1 && set == kPackMatmulPre) return L ? kPackMatmulPreRight : kPackMatmulPreLeft;
+    return set;
+  }
   bool fits_inline() const { return jobs.size() <= (size_t)kInlineJobs; }
   void add(Blob& blob) {
     for (const auto& s : starts) ostarts.push_back(blob.add(s.data(), s.size()));
@@ -1004,7 +1011,7 @@ struct PackLaunch {
         t.jobs = (const PackJob*)(dev + ojobs) + first[L];
         t.block_start = (const i64*)(dev + ostarts[L]);
       }
-      CHK(hip_status(launch(c->s[0], t, starts[L].back(), set)));
+      CHK(hip_status(launch(c->s[0], t, starts[L].back(), set_of(L))));
       c->stats.launches++;
     }
     return MPC_OK;

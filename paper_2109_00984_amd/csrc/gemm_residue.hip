@@ -876,6 +876,8 @@ hipError_t launch_res_pack(hipStream_t s, const PackTables& t, i64 total_units, 
     case kPackDealConv: return launch_res_pack_set(s, t, total_units, SetPairs<kPackDealConv>::T{});
     case kPackDealConvDirect: return launch_res_pack_set(s, t, total_units, SetPairs<kPackDealConvDirect>::T{});
     case kPackRing: return launch_res_pack_set(s, t, total_units, SetPairs<kPackRing>::T{});
+    case kPackMatmulLeft: return launch_res_pack_set(s, t, total_units, SetPairs<kPackMatmulLeft>::T{});
+    case kPackMatmulRight: return launch_res_pack_set(s, t, total_units, SetPairs<kPackMatmulRight>::T{});
     default: return hipErrorInvalidValue;
   }
 }

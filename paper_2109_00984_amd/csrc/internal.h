@@ -311,7 +311,9 @@ struct PackTables {
 // operands in one launch, a kernel per set.
 enum PackSet : int {
   kPackMatmul, kPackMatmulPre, kPackConv, kPackConvDirect, kPackDeal, kPackDealPre, kPackDealConv, kPackDealConvDirect,
-  kPackRing, kPackSets
+  kPackRing,
+  // one side of a group's products
+  kPackMatmulLeft, kPackMatmulRight, kPackMatmulPreLeft, kPackMatmulPreRight, kPackSets
 };
 hipError_t launch_pack(hipStream_t s, const PackTables& t, i64 total_units, PackSet set);
 // The open and pack of a Beaver matmul among P parties, both operands in one

@@ -119,6 +119,10 @@ template <> struct SetPairs<kPackDeal> { using T = PackPairs<km(kPackRow, kModeP
 template <> struct SetPairs<kPackDealPre> { using T = PackPairs<km(kPackRow, kModePrgSum2A), km(kPackCol, kModePrgSum2B)>; };
 template <> struct SetPairs<kPackDealConv> { using T = PackPairs<km(kPackRow, kModePrgSum2), km(kPackIm2col, kModeSum2)>; };
 template <> struct SetPairs<kPackDealConvDirect> { using T = PackPairs<km(kPackConvRow, kModePrgSum2), km(kPackChan, kModeSum2)>; };
+template <> struct SetPairs<kPackMatmulLeft> { using T = PackPairs<km(kPackRow, kModeOpenLeft)>; };
+template <> struct SetPairs<kPackMatmulRight> { using T = PackPairs<km(kPackCol, kModeOpenRight)>; };
+template <> struct SetPairs<kPackMatmulPreLeft> { using T = PackPairs<km(kPackRow, kModeOpenLeft2)>; };
+template <> struct SetPairs<kPackMatmulPreRight> { using T = PackPairs<km(kPackCol, kModeOpenRight1)>; };
 template <> struct SetPairs<kPackRing> { using T = PackPairs<km(kPackRow, kModeCopy), km(kPackCol, kModeCopy)>; };
 
 // One block of one side of a P-party open: every party's two shares are read
