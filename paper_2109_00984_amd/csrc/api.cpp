@@ -504,6 +504,14 @@ Form packing_form(i64 M, i64 N, i64 K, int P = 2) {
   return residue_gain_us(M, N, 2 * K, P, P + 1, 2, false) > 0 ? kFormResidue : MPC_FORM_LIMB8;
 }
 
+// The packing form of a dealt product whose a_1, b_0, b_1 are also packed for
+// the limb form: in the residue form that is a pass of its own, which reads
+// those shares again (at 5 TB/s) in one launch more.
+Form deal_packed_form(i64 M, i64 N, i64 K) {
+  const double again = (double)(M + 2 * N) * (double)K * 8.0 / 5.0e6 + 3.0;
+  return residue_gain_us(M, N, K, 1, 1, 1, false) > again ? kFormResidue : MPC_FORM_LIMB8;
+}
+
 // AUTO: a matrix-core form, unless the limb form cannot address the K segments
 // or they fill less than a quarter of its 64-wide k step.  The plain form's launches cost more than a small product
 // (ring GEMM in a captured loop, plain against limb: 64 x 32 x 128 17.5 / 10.8
@@ -2124,24 +2132,44 @@ mpc_status mpc_dealer_triples_packed(mpc_ctx* c, uint64_t dseed, uint64_t tag, i
   for (int sl = 0; sl < 6; ++sl) key[sl] = stream_key(dseed, tag, (u64)sl);
   CHK(set_device(c));
   // the same draws and the same c as mpc_dealer_triples: a_p, b_p drawn
-  // inside their packs (which also pack a_1, b_0, b_1 into `packed`), c_0
-  // from the PRG, c_1 = (a_0 + a_1) @ (b_0 + b_1) - c_0
+  // inside their packs, c_0 from the PRG, c_1 = (a_0 + a_1) @ (b_0 + b_1) - c_0
   JobSpec jl = left_job(M, K, K), jr = right_job(K, N, N);
   set_prg_sum2(jl, key[kSlotA0], key[kSlotA0 + 1], t->a0, t->a1);
   set_prg_sum2(jr, key[kSlotB0], key[kSlotB0 + 1], t->b0, t->b1);
-  jl.mode = kModePrgSum2A;
-  jr.mode = kModePrgSum2B;
-  CHK(ensure_ws(c, kAlign + align_up(packed_bytes(M, K)) + align_up(packed_bytes(N, K))));
+  Form form = deal_packed_form(M, N, K);
+  CHK(ensure_form_ws(c, &form, false, [&](Form f) {
+    return kAlign + align_up(packed_bytes(M, K, f)) + align_up(packed_bytes(N, K, f)) + (f == kFormResidue ? res_out_bytes(M, N, K, 0) : 0);
+  }));
   CHK(hip_status(launch_prg_fill(c->s[0], key[kSlotC0], t->c0, nc)));
   c->stats.launches++;
   Carve cv(c->ws);
-  PackJob L = place_job(jl, cv, MPC_FORM_LIMB8, 1), R = place_job(jr, cv, MPC_FORM_LIMB8, 1);
   uint8_t* pk = (uint8_t*)packed;
-  L.dst[1] = pk + off[0];
-  R.dst[1] = pk + off[1];
-  R.dst[2] = pk + off[2];
   const Epilogue ep = make_ep(t->c0, -1, 0, t->c1, rowmajor_view(N));
-  CHK(issue_limb(c, {L, R}, {limb_req(M, N, K, 0, L.dst[0], nullptr, R.dst[0], nullptr, ep)}, c->sched_default));
+  std::vector<PackJob> jobs;
+  if (form == kFormResidue) {
+    // the limb form's a_1, b_0, b_1 in a pack of their own, from the drawn shares
+    jobs = {place_job(jl, cv, form), place_job(jr, cv, form)};
+    CHK(issue_residue(c, cv, jobs, {limb_req(M, N, K, 0, jobs[0].dst[0], nullptr, jobs[1].dst[0], nullptr, ep)}));
+    JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
+    const u64* in[3] = {t->a1, t->b0, t->b1};
+    jobs.clear();
+    for (int i = 0; i < 3; ++i) {
+      JobSpec& j = i ? jb : ja;
+      set_mode(j, kModeCopy, {in[i]});
+      jobs.push_back(place_job(j, cv, MPC_FORM_LIMB8, 0));
+      jobs.back().dst[0] = pk + off[i];
+    }
+    CHK(PackLaunch(jobs).issue(c, nullptr, launch_pack));
+  } else {
+    // the packs also write a_1, b_0, b_1 to `packed`
+    jl.mode = kModePrgSum2A;
+    jr.mode = kModePrgSum2B;
+    jobs = {place_job(jl, cv, form, 1), place_job(jr, cv, form, 1)};
+    jobs[0].dst[1] = pk + off[0];
+    jobs[1].dst[1] = pk + off[1];
+    jobs[1].dst[2] = pk + off[2];
+    CHK(issue_limb(c, jobs, {limb_req(M, N, K, 0, jobs[0].dst[0], nullptr, jobs[1].dst[0], nullptr, ep)}, c->sched_default));
+  }
   return end_call(c);
 }
 

@@ -76,6 +76,27 @@ def test_beaver_matmul_matches_plain(m, c, M, N, K, trunc):
         assert same(z, want)
 
 
+@pytest.mark.parametrize("M,N,K", [(3072, 3072, 3072), (3001, 3303, 4001)])
+def test_dealt_packed_operands(m, c, M, N, K):
+    """The limb-packed a1, b0, b1 beside a c that is large enough for the residue form are those of a dealer's
+    product over the same a (of 64 columns) and over the same b (of 64 rows), which take the limb form."""
+    say(f"packed operands of a dealt product {M}x{N}x{K}")
+
+    def deal(M, N):
+        t = m.TripleShares(*(c.empty(s) for s in ((M, K), (M, K), (K, N), (K, N), (M, N), (M, N))))
+        packed = torch.zeros(c.packed_triple_bytes(M, N, K), dtype=torch.uint8, device="cuda")
+        c._dealer_packed_into(DSEED, 5, (M, N, K), t, packed)
+        c.sync()
+        return t, packed
+
+    t, packed = deal(M, N)
+    b64 = c.packed_triple_bytes(64, 64, K) // 3
+    a1 = c.packed_triple_bytes(M, 64, K) - 2 * b64
+    assert torch.equal(packed[:a1], deal(M, 64)[1][:a1])
+    assert torch.equal(packed[a1:], deal(64, N)[1][b64:])
+    assert torch.equal(t.c0 + t.c1, c.ring_gemm(t.a0 + t.a1, t.b0 + t.b1, "plain"))
+
+
 def test_mixed_group_and_graph_replay(m):
     """A group with products of both packing forms, more than fit the kernel arguments, eager and replayed."""
     say("residue and limb products in one group")
