@@ -4,8 +4,9 @@
 One step is one pass of the whole hot path over one 4096x4096x4096 problem
 with inputs resident in HBM: both operands secret-shared (PRZS), a fresh
 matrix Beaver triple from the dealer, the Beaver matmul (mask, device-local
-open, each party's finish GEMM with fused 2^16 truncation) in the limb (INT8
-matrix core) form, and the reveal.  `value` is plaintext-equivalent ring
+open, each party's finish GEMM with fused 2^16 truncation) on the INT8 matrix
+cores (over an offline-packed triple the library picks between the limb and
+the residue form), and the reveal.  `value` is plaintext-equivalent ring
 operations 2*M*N*K per step divided by the step time (Tops/s).
 
 Also reported (outside the timed region): the ring GEMM alone in both forms
@@ -28,6 +29,7 @@ sys.path.insert(0, ROOT)
 METRIC = ("secure int64-ring GEMM Tops/s (limb-MFMA vs plain, bit-exact); Beaver mul elem/s")
 INT8_PEAK_TOPS = 5000.0  # MI355X dense INT8 matrix peak, 5.0 POP/s
 HBM_PEAK_GBS = 8000.0
+RESIDUE_MODULI = 18  # int8 products per ring product in the residue form
 FP64_PEAK_TFLOPS = 78.6  # MI355X dense FP64 matrix peak
 M = N = K = 4096
 FRAC = 16
@@ -97,16 +99,25 @@ def main():
         ctx.share(Y, 1, 2, out=y)
         if packed_triples:
             ctx._dealer_packed_into(dealer_seed, 3, dims, t, packed)
-            ctx.beaver_matmul_prepacked(x, y, t, packed, FRAC, out=z)
         else:
             ctx.dealer_into(mpc.TRIPLE_MATMUL, dealer_seed, 3, dims, t)
-            ctx.beaver_matmul(x, y, t, FRAC, args.form, out=z)
+        online()
         ctx.reveal(z, out=r)
 
-    ctx.profile(True)
+    def online():
+        # only the finish GEMM, the step's dominant kernel, is timed by events
+        ctx.profile(True)
+        if packed_triples:
+            ctx.beaver_matmul_prepacked(x, y, t, packed, FRAC, out=z)
+        else:
+            ctx.beaver_matmul(x, y, t, FRAC, args.form, out=z)
+        ctx.profile(False)
+
     log(f"bench: warmup {args.warmup}")
     for _ in range(args.warmup):
         step()
+    ctx.sync()
+    residue = args.form == "limb8" and finish_in_residue_form(ctx, online)
     ctx.sync()
     ctx.profile_read()  # clear
     torch.cuda.synchronize()
@@ -118,28 +129,30 @@ def main():
     torch.cuda.synchronize()
     t1 = time.perf_counter()
     prof = ctx.profile_read()
-    ctx.profile(False)
     elapsed = t1 - t0
     ms_per_step = elapsed / args.steps * 1e3
     value = 2.0 * M * N * K * args.steps / elapsed / 1e12
     log(f"bench: {ms_per_step:.3f} ms/step, {value:.2f} Tops/s")
 
-    # dominant kernel: the ring GEMM launches of the timed region
+    # dominant kernel: the finish GEMM launches of the timed region
     g = prof[args.form]
     avg_ms = g["total_ms"] / max(1, g["launches"])
     if args.form == "limb8":
-        per_launch_ops = 72.0 * g["ring_macs"] / max(1, g["launches"])  # 36 int8 MACs per ring MAC
+        pairs = RESIDUE_MODULI if residue else 36  # int8 MACs per ring MAC
+        per_launch_ops = 2.0 * pairs * g["ring_macs"] / max(1, g["launches"])
         achieved = per_launch_ops / (avg_ms * 1e-3) / 1e12
-        tile = ctx.default_tile_config()
-        kernel = "k_limb_gemm_lds" if tile["variant"].startswith("lds") else "k_limb_gemm"
+        variant = ctx.default_tile_config()["variant"]
+        kernel = "k_res_gemm" if residue else "k_limb_gemm_lds" if variant.startswith("lds") else "k_limb_gemm"
+        tile = "by the shape (256x256 here)" if residue else variant
         traffic, alg_bytes = measured_traffic(kernel)
         roofline = {"bound": "mfma", "achieved": round(achieved, 1), "peak": INT8_PEAK_TOPS,
                     "unit": "TOP/s", "frac": round(achieved / INT8_PEAK_TOPS, 4),
                     "traffic": traffic, "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE "
                     "+ WRITE_SIZE, copy-calibrated)", "algorithmic_bytes_per_launch": alg_bytes,
-                    "kernel": kernel, "tile": tile["variant"], "launches": g["launches"],
+                    "kernel": kernel, "tile": tile, "launches": g["launches"],
                     "avg_launch_ms": round(avg_ms, 4),
-                    "work_per_launch": "72 int8 ops per ring multiply-accumulate (36 limb pairs)"}
+                    "work_per_launch": f"{2 * pairs} int8 ops per ring multiply-accumulate "
+                    + ("(18 moduli)" if residue else "(36 limb pairs)")}
     else:
         per_launch_ops = 2.0 * g["ring_macs"] / max(1, g["launches"])
         achieved = per_launch_ops / (avg_ms * 1e-3) / 1e12
@@ -210,21 +223,32 @@ def main():
     return 0
 
 
+def finish_in_residue_form(ctx, online):
+    """Whether the library runs this Beaver matmul in the residue form, which
+    it records as the limb form: told by its launches (open + pack, GEMM,
+    combine), where the limb form without split-K has two."""
+    ctx.sync()
+    before = ctx.stats()["launches"]
+    online()
+    return ctx.stats()["launches"] - before == 3
+
+
 def traffic_file(kernel):
     return os.path.join(ROOT, "profiles", f"{kernel}_secure_gemm_4096_traffic.md")
 
 
-LIMB_SOURCE = os.path.join(ROOT, "paper_2109_00984_amd", "csrc", "gemm_limb.hip")
+GEMM_SOURCES = {"k_res_gemm": ("gemm_residue.hip",)}  # else the limb GEMM's
 API_SOURCE = os.path.join(ROOT, "paper_2109_00984_amd", "csrc", "api.cpp")
 
 
-def kernel_fingerprint():
-    """sha256 over the limb GEMM source (comments and blank space dropped) and
-    the library's default tile schedule: the two things the GEMM's HBM traffic
-    depends on."""
+def kernel_fingerprint(kernel):
+    """sha256 over the GEMM's source (comments and blank space dropped) and
+    the library's default tile schedule: what the GEMM's HBM traffic depends
+    on."""
     import hashlib
     import re
-    src = open(LIMB_SOURCE).read()
+    src = "".join(open(os.path.join(os.path.dirname(API_SOURCE), f)).read()
+                  for f in GEMM_SOURCES.get(kernel, ("gemm_limb.hip",)))
     src = re.sub(r"//[^\n]*", "", src)
     src = "\n".join(" ".join(ln.split()) for ln in src.splitlines() if ln.strip())
     h = hashlib.sha256(src.encode())
@@ -234,7 +258,7 @@ def kernel_fingerprint():
 
 
 def measured_traffic(kernel):
-    """HBM bytes per limb-GEMM launch of this workload (and the algorithmic
+    """HBM bytes per finish-GEMM launch of this workload (and the algorithmic
     bytes beside them), from the committed rocprofv3 FETCH_SIZE / WRITE_SIZE
     summary, each counter scaled by its reading on a copy of known size.
     (None, None) when no summary exists or the kernel or its default schedule
@@ -249,7 +273,7 @@ def measured_traffic(kernel):
         k, _, v = line.partition(":")
         if k.strip() in keys:
             fields[k.strip()] = v.strip()
-    if any(k not in fields for k in keys) or fields["kernel_sha256"] != kernel_fingerprint():
+    if any(k not in fields for k in keys) or fields["kernel_sha256"] != kernel_fingerprint(kernel):
         return None, None
     return float(fields["hbm_bytes_per_launch"]), float(fields["algorithmic_bytes_per_launch"])
 
