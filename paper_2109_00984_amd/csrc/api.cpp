@@ -409,8 +409,12 @@ bool conv_direct(const mpc_conv1d_shape& s) {
 
 // Time of the residue GEMM's tiles: a round of workgroups over the compute
 // units takes a fixed part (first loads, epilogue) and one part per 64-wide k
-// step, as measured per tile shape on 4096 x 4096 outputs at k of 4096 and 8192.
-constexpr double kResFixedUs[kResTiles] = {5.8, 3.9, 3.9, 2.0}, kResStepUs[kResTiles] = {0.71, 0.82, 0.82, 0.48};
+// step.  256 x 256 as measured on 4096 x 4096 outputs at k of 4096 and 8192 and,
+// within 5 %, from 768 x 1536 up; the smaller tiles read more of their operands
+// from beyond the L2 where a GEMM has few of them, and take a fifth longer there
+// than on 4096 x 4096 (0.82, 0.82, 0.48 a step): 777 x 1500 x 3001, 36 GEMMs, 324
+// us in three rounds of 128 x 256, the 384 tiles of 128 x 128 beside 1024 x 1500 57.
+constexpr double kResFixedUs[kResTiles] = {5.8, 3.9, 3.9, 2.0}, kResStepUs[kResTiles] = {0.71, 1.0, 1.0, 0.60};
 constexpr int kPlanCUs = 256;
 double res_round_us(int v, i64 steps) { return kResFixedUs[v] + kResStepUs[v] * (double)steps; }
 i64 res_tiles(int v, i64 M, i64 N) {
@@ -465,18 +469,26 @@ int res_tile_of(i64 M, i64 N, i64 steps, double* us) {
 // K summed k, each operand packed `outs` times over K / segs; the difference
 // of the two forms' times, in us: limb work at 3.1 PMAC-op/s, packed bytes at
 // 5.0 TB/s, the combine's 34 bytes an output at 4.4, the residue form's further
-// launches 6 us, and 4 % against the model's own error.  Measured, Beaver
+// launches 6 us, and 2 % against the model's own error.  The limb form's last
+// round of 64 x 64 tiles (two workgroups a compute unit) takes 0.3 of a round at
+// least, however few its tiles are: 1100 x 900 x 2500, 540 tiles for 512 places,
+// 360 us against 317 in the residue form, 900 x 1200 x 1800, 570 tiles, 268 /
+// 230.  Measured, Beaver
 // matmuls, limb against residue: 512 x 2048 x 2048 244 / 261 us, 512 x 2048 x
 // 4096 491 / 471, 1024 x 2048 x 1024 222 / 225, 1024 x 2048 x 2048 453 / 393,
-// 2048 x 2048 x 1024 441 / 410, 2048^3 859 / 678, 777 x 1500 x 3001 452 / 472;
-// ring GEMMs 2048 x 2048 x 1024 114 / 119, 2048 x 2048 x 4096 435 / 376.
+// 2048 x 2048 x 1024 441 / 410, 2048^3 859 / 678, 700 x 1700 x 2100 313 / 299, 777 x
+// 1500 x 2048 307 / 326; ring GEMMs 2048 x 2048 x 1024 114 / 119, 1500 x 1500 x
+// 3000 218 / 179, 2048^3 211 / 207, 3000 x 1500 x 1000 129 / 140.
 // grouped: many products in one call, no rounding up to rounds.
 double residue_gain_us(i64 M, i64 N, i64 K, int gemms, int outs, int segs, bool grouped) {
   if (K < 256 || std::min(M, N) < 64) return -1;
   const double m64 = (double)((M + 63) / 64 * 64), n64 = (double)((N + 63) / 64 * 64);
   const i64 steps = (K + 63) / 64;
-  const double limb = gemms * 72.0 * m64 * n64 * (double)K / 3.1e9;
-  double gemm;
+  double limb = gemms * 72.0 * m64 * n64 * (double)K / 3.1e9, gemm;
+  if (!grouped) {
+    const double rounds = gemms * m64 * n64 / (4096.0 * 2 * kPlanCUs), full = std::floor(rounds);
+    if (full > 0 && rounds > full) limb *= (full + std::max(0.3, rounds - full)) / rounds;
+  }
   if (grouped) {
     res_tile_of(M, N, steps, &gemm);
     gemm *= gemms * kRes;
@@ -485,9 +497,9 @@ double residue_gain_us(i64 M, i64 N, i64 K, int gemms, int outs, int segs, bool 
   }
   // rows that do not start on 128-byte lines slow its packing more
   const bool aligned = K / segs % 16 == 0 && N % 16 == 0;
-  const double packed = (double)(M + N) * (double)(K / segs) * outs * ((kRes - 8.0) / 5.0e6 + (aligned ? 0.0 : 2.0e-6));
+  const double packed = (double)(M + N) * (double)(K / segs) * outs * ((kRes - 8.0) / 5.0e6 + (aligned ? 0.0 : 1.0e-6));
   const double res = gemm + packed + gemms * 34.0 * (double)M * (double)N / 4.4e6 + (grouped ? 0.0 : 6.0);
-  return limb - 1.04 * res;
+  return limb - 1.02 * res;
 }
 // A convolution packed without im2col writes its activation once, not once per
 // tap, so only its k (against the combine, 18 bytes an output) and its whole
