@@ -972,6 +972,36 @@ std::vector<Region> limb_regions(const LimbReq& r, const TileSched& ts) {
   return limb_regions(r.M, r.N, r.cls, ts.variant, r.ep.view.ld_q == 0 && r.ep.view.n_div >= r.N);
 }
 
+// k slices of a launch of `tiles` 64 x 64 tiles over `steps` k steps: what the
+// launch takes as whole rounds of two workgroups a unit (2.7 us a step) and a
+// last one, which takes less than half of that where no unit holds two of its
+// workgroups (1.2), and the slices' partial sums, written and read at 4.5 TB/s
+// by a launch more.  The 1.2 and 2.7 are a fit over 16 products, each at 1 to 8
+// slices; it picks the fastest or one within 3 % of it in all of them.  Beaver
+// matmuls, unsliced (or one workgroup a unit where that is more slices) against
+// its choice: 81 x 3157 x 4090 339 / 296 us (5), 128 x 5000 x 2000 275 / 249
+// (4), 500 x 1100 x 1000 103 / 94 (4), 515 x 515 x 4000 192 / 177 (3), 300 x
+// 4000 x 4000 678 / 650 (2), 250 x 771 x 1750 two slices of 8, 600 x 600 x 2000
+// and 400 x 1000 x 500 none.  Beyond three workgroups a unit nothing gains (600
+// x 3000 x 1500, 940 tiles: 334 / 359).
+constexpr i64 kSliceMaxWorkgroups = 3;  // a unit
+i64 limb_slices(i64 tiles, i64 steps, i64 min_slices, i64 outs, i64 cus) {
+  i64 pick = 1;
+  double best = -1;
+  const i64 top = std::max(min_slices, std::min(std::max<i64>(tiles < cus ? 8 : 4, cus / tiles), steps / (i64)kLimbMinSliceSteps));
+  for (i64 s = 1; s <= top; ++s) {
+    if (s > 1 && s < min_slices) continue;
+    const i64 groups = tiles * s, last = groups % (2 * cus), n = (steps + s - 1) / s;
+    double us = (double)n * ((double)(groups / (2 * cus)) * 2.7 + (last == 0 ? 0.0 : last <= cus ? 1.2 : 2.7));
+    if (s > 1) us += 2 + (double)(outs * 16 * s) / 4.5e6;
+    if (best < 0 || us < best) {
+      best = us;
+      pick = s;
+    }
+  }
+  return pick;
+}
+
 // The pack launches of one call: its jobs, ordered by kind and mode (the waves
 // of one workgroup then mostly run the same code), with the prefix sums of
 // their units, and the kernel for the kinds and modes among them.  One launch
@@ -1090,18 +1120,25 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
     tiles_all += tiles_of(q);
   }
   size_t part_bytes = 0;
-  if (!no_alloc && tiles_all > 0 && tiles_all < c->num_cu) {
-    // As many slices as give every unit one workgroup, not two: a second
-    // workgroup on some units makes the launch as long as they take, and every
-    // slice has its own first loads, epilogue and partial sums (Beaver matmuls
-    // in a captured loop, two workgroups a unit against one: 128 x 1024 x 784
-    // 36.5 / 33.3 us, 1 x 1000 x 4000 68 / 63, 250 x 771 x 1750 76 / 64,
-    // 600 x 600 x 2000 121 / 108, 64 x 512 x 2048 33.1 / 33.7).
-    const i64 want = c->num_cu / tiles_all;
+  // the default tiles, two workgroups a unit, over one k length
+  bool alike = true;
+  for (size_t q = 0; q < nreq; ++q) {
+    const int v = sched_of(q).variant;
+    alike = alike && (v == kLimbLds64x64 || v == kLimbClasses) && reqs[q].K0 == reqs[0].K0 && reqs[q].K1 == reqs[0].K1;
+  }
+  if (!no_alloc && tiles_all > 0 && tiles_all < (alike ? kSliceMaxWorkgroups : 1) * c->num_cu) {
+    // As many slices as give every unit one workgroup, or what the model of
+    // the default tiles' rounds says.
+    i64 want = c->num_cu / tiles_all;
+    if (alike) {
+      i64 outs = 0;
+      for (const LimbReq& r : reqs) outs += r.M * r.N;
+      want = limb_slices(tiles_all, (limb_kblocks(reqs[0].K0) + limb_kblocks(reqs[0].K1)) / 2, nchunks[0], outs, c->num_cu);
+    }
     for (size_t q = 0; q < nreq; ++q) {
       const i64 steps = (limb_kblocks(reqs[q].K0) + limb_kblocks(reqs[q].K1)) / 2;
       const i64 sl = std::max<i64>(nchunks[q], std::min<i64>(want, steps / kLimbMinSliceSteps));
-      if (sl > 1) {
+      if (sl > 1 && (want > 1 || tiles_all < c->num_cu)) {
         nslices[q] = (int)sl;
         part_bytes += align_up((size_t)(sl * reqs[q].M * reqs[q].N) * 8);
       }

@@ -61,6 +61,36 @@ def test_ring_gemm_auto(c, M, N, K):
         assert np.array_equal(host(c, c.ring_gemm(dev(A), dev(B), form)), want), form
 
 
+@pytest.mark.parametrize("M,N,K", [(81, 3157, 1000), (512, 1024, 1100), (500, 1100, 130), (777, 1500, 1001), (1500, 1000, 1030),
+                                   (1024, 1537, 777), (300, 200, 20000)])
+def test_k_slices(m, c, M, N, K):
+    """The limb form where its tiles leave a round of the chip partly empty (k slices), up to past the last size that
+    is sliced, eager and replayed, against the plain form."""
+    say(f"k slices {M}x{N}x{K}")
+    x, y = c.share(dev(rnd(M, (M, K))), 0, 1), c.share(dev(rnd(N, (K, N))), 1, 2)
+    t = c.dealer(m.TRIPLE_MATMUL, DSEED, K, (M, N, K))
+    want = c.beaver_matmul(x, y, t, 16, "plain")
+    z = c.beaver_matmul(x, y, t, 16, "limb8")
+    c.sync()
+    assert torch.equal(z.s0, want.s0) and torch.equal(z.s1, want.s1)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        g = m.Context(device=0, seed=SEED)
+        g.beaver_matmul(x, y, t, 16, "limb8", out=z)
+        g.sync()
+        g.graph_begin()
+        g.beaver_matmul(x, y, t, 16, "limb8", out=z)
+        gr = g.graph_end()
+        for _ in range(2):
+            z.s0.zero_()
+            z.s1.zero_()
+            g.graph_launch(gr)
+            g.sync()
+            assert torch.equal(z.s0, want.s0) and torch.equal(z.s1, want.s1)
+        m.Context.graph_destroy(gr)
+        g.close()
+
+
 @pytest.mark.parametrize("P", [2, 3, 7])
 @pytest.mark.parametrize("M,N,K", [(5, 9, 17), (64, 32, 128), (20, 300, 2000)])
 def test_party_matmul_auto(m, c, P, M, N, K):
