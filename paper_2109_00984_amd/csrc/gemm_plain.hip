@@ -11,6 +11,8 @@
 // aL*bL goes into a 64-bit accumulator (v_mad_u64_u32); the cross terms only
 // matter modulo 2^32 and go into a 32-bit accumulator that is shifted in once
 // at the end.
+#include <utility>
+
 #include "packed.h"
 
 namespace mpc {
@@ -231,48 +233,77 @@ hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceTables& t, i6
 }
 
 // Whole Beaver matmul of a small product in one launch.  A workgroup owns a
-// 4x4 block of outputs of both parties' shares; its 512 threads are those 16
-// outputs times 32 lanes of k (k = lane, lane + 32, ...): the launch is a chain
-// of dependent loads, 32 steps of k at the longest.  Measured in a captured
-// loop, with 16, 32 and 64 lanes: 64 x 64 x 256 7.0, 6.6 and 7.1 us, 64 x 64 x
-// 512 11.4, 10.2 and 11.1, 128 x 10 x 1024 20.6, 17.1 and 18.2 (the plain form's
-// open, GEMM and reduction 25 to 31, the limb form 19 to 20).  Each thread forms
-// the opened eps = x - a and delta = y - b of the elements it reads from the
-// shares themselves (an open pass and its workspace would cost more than the
-// product at this size), accumulates
+// 4x4 block of outputs of both parties' shares.  Each of its 512 threads takes
+// one column of the block and every 128th k: it forms the opened eps = x - a
+// and delta = y - b of the elements it reads from the shares themselves (an
+// open pass and its workspace would cost more than the product at this size)
+// and accumulates
 //   z_0 = eps b_0 + (a_0 + eps) delta,  z_1 = eps b_1 + a_1 delta
-// over its k, and the 32 partial sums of an output are added through LDS
-// before c_p and the truncation.  Ring sums do not depend on their order.
-constexpr int kSmallSide = 4, kSmallOut = kSmallSide * kSmallSide, kSmallKl = 32;
+// for the column's four rows.  Bound by the number of load instructions (some
+// 16 cycles each, and more where they touch more than 16 lines): 20 per 4
+// outputs and k, where a thread of one output has 8 per output (128 x 10 x 1024
+// 12.0 us, that form 16.8; the plain form's open, GEMM and reduction 25 to 31,
+// the limb form 19 to 20), and one of all 16, 2 per output, reads the right
+// operand in 64 lines an instruction (11.8 there, but 64 x 64 x 512 13.2 against
+// 7.7, 9.7 with one output; 64 x 32 x 128 5.7, 3.9 and 4.1).  The eight sums of
+// a wave's 16 threads of one column meet by a butterfly that halves the values
+// a lane holds with every step, then in LDS across the waves, before c_p and
+// the truncation.  Ring sums do not depend on their order.
+constexpr int kSmallSide = 4, kSmallOut = kSmallSide * kSmallSide, kSmallThreads = 512;
 
-__global__ void __launch_bounds__(kSmallOut * kSmallKl) k_beaver_matmul_small(SmallMatmul s) {
-  __shared__ u64 part[2][kSmallKl][kSmallOut];
-  const int o = threadIdx.x % kSmallOut, kl = threadIdx.x / kSmallOut;
-  const i64 ntn = (s.N + kSmallSide - 1) / kSmallSide;
-  const i64 m = (blockIdx.x / ntn) * kSmallSide + o / kSmallSide;
-  const i64 n = (blockIdx.x % ntn) * kSmallSide + o % kSmallSide;
-  const bool ok = m < s.M && n < s.N;
-  u64 z0 = 0, z1 = 0;
-  if (ok) {
-#pragma unroll 8
-    for (i64 k = kl; k < s.K; k += kSmallKl) {
-      const i64 ia = m * s.K + k, ib = k * s.N + n;
-      const u64 a0 = s.a0[ia], a1 = s.a1[ia], b0 = s.b0[ib], b1 = s.b1[ib];
+__global__ void __launch_bounds__(kSmallThreads) k_beaver_matmul_small(SmallMatmul s) {
+  constexpr int S = kSmallSide;
+  __shared__ u64 part[kSmallThreads / 64][2][kSmallOut];
+  const i64 ntn = (s.N + S - 1) / S;
+  const i64 m0 = (blockIdx.x / ntn) * S, n0 = (blockIdx.x % ntn) * S;
+  // rows and columns past the product's read its last one
+  const i64 nc = min(n0 + threadIdx.x % S, s.N - 1);
+  i64 row[S];
+#pragma unroll
+  for (int i = 0; i < S; ++i) row[i] = min(m0 + i, s.M - 1) * s.K;
+  u64 v[2 * S] = {};
+#pragma unroll 1
+  for (i64 k = threadIdx.x / S; k < s.K; k += kSmallThreads / S) {
+    const i64 ib = k * s.N + nc;
+    const u64 b0 = s.b0[ib], b1 = s.b1[ib];
+    const u64 del = (s.y0[ib] - b0) + (s.y1[ib] - b1);
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+      if (i && m0 + i >= s.M) break;
+      const i64 ia = row[i] + k;
+      const u64 a0 = s.a0[ia], a1 = s.a1[ia];
       const u64 eps = (s.x0[ia] - a0) + (s.x1[ia] - a1);
-      const u64 del = (s.y0[ib] - b0) + (s.y1[ib] - b1);
-      z0 += eps * b0 + (a0 + eps) * del;
-      z1 += eps * b1 + a1 * del;
+      v[i] += eps * b0 + (a0 + eps) * del;
+      v[S + i] += eps * b1 + a1 * del;
     }
   }
-  part[0][kl][o] = z0;
-  part[1][kl][o] = z1;
+  // lanes 32, 16 and 8 apart split the values they both hold: each ends with
+  // one, of party lane / 32 and row lane / 8 % 4
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  [&]<int... B>(std::integer_sequence<int, B...>) {
+    (
+        [&] {
+          constexpr int half = S >> B, d = 32 >> B;
+          const bool up = lane & d;
+#pragma unroll
+          for (int q = 0; q < half; ++q) {
+            const u64 keep = up ? v[q + half] : v[q], send = up ? v[q] : v[q + half];
+            v[q] = keep + __shfl_xor(send, d);
+          }
+        }(),
+        ...);
+  }(std::make_integer_sequence<int, 3>{});
+  v[0] += __shfl_xor(v[0], 4);
+  if (!(lane & 4)) part[wave][lane >> 5][(lane >> 3 & 3) * S + lane % S] = v[0];
   __syncthreads();
-  if (kl == 0 && ok) {
+  const int o = threadIdx.x;
+  const i64 m = m0 + o / S, n = n0 + o % S;
+  if (o < kSmallOut && m < s.M && n < s.N) {
     u64 v0 = 0, v1 = 0;
 #pragma unroll
-    for (int q = 0; q < kSmallKl; ++q) {
-      v0 += part[0][q][o];
-      v1 += part[1][q][o];
+    for (int w = 0; w < kSmallThreads / 64; ++w) {
+      v0 += part[w][0][o];
+      v1 += part[w][1][o];
     }
     const i64 off = m * s.N + n;
     v0 += s.c0[off];
@@ -291,7 +322,7 @@ int plain_tiles(i64 M, i64 N) { return (int)(((M + BM - 1) / BM) * ((N + BN - 1)
 hipError_t launch_beaver_matmul_small(hipStream_t s, const SmallMatmul& m) {
   const i64 tiles = ((m.M + kSmallSide - 1) / kSmallSide) * ((m.N + kSmallSide - 1) / kSmallSide);
   if (tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_beaver_matmul_small, dim3((unsigned)tiles), dim3(kSmallOut * kSmallKl), 0, s, m);
+  hipLaunchKernelGGL(k_beaver_matmul_small, dim3((unsigned)tiles), dim3(kSmallThreads), 0, s, m);
   return hipGetLastError();
 }
 
