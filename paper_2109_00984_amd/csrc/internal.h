@@ -255,9 +255,10 @@ struct SmallMatmul {
   int trunc;
 };
 // Products of at most kSmallMatmulMacs ring multiply-accumulates per party with
-// k at most kSmallMatmulK take it.  At 3 * 2^20 with k of 1024 it takes the limb
-// form's 20 us, at 2^21 with k of 128 to 512 10 us against 17 to 20; at 2^22.9
-// (200 x 200 x 200) 30 against 22, and at k of 2048 (2^21) 31 against 21.
+// k at most kSmallMatmulK take it.  At 3 * 2^20 with k of 1024 it takes 12.4 us
+// (64 x 48) to 16 (128 x 24, 30 x 100) against the limb form's 20.  Beyond, when
+// it had one output a thread (1.4 times the time), 200 x 200 x 200 took 30
+// against 22, and k of 2048 at 2^21 31 against 21.
 constexpr i64 kSmallMatmulMacs = (i64)3 << 20, kSmallMatmulK = 1024;
 inline bool small_matmul(i64 M, i64 N, i64 K) {
   return K <= kSmallMatmulK && M * N <= kSmallMatmulMacs && M * N * K <= kSmallMatmulMacs;
