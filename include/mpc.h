@@ -71,9 +71,10 @@ typedef enum {
  *          longer ones return MPC_E_UNSUPPORTED.
  *   AUTO:  the library's choice: PLAIN if its k is below 16 or longer than
  *          LIMB8 takes, or for a Beaver matmul of at most 3 * 2^20
- *          multiply-accumulates per party with k of at most 1024 (one launch);
- *          else LIMB8 or, where each operand element
- *          enters many outputs, a residue form of its own: the product modulo
+ *          multiply-accumulates per party (6 * 2^20 with the rows counted to a
+ *          multiple of four) with k of at most 1024 (one launch); else LIMB8
+ *          or, where each operand element enters many outputs, a residue form
+ *          of its own: the product modulo
  *          18 coprime moduli of at most 256, each an exact INT8 GEMM, put
  *          together by the Chinese remainder theorem.  Bit-identical to PLAIN;
  *          it takes a larger workspace (18 bytes a packed element and output,

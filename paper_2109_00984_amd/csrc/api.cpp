@@ -2127,7 +2127,7 @@ mpc_status mpc_beaver_matmul(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const 
   MatmulPlan m{M, N, K, x0, x1, y0, y1, *t, z0, z1};
   CHK(validate_matmul(m));
   const bool automatic = want == MPC_FORM_AUTO;
-  const Form form = automatic && small_matmul(M, N, K) ? MPC_FORM_PLAIN : resolve_form(want, M, N, K, 2);
+  const Form form = automatic && small_matmul_auto(M, N, K) ? MPC_FORM_PLAIN : resolve_form(want, M, N, K, 2);
   CHK(check_limb_k(form, K));
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
@@ -2289,7 +2289,7 @@ mpc_status mpc_beaver_matmul_noalloc(mpc_ctx* c, int64_t M, int64_t N, int64_t K
   if (M == 0 || N == 0) return MPC_OK;
   if (!c->scratch) return MPC_E_HIP;
   CHK(set_device(c));
-  if (form == MPC_FORM_AUTO && small_matmul(M, N, K)) {
+  if (form == MPC_FORM_AUTO && small_matmul_auto(M, N, K)) {
     // a small product: open and finish in one launch, no workspace at all
     const SmallMatmul s{M, N, K, x0, x1, y0, y1, t->a0, t->a1, t->b0, t->b1, t->c0, t->c1, z0, z1, trunc_bits};
     CHK(hip_status(launch_beaver_matmul_small(c->s[0], s)));

@@ -263,6 +263,13 @@ constexpr i64 kSmallMatmulMacs = (i64)3 << 20, kSmallMatmulK = 1024;
 inline bool small_matmul(i64 M, i64 N, i64 K) {
   return K <= kSmallMatmulK && M * N <= kSmallMatmulMacs && M * N * K <= kSmallMatmulMacs;
 }
+// AUTO's choice of it: rows count to a multiple of four, as a workgroup reads
+// its columns of the right operand for four rows whether they are there or not
+// (against the limb form: 1 x 3072 x 1024 61 / 48 us, 1 x 2048 x 1024 42 / 35, 1
+// x 10000 x 300 55 / 50; within: 2 x 1500 x 1024 30 / 32, 1 x 1024 x 784 18 / 26).
+inline bool small_matmul_auto(i64 M, i64 N, i64 K) {
+  return small_matmul(M, N, K) && (M + 3) / 4 * 4 * N * K <= 2 * kSmallMatmulMacs;
+}
 hipError_t launch_beaver_matmul_small(hipStream_t s, const SmallMatmul& m);
 hipError_t launch_plain_gemm(hipStream_t s, const PlainProblem* probs, TileMap map,
                              int total_tiles);

@@ -31,7 +31,7 @@ def rnd(seed, shape):
 
 
 @pytest.mark.parametrize("M,N,K,launches", [(1, 1, 1, 1), (4, 4, 32, 1), (5, 3, 33, 1), (3, 7, 31, 1), (64, 48, 1024, 1), (128, 10, 1024, 1),
-                                            (1024, 3, 1023, 1), (128, 128, 128, 1), (1, 3072, 1024, 1), (65, 48, 1024, None),
+                                            (1024, 3, 1023, 1), (128, 128, 128, 1), (1, 3072, 1024, None), (1, 1536, 1024, 1), (1, 1540, 1024, None), (65, 48, 1024, None),
                                             (16, 24, 1025, None), (7, 9, 2049, None)])
 @pytest.mark.parametrize("trunc", [0, 16])
 def test_beaver_matmul_auto(m, c, M, N, K, launches, trunc):
