@@ -71,8 +71,11 @@ typedef enum {
  *          longer ones return MPC_E_UNSUPPORTED.
  *   AUTO:  the library's choice: PLAIN if its k is below 16 or longer than
  *          LIMB8 takes, or for a Beaver matmul of at most 3 * 2^20
- *          multiply-accumulates per party (6 * 2^20 with the rows counted to a
- *          multiple of four) with k of at most 1024 (one launch); else LIMB8
+ *          multiply-accumulates per party with k of at most 1024 (one launch,
+ *          which PLAIN takes in the same range; beyond k of 48 also at most
+ *          6 * 2^20 with the rows counted to a multiple of four, and below k of
+ *          128 at most 2^14 blocks of 4 x 4 outputs unless it has at most 16
+ *          rows or columns); else LIMB8
  *          or, where each operand element enters many outputs, a residue form
  *          of its own: the product modulo
  *          18 coprime moduli of at most 256, each an exact INT8 GEMM, put

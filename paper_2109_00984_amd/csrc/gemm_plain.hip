@@ -232,8 +232,61 @@ hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceTables& t, i6
   return hipGetLastError();
 }
 
-// Whole Beaver matmul of a small product in one launch.  A workgroup owns a
-// 4x4 block of outputs of both parties' shares.  Each of its 512 threads takes
+// Whole Beaver matmul of a small product in one launch, for k below
+// kSmallMatmulShortK.  A workgroup owns a 4x4 block of outputs of both parties'
+// shares; its 256 threads are those 16 outputs times 16 lanes of k.  Bound by
+// the launch and the workgroups' own latency (4 us up to some 4000 outputs,
+// then 0.75 us per 1024 workgroups at k of 16 and less): the kernel below, with
+// 128 lanes of k and 512 threads, has most of them idle here.  This one against
+// that one: 256 x 256 x 1 5.5 / 16.2 us, 512 x 512 x 1 13.6 / 56.8, 256 x 256 x
+// 16 7.4 / 16.9, 256 x 256 x 32 10.9 / 18.3, 128 x 128 x 64 6.9 / 7.6, 128 x 128 x
+// 96 8.7 / 8.9; from 128 on the other way round (128 x 128 x 128 10.7 / 9.8, 128
+// x 128 x 192 14.2 / 11.9).
+constexpr int kShortSide = 4, kShortOut = kShortSide * kShortSide, kShortKl = kThreads / kShortOut;
+
+__global__ void __launch_bounds__(kThreads) k_beaver_matmul_short(SmallMatmul s) {
+  __shared__ u64 part[2][kShortKl][kShortOut];
+  const int o = threadIdx.x % kShortOut, kl = threadIdx.x / kShortOut;
+  const i64 ntn = (s.N + kShortSide - 1) / kShortSide;
+  const i64 m = (blockIdx.x / ntn) * kShortSide + o / kShortSide;
+  const i64 n = (blockIdx.x % ntn) * kShortSide + o % kShortSide;
+  const bool ok = m < s.M && n < s.N;
+  u64 z0 = 0, z1 = 0;
+  if (ok) {
+#pragma unroll 8
+    for (i64 k = kl; k < s.K; k += kShortKl) {
+      const i64 ia = m * s.K + k, ib = k * s.N + n;
+      const u64 a0 = s.a0[ia], a1 = s.a1[ia], b0 = s.b0[ib], b1 = s.b1[ib];
+      const u64 eps = (s.x0[ia] - a0) + (s.x1[ia] - a1);
+      const u64 del = (s.y0[ib] - b0) + (s.y1[ib] - b1);
+      z0 += eps * b0 + (a0 + eps) * del;
+      z1 += eps * b1 + a1 * del;
+    }
+  }
+  part[0][kl][o] = z0;
+  part[1][kl][o] = z1;
+  __syncthreads();
+  if (kl == 0 && ok) {
+    u64 v0 = 0, v1 = 0;
+#pragma unroll
+    for (int q = 0; q < kShortKl; ++q) {
+      v0 += part[0][q][o];
+      v1 += part[1][q][o];
+    }
+    const i64 off = m * s.N + n;
+    v0 += s.c0[off];
+    v1 += s.c1[off];
+    if (s.trunc) {
+      v0 = (u64)((i64)v0 >> s.trunc);
+      v1 = (u64)((i64)v1 >> s.trunc);
+    }
+    s.z0[off] = v0;
+    s.z1[off] = v1;
+  }
+}
+
+// The same for k of kSmallMatmulShortK and more.  A workgroup owns a 4x4 block
+// of outputs of both parties' shares.  Each of its 512 threads takes
 // one column of the block and every 128th k: it forms the opened eps = x - a
 // and delta = y - b of the elements it reads from the shares themselves (an
 // open pass and its workspace would cost more than the product at this size)
@@ -320,9 +373,11 @@ __global__ void __launch_bounds__(kSmallThreads) k_beaver_matmul_small(SmallMatm
 int plain_tiles(i64 M, i64 N) { return (int)(((M + BM - 1) / BM) * ((N + BN - 1) / BN)); }
 
 hipError_t launch_beaver_matmul_small(hipStream_t s, const SmallMatmul& m) {
-  const i64 tiles = ((m.M + kSmallSide - 1) / kSmallSide) * ((m.N + kSmallSide - 1) / kSmallSide);
+  static_assert(kShortSide == kSmallMatmulSide && kSmallSide == kSmallMatmulSide, "one grid for both");
+  const i64 tiles = small_matmul_groups(m.M, m.N);
   if (tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_beaver_matmul_small, dim3((unsigned)tiles), dim3(kSmallThreads), 0, s, m);
+  if (m.K < kSmallMatmulShortK) hipLaunchKernelGGL(k_beaver_matmul_short, dim3((unsigned)tiles), dim3(kThreads), 0, s, m);
+  else hipLaunchKernelGGL(k_beaver_matmul_small, dim3((unsigned)tiles), dim3(kSmallThreads), 0, s, m);
   return hipGetLastError();
 }
 

@@ -258,17 +258,29 @@ struct SmallMatmul {
 // k at most kSmallMatmulK take it.  At 3 * 2^20 with k of 1024 it takes 12.4 us
 // (64 x 48) to 16 (128 x 24, 30 x 100) against the limb form's 20.  Beyond, when
 // it had one output a thread (1.4 times the time), 200 x 200 x 200 took 30
-// against 22, and k of 2048 at 2^21 31 against 21.
-constexpr i64 kSmallMatmulMacs = (i64)3 << 20, kSmallMatmulK = 1024;
-inline bool small_matmul(i64 M, i64 N, i64 K) {
-  return K <= kSmallMatmulK && M * N <= kSmallMatmulMacs && M * N * K <= kSmallMatmulMacs;
+// against 22, and k of 2048 at 2^21 31 against 21.  With k below
+// kSmallMatmulShortK, where its time is that of its workgroups (0.75 us per
+// 1024), it takes at most 2^14 of them, unless a side is so short that the other
+// forms' tiles are mostly padding: 512 x 512 x 1 13.6 us against 15.9 in the
+// plain form and 16.5 in the limb form, 1024 x 1024 x 1 49 / 19 / 23, 32 x 32768
+// x 1 47 / 41 / 31, but 16 x 16384 x 8 16 / 24 / 20, 262144 x 1 x 1 51 / 109 / 201.
+constexpr i64 kSmallMatmulMacs = (i64)3 << 20, kSmallMatmulK = 1024, kSmallMatmulShortK = 128;
+constexpr i64 kSmallMatmulSide = 4;  // a workgroup's block of outputs is 4 x 4
+inline i64 small_matmul_groups(i64 M, i64 N) {
+  return ((M + kSmallMatmulSide - 1) / kSmallMatmulSide) * ((N + kSmallMatmulSide - 1) / kSmallMatmulSide);
 }
-// AUTO's choice of it: rows count to a multiple of four, as a workgroup reads
-// its columns of the right operand for four rows whether they are there or not
-// (against the limb form: 1 x 3072 x 1024 61 / 48 us, 1 x 2048 x 1024 42 / 35, 1
-// x 10000 x 300 55 / 50; within: 2 x 1500 x 1024 30 / 32, 1 x 1024 x 784 18 / 26).
+inline bool small_matmul(i64 M, i64 N, i64 K) {
+  return K <= kSmallMatmulK && M * N <= kSmallMatmulMacs && M * N * K <= kSmallMatmulMacs &&
+         (K >= kSmallMatmulShortK || M <= 16 || N <= 16 || small_matmul_groups(M, N) <= (i64)1 << 14);
+}
+// AUTO's choice of it: beyond k of 48 rows count to a multiple of four, as a
+// workgroup reads its columns of the right operand for four rows whether they
+// are there or not (against the limb form: 1 x 3072 x 1024 61 / 48 us, 1 x 2048 x
+// 1024 42 / 35, 1 x 10000 x 300 55 / 50; within: 2 x 1500 x 1024 30 / 32, 1 x 1024
+// x 784 18 / 26).  Shorter, a single row's long limb tiles cost more: 1 x 65536 x
+// 32 40 / 52, x 48 57 / 57, x 64 75 / 62.
 inline bool small_matmul_auto(i64 M, i64 N, i64 K) {
-  return small_matmul(M, N, K) && (M + 3) / 4 * 4 * N * K <= 2 * kSmallMatmulMacs;
+  return small_matmul(M, N, K) && (K <= 48 || (M + 3) / 4 * 4 * N * K <= 2 * kSmallMatmulMacs);
 }
 hipError_t launch_beaver_matmul_small(hipStream_t s, const SmallMatmul& m);
 hipError_t launch_plain_gemm(hipStream_t s, const PlainProblem* probs, TileMap map,

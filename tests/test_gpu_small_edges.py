@@ -1,0 +1,40 @@
+"""The one-launch Beaver matmul at the edges of its two kernels (k lanes of 16 and of 128, 4 x 4 blocks of outputs) and
+of the range in which a short k takes it, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import dev, pair, say
+
+pytestmark = pytest.mark.gpu
+
+SEED, DSEED = 2071, 3071
+
+
+@pytest.fixture(scope="module")
+def m():
+    import paper_2109_00984_amd as mpc
+    return mpc
+
+
+@pytest.fixture(scope="module")
+def c(m):
+    ctx = m.Context(device=0, seed=SEED)
+    yield ctx
+    ctx.close()
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 1, 0), (1, 1, 1), (5, 7, 1), (4, 4, 15), (3, 5, 16), (9, 6, 17), (33, 30, 126), (64, 48, 127), (61, 47, 128),
+                                   (17, 19, 129), (5, 3, 255), (6, 9, 256), (7, 2, 257), (512, 511, 1), (513, 512, 1), (300, 700, 3), (1, 9000, 17),
+                                   (9001, 1, 16), (16, 4099, 5), (1, 2000, 49), (2, 3, 1023), (3, 2, 1024)])
+@pytest.mark.parametrize("form", ["auto", "plain"])
+def test_matches_oracle(m, c, M, N, K, form):
+    say(f"small Beaver matmul {M}x{N}x{K} {form}")
+    tag = M + 7 * N + 11 * K
+    g = np.random.default_rng(tag)
+    X, Y = (g.integers(0, 2**64, size=s, dtype=np.uint64) for s in ((M, K), (K, N)))
+    x, y = c.share(dev(X), 0, 1), c.share(dev(Y), 1, 2)
+    t = c.dealer(m.TRIPLE_MATMUL, DSEED, tag, (M, N, K))
+    got = pair(c, c.beaver_matmul(x, y, t, 16, form))
+    want = oracle.beaver_matmul(oracle.share(X, 0, SEED, 1), oracle.share(Y, 1, SEED, 2), oracle.dealer_matmul(DSEED, tag, M, N, K), 16)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])

@@ -1,0 +1,34 @@
+"""Which kernels a call launches, from the library's own host code without a GPU (tests/host_double.py)."""
+import pytest
+
+from tests.host_double import Double, form
+
+
+@pytest.fixture()
+def d():
+    c = Double()
+    yield c
+    c.close()
+
+
+# ---------------------------------------------------------------- the one-launch kernel
+@pytest.mark.parametrize("M,N,K,small", [(1, 1, 1, True), (256, 256, 1, True), (512, 512, 1, True), (512, 513, 1, False), (1024, 1024, 1, False),
+                                         (1000, 1000, 3, False), (3031, 518, 2, False), (449, 591, 5, False), (32, 32768, 1, False),
+                                         (16, 16384, 8, True), (262144, 1, 1, True), (1, 262144, 4, True), (512, 512, 12, True),
+                                         (128, 128, 127, True), (128, 128, 128, True), (128, 192, 128, True), (128, 193, 128, False),
+                                         (3072, 1, 1024, True), (16, 16, 1025, False)])
+def test_one_launch_only_where_its_workgroups_pay(d, M, N, K, small):
+    """Its time is that of its 4 x 4 blocks where k is short: not for many of them (1000 x 1000 x 3 took 247 us in it,
+    23 in the plain form)."""
+    for f in ("auto", "plain"):
+        log = d.matmul(M, N, K, f)
+        assert (form(log) == "small") == small, (f, log)
+        assert not small or len(log) == 1
+
+
+def test_one_launch_single_rows(d):
+    """AUTO counts rows to a multiple of four beyond k of 48, where the kernel shares the columns' loads among them."""
+    assert form(d.matmul(1, 65536, 48)) == "small" and form(d.matmul(1, 32768, 49)) == "limb"
+    assert form(d.matmul(1, 32768, 49, "plain")) == "small"
+    assert form(d.matmul(1, 1536, 1024)) == "small" and form(d.matmul(1, 1540, 1024)) == "limb"
+    assert form(d.matmul(1, 1540, 1024, "plain")) == "small"
