@@ -69,13 +69,17 @@ typedef enum {
  *          Each operand's k range (K of a product; each of the two halves of
  *          a Beaver finish, whose summed k is 2K) is at most 2,097,088 long;
  *          longer ones return MPC_E_UNSUPPORTED.
- *   AUTO:  the library's choice: PLAIN if its k is below 16 or longer than
- *          LIMB8 takes, or for a Beaver matmul of at most 3 * 2^20
+ *   AUTO:  the library's choice.  PLAIN if k is longer than LIMB8 takes, or
+ *          below 16 where that is faster: products of less than 2^22
+ *          multiply-adds (summed k), and of k of at most 8 with at least 96
+ *          rows and 2^22 outputs (a public product: any k below 16; the
+ *          many-party product: any with k of at most 8; the dealer: none).
+ *          PLAIN also for a Beaver matmul of at most 3 * 2^20
  *          multiply-accumulates per party with k of at most 1024 (one launch,
  *          which PLAIN takes in the same range; beyond k of 48 also at most
  *          6 * 2^20 with the rows counted to a multiple of four, and below k of
  *          128 at most 2^14 blocks of 4 x 4 outputs unless it has at most 16
- *          rows or columns); else LIMB8
+ *          rows or columns).  Else LIMB8
  *          or, where each operand element enters many outputs, a residue form
  *          of its own: the product modulo
  *          18 coprime moduli of at most 256, each an exact INT8 GEMM, put

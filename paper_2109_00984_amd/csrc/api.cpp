@@ -524,18 +524,41 @@ Form deal_packed_form(i64 M, i64 N, i64 K) {
   return residue_gain_us(M, N, K, 1, 1, 1, false) > again ? kFormResidue : MPC_FORM_LIMB8;
 }
 
+// A product as AUTO tells them apart: of public operands, of dealt ones, and
+// Beaver products of two parties' calls and of many parties'.
+enum ProductKind { kProductPublic, kProductDealt, kProductBeaver, kProductParties };
+
+// AUTO below kLimbMinSegK, where the operands fill less than a quarter of the
+// limb form's 64-wide k step.  Below 2^22 multiply-adds the plain form.  Beyond,
+// its upload (12 us of the host's time), its 128-row tiles and its k steps of 16
+// cost more, except for many outputs of at least 96 rows with k of at most 8 (15
+// in a product of public operands), and for k of at most 8 in the many-party
+// call, which packs 2 (P + 1) operands.  In a captured loop, plain against limb:
+// Beaver matmuls 2048 x 2048 x 3 47 / 56 us, 4096 x 4096 x 8 163 / 193, x 15 216 /
+// 193, 16 x 100000 x 15 155 / 74, 64 x 64000 x 12 106 / 71, 512 x 4096 x 3 31 / 36
+// (but eager 43 / 35); public products 2048 x 2048 x 15 20 / 25; five parties
+// 40000 x 64 x 1 65 / 119, 2048 x 2048 x 8 109 / 135, 64 x 64000 x 9 250 / 174; the
+// dealer 64 x 64000 x 12 62 / 49; convolutions of 8 x 1 x 16000 to 64 channels
+// with 15 taps 227 / 152, to 512 with 3 taps 608 / 846.
+constexpr i64 kLimbMinSegK = 16;
+Form short_k_form(ProductKind kind, i64 M, i64 N, i64 K, bool beaver) {
+  if ((double)M * (double)N * (double)K * (beaver ? 2 : 1) < (double)(1 << 22)) return MPC_FORM_PLAIN;
+  if (kind == kProductDealt) return MPC_FORM_LIMB8;
+  if (kind == kProductParties) return K <= 8 ? MPC_FORM_PLAIN : MPC_FORM_LIMB8;
+  return M >= 96 && (double)M * (double)N >= (double)(1 << 22) && (kind == kProductPublic || K <= 8) ? MPC_FORM_PLAIN : MPC_FORM_LIMB8;
+}
+
 // AUTO: a matrix-core form, unless the limb form cannot address the K segments
-// or they fill less than a quarter of its 64-wide k step.  The plain form's launches cost more than a small product
+// or k is short.  The plain form's launches cost more than a small product
 // (ring GEMM in a captured loop, plain against limb: 64 x 32 x 128 17.5 / 10.8
 // us, 200 x 100 x 50 28.6 / 10.4, 4 x 4 x 8192 34 / 19, 512 x 512 x 16 10.8 /
-// 10.9, 1024 x 1024 x 4 11.6 / 12.2; among three parties 23.8 / 18.6, 33.0 /
-// 17.6, 94 / 36, 24.3 / 18.9, 26.0 / 35.4).
-constexpr i64 kLimbMinSegK = 16;
+// 10.9; among three parties 23.8 / 18.6, 33.0 / 17.6, 94 / 36, 24.3 / 18.9).
 // parties: of a Beaver product over K k, or 0 for one product of public or
 // dealt operands.
-Form resolve_form(Form f, i64 M, i64 N, i64 K, int parties, const mpc_conv1d_shape* conv = nullptr) {
+Form resolve_form(Form f, ProductKind kind, i64 M, i64 N, i64 K, int parties, const mpc_conv1d_shape* conv = nullptr) {
   if (f != MPC_FORM_AUTO) return f;
-  if (K > kLimbMaxSegK || K < kLimbMinSegK) return MPC_FORM_PLAIN;
+  if (K > kLimbMaxSegK) return MPC_FORM_PLAIN;
+  if (K < kLimbMinSegK) return short_k_form(kind, M, N, K, parties > 0);
   const int gemms = parties ? parties : 1, outs = parties ? parties + 1 : 1, segs = parties ? 2 : 1;
   const bool res = conv ? residue_pays_conv(*conv, N, segs * K, gemms, outs, segs) : residue_gain_us(M, N, segs * K, gemms, outs, segs, false) > 0;
   return res ? kFormResidue : MPC_FORM_LIMB8;
@@ -1730,7 +1753,7 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
     for (int j = 0; j < i; ++j)
       if (overlap(bufs[i], ns[i], bufs[j], ns[j])) return MPC_E_ALIAS;
 
-  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, 0, kind == MPC_TRIPLE_CONV1D ? &cs : nullptr);
+  Form form = resolve_form(MPC_FORM_AUTO, kProductDealt, M, N, K, 0, kind == MPC_TRIPLE_CONV1D ? &cs : nullptr);
   const Epilogue ep = make_ep(t->c0, -1, 0, t->c1, view);
   // the left factor is a (matmul) or the weight b (conv); the right one b or im2col(a)
   const u64 *L0 = kind == MPC_TRIPLE_MATMUL ? t->a0 : t->b0, *L1 = kind == MPC_TRIPLE_MATMUL ? t->a1 : t->b1;
@@ -2127,7 +2150,7 @@ mpc_status mpc_beaver_matmul(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const 
   MatmulPlan m{M, N, K, x0, x1, y0, y1, *t, z0, z1};
   CHK(validate_matmul(m));
   const bool automatic = want == MPC_FORM_AUTO;
-  const Form form = automatic && small_matmul_auto(M, N, K) ? MPC_FORM_PLAIN : resolve_form(want, M, N, K, 2);
+  const Form form = automatic && small_matmul_auto(M, N, K) ? MPC_FORM_PLAIN : resolve_form(want, kProductBeaver, M, N, K, 2);
   CHK(check_limb_k(form, K));
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
@@ -2335,7 +2358,7 @@ mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const ui
   // transposed orientation: z_p[b][o][l] is element (o, b*Lout + l) of
   //   c_p + Wm(b_p) @ im2col(eps) + Wm(delta) @ im2col(g_p),  g_0 = a_0 + eps, g_1 = a_1
   const i64 M = s.cout, N = s.batch * lout, K = s.cin * s.ksize;
-  Form form = resolve_form(want, M, N, K, 2, &s);
+  Form form = resolve_form(want, kProductBeaver, M, N, K, 2, &s);
   CHK(check_limb_k(form, K));
   const OutView view{lout, std::max<i64>(lout, 1), s.cout * lout};
   // delta, b0, b1 (weights); im2col of eps, g0, a1 (activations), or in the
@@ -2422,7 +2445,7 @@ mpc_status mpc_ring_gemm(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const uint
     return MPC_E_ALIAS;
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
-  Form form = resolve_form(want, M, N, K, 0);
+  Form form = resolve_form(want, kProductPublic, M, N, K, 0);
   CHK(check_limb_k(form, K));
   const Epilogue ep = make_ep(nullptr, +1, 0, C, rowmajor_view(N));
   JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
@@ -3102,7 +3125,7 @@ mpc_status mpc_mp_dealer_triples(mpc_ctx* c, int P, mpc_triple_kind kind, uint64
   CHK(mp_alias(a, P, na, {{&bi, nb}, {&ci, nc}}));
   CHK(mp_alias(b, P, nb, {{&ci, nc}}));
   if (!na && !nb && !nc) return MPC_OK;
-  Form form = resolve_form(MPC_FORM_AUTO, M, N, K, 0);
+  Form form = resolve_form(MPC_FORM_AUTO, kProductDealt, M, N, K, 0);
   // workspace: a = sum a_p, b = sum b_p, S = sum_{p<P-1} c_p, then the GEMM's packs
   JobSpec ja = left_job(M, K, K), jb = right_job(K, N, N);
   CHK(ensure_form_ws(c, &form, true, [&](Form f) {
@@ -3192,7 +3215,7 @@ mpc_status mpc_mp_beaver_matmul(mpc_ctx* c, int P, int64_t M, int64_t N, int64_t
   CHK(mp_alias(zo, P, nc, {{&xi, na}, {&yi, nb}, {&ai, na}, {&bi, nb}, {&ci, nc}}));
   if (!nc) return MPC_OK;
   CHK(set_device(c));
-  Form form = resolve_form(want, M, N, K, P);
+  Form form = resolve_form(want, kProductParties, M, N, K, P);
   CHK(check_limb_k(form, K));
   const hipStream_t st = c->s[0];
   // party p's finish z_p = c_p + [a_p + [p=0] eps | eps] @ [delta ; b_p]; the

@@ -38,3 +38,20 @@ def test_matches_oracle(m, c, M, N, K, form):
     got = pair(c, c.beaver_matmul(x, y, t, 16, form))
     want = oracle.beaver_matmul(oracle.share(X, 0, SEED, 1), oracle.share(Y, 1, SEED, 2), oracle.dealer_matmul(DSEED, tag, M, N, K), 16)
     assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("M,N,K", [(2048, 2050, 8), (2048, 2050, 9), (96, 43691, 8), (95, 23000, 1), (16, 30000, 15)])
+def test_short_k_forms_agree(m, c, M, N, K):
+    """What AUTO takes for k below 16 against the plain form, for every call that chooses."""
+    say(f"short k {M}x{N}x{K}")
+    g = np.random.default_rng(M + K)
+    A, B = (dev(g.integers(0, 2**64, size=s, dtype=np.uint64)) for s in ((M, K), (K, N)))
+    want = c.ring_gemm(A, B, "plain")
+    assert (c.ring_gemm(A, B) == want).all()
+    t = c.dealer(m.TRIPLE_MATMUL, DSEED, 5, (M, N, K))
+    assert (t.c0 + t.c1 == c.ring_gemm(t.a0 + t.a1, t.b0 + t.b1, "plain")).all()
+    x, y = c.share(A, 0, 1), c.share(B, 1, 2)
+    z, p = c.beaver_matmul(x, y, t, 16), c.beaver_matmul(x, y, t, 16, "plain")
+    assert (z.s0 == p.s0).all() and (z.s1 == p.s1).all()
+    xs, ys, tm = c.mp_share(A, 3, 0, 1), c.mp_share(B, 3, 1, 2), c.mp_dealer(3, m.TRIPLE_MATMUL, DSEED, 6, (M, N, K))
+    assert (c.mp_reveal(c.mp_beaver_matmul(xs, ys, tm)) == want).all()

@@ -32,3 +32,27 @@ def test_one_launch_single_rows(d):
     assert form(d.matmul(1, 32768, 49, "plain")) == "small"
     assert form(d.matmul(1, 1536, 1024)) == "small" and form(d.matmul(1, 1540, 1024)) == "limb"
     assert form(d.matmul(1, 1540, 1024, "plain")) == "small"
+
+
+# ---------------------------------------------------------------- k below 16
+@pytest.mark.parametrize("M,N,K,beaver,ring,deal,party", [
+    (2048, 2048, 4, "plain", "plain", "limb", "plain"), (4096, 4096, 8, "plain", "plain", "limb", "plain"),
+    (4096, 4096, 9, "limb", "plain", "limb", "limb"), (2048, 2048, 15, "limb", "plain", "limb", "limb"),
+    (16, 100000, 15, "limb", "limb", "limb", "limb"), (64, 200000, 12, "limb", "limb", "limb", "limb"),
+    (95, 50000, 8, "limb", "limb", "limb", "plain"), (96, 43691, 8, "plain", "plain", "limb", "plain"),
+    (96, 43690, 8, "limb", "limb", "limb", "plain"), (512, 4096, 8, "limb", "limb", "limb", "plain"),
+    (1, 4000000, 3, "limb", "limb", "limb", "plain"), (1024, 1024, 1, "plain", "plain", "plain", "plain"),
+    (2048, 2048, 0, "plain", "plain", "plain", "plain"), (2048, 2048, 16, "limb", "limb", "limb", "limb")])
+def test_short_k(d, M, N, K, beaver, ring, deal, party):
+    """AUTO below k of 16 (16 x 100000 x 15 took 154 us in the plain form, 82 in the limb form)."""
+    assert form(d.matmul(M, N, K)) == beaver
+    assert form(d.ring(M, N, K)) == ring
+    assert form(d.deal(M, N, K)) == deal
+    assert form(d.party(3, M, N, K)) == party
+
+
+@pytest.mark.parametrize("conv,online,dealt", [((8, 3, 8000, 64, 5, 1), "limb", "limb"), ((8, 1, 160000, 32, 9, 4), "limb", "limb"),
+                                               ((8, 1, 16000, 64, 15, 1), "limb", "limb"), ((8, 1, 16000, 512, 3, 1), "plain", "limb"),
+                                               ((64, 1, 4000, 128, 7, 1), "plain", "limb"), ((1, 1, 160, 32, 15, 1), "plain", "plain")])
+def test_short_k_convolutions(d, conv, online, dealt):
+    assert form(d.conv(*conv)) == online and form(d.deal_conv(*conv)) == dealt
