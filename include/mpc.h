@@ -79,7 +79,7 @@ typedef enum {
  *          which PLAIN takes in the same range; beyond k of 48 also at most
  *          6 * 2^20 with the rows counted to a multiple of four, and below k of
  *          128 at most 2^14 blocks of 4 x 4 outputs unless it has at most 16
- *          rows or columns).  Else LIMB8
+ *          rows or 8 columns).  Else LIMB8
  *          or, where each operand element enters many outputs, a residue form
  *          of its own: the product modulo
  *          18 coprime moduli of at most 256, each an exact INT8 GEMM, put

@@ -263,7 +263,8 @@ struct SmallMatmul {
 // 1024), it takes at most 2^14 of them, unless a side is so short that the other
 // forms' tiles are mostly padding: 512 x 512 x 1 13.6 us against 15.9 in the
 // plain form and 16.5 in the limb form, 1024 x 1024 x 1 49 / 19 / 23, 32 x 32768
-// x 1 47 / 41 / 31, but 16 x 16384 x 8 16 / 24 / 20, 262144 x 1 x 1 51 / 109 / 201.
+// x 1 47 / 41 / 31, 100000 x 16 x 1 75 / 61 / 72, but 16 x 100000 x 1 77 / 99 / 71,
+// 200000 x 4 x 1 39 / 98 / 148, 262144 x 1 x 1 51 / 109 / 201.
 constexpr i64 kSmallMatmulMacs = (i64)3 << 20, kSmallMatmulK = 1024, kSmallMatmulShortK = 128;
 constexpr i64 kSmallMatmulSide = 4;  // a workgroup's block of outputs is 4 x 4
 inline i64 small_matmul_groups(i64 M, i64 N) {
@@ -271,7 +272,7 @@ inline i64 small_matmul_groups(i64 M, i64 N) {
 }
 inline bool small_matmul(i64 M, i64 N, i64 K) {
   return K <= kSmallMatmulK && M * N <= kSmallMatmulMacs && M * N * K <= kSmallMatmulMacs &&
-         (K >= kSmallMatmulShortK || M <= 16 || N <= 16 || small_matmul_groups(M, N) <= (i64)1 << 14);
+         (K >= kSmallMatmulShortK || M <= 16 || N <= 8 || small_matmul_groups(M, N) <= (i64)1 << 14);
 }
 // AUTO's choice of it: beyond k of 48 rows count to a multiple of four, as a
 // workgroup reads its columns of the right operand for four rows whether they
