@@ -380,7 +380,8 @@ typedef struct {
  * exact GEMM problems that a Beaver matmul (count = 1) or a grouped call of
  * these `count` shapes issues in the limb form (dims: HOST array of M, N, K
  * per problem), on random operands, and remembers each class's fastest for
- * later calls with the same shapes, unless one launch of all of them is
+ * later calls with the same shapes (of whose products those use it that run in
+ * the limb form), unless one launch of all of them is
  * faster than the classes' separate launches (each single schedule, and
  * schedules 14 and 15 with every product in its own class, are timed that way).  `best` (may be NULL) receives the
  * schedule of the class that takes longest and, in `ms`, the summed time of

@@ -2090,12 +2090,14 @@ mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int tru
     Carve cv(c->ws);
     std::vector<PackJob> jobs, rjobs;
     std::vector<LimbReq> reqs, rreqs;
-    std::vector<std::array<i64, 3>> shapes;
+    std::vector<std::array<i64, 3>> shapes;  // of all products: the list that a tuned schedule is kept under
+    std::vector<size_t> owner;               // the product of each pair of limb requests
     for (size_t q = 0; q < plans.size(); ++q) {
       const MatmulPlan& m = plans[q];
       const bool res = forms[q] == kFormResidue;
       matmul_packed(m, cv, trunc, forms[q], res ? rjobs : jobs, res ? rreqs : reqs);
-      if (!res) shapes.push_back({m.M, m.N, m.K});
+      shapes.push_back({m.M, m.N, m.K});
+      if (!res) owner.push_back(q);
     }
     if (!rreqs.empty()) {
       CHK(issue_residue(c, cv, rjobs, rreqs));
@@ -2107,8 +2109,8 @@ mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int tru
       const std::vector<ProbSched> ts = scheds_for(c, shapes);
       for (size_t q = 0; q < reqs.size(); ++q) {
         reqs[q].own_sched = true;
-        reqs[q].sched = ts[q / 2].s;
-        reqs[q].cls = ts[q / 2].cls;
+        reqs[q].sched = ts[owner[q / 2]].s;
+        reqs[q].cls = ts[owner[q / 2]].cls;
       }
       CHK(issue_limb(c, jobs, reqs, c->sched_default));
     }

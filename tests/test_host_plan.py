@@ -1,4 +1,6 @@
 """Which kernels a call launches, from the library's own host code without a GPU (tests/host_double.py)."""
+import ctypes
+
 import pytest
 
 from tests.host_double import Double, form
@@ -56,3 +58,36 @@ def test_short_k(d, M, N, K, beaver, ring, deal, party):
                                                ((64, 1, 4000, 128, 7, 1), "plain", "limb"), ((1, 1, 160, 32, 15, 1), "plain", "plain")])
 def test_short_k_convolutions(d, conv, online, dealt):
     assert form(d.conv(*conv)) == online and form(d.deal_conv(*conv)) == dealt
+
+
+# ---------------------------------------------------------------- tuned schedules
+def shapes_key(shapes):
+    """The hash that the tuned schedules' file keeps a shape list under (FNV-1a over 64-bit words)."""
+    h = 1469598103934665603
+    for v in [len(shapes)] + [v for s in shapes for v in s]:
+        for b in v.to_bytes(8, "little"):
+            h = (h ^ b) * 1099511628211 % 2**64
+    return h
+
+
+GROUP = [(300, 220, 500), (2040, 1040, 2512), (17, 200, 300), (1500, 2104, 3003), (40, 600, 64), (1825, 2281, 2304)]
+
+
+@pytest.mark.parametrize("packed", [False, True])
+def test_tuned_schedules_of_a_mixed_group(d, tmp_path, packed):
+    """A group some of whose products take the residue form runs the others in the schedules tuned for the group."""
+    order = sorted(GROUP, key=lambda s: -s[2])  # as the call issues them
+    path = tmp_path / "tuned"
+    path.write_text(f"{shapes_key(order):016x} 3 4 0 12 16 1 13 16 1\n")
+    log = d.grouped(GROUP, packed=packed)
+    assert form(log) == "residue+limb" and {f["variant"] for n, f in log if n == "limb"} == {14}
+    d.call("mpc_autotune_load", ctypes.c_char_p(str(path).encode()))
+    log = d.grouped(GROUP, packed=packed)
+    assert form(log) == "residue+limb"
+    got, sched = {}, None
+    for n, f in log:
+        if n == "limb":
+            sched = (f["variant"], f["group_m"], f["remap"])
+        elif n == "limb_problem":
+            got[(f["M"], f["N"])] = sched
+    assert got == {(17, 200): (12, 16, 1), (300, 220): (3, 4, 0), (40, 600): (3, 4, 0)}
