@@ -160,7 +160,8 @@ mpc_status mpc_ctx_destroy(mpc_ctx *ctx);
 mpc_status mpc_sync(mpc_ctx *ctx);
 mpc_status mpc_ctx_stats(const mpc_ctx *ctx, mpc_stats *out);
 /* Pre-sizes the library-owned workspace to at least `bytes` (optional; calls
- * grow it on demand, synchronising both streams when they do). */
+ * grow it on demand, synchronising both streams when they do).  Where the
+ * device does not have that much it keeps the size it had (MPC_E_NOMEM). */
 mpc_status mpc_reserve(mpc_ctx *ctx, size_t bytes);
 
 /* ---- sharing (section 5.1) --------------------------------------------- */
@@ -429,8 +430,9 @@ mpc_status mpc_limb_plan(int64_t M, int64_t N, int variant, int *cls, int64_t *r
  * the context that captured it (MPC_E_INVAL for another context);
  * mpc_graph_destroy frees it.  A graph refers to the context's workspace by
  * address, so while any graph of a context exists the workspace cannot move:
- * a call that would need a larger one returns MPC_E_NOMEM (reserve enough
- * before capturing).  A graph owns the descriptor buffers made while it was
+ * a call that would need a larger one returns MPC_E_NOMEM, or where the
+ * library chooses its form takes a slower one that fits (reserve enough before
+ * capturing).  A graph owns the descriptor buffers made while it was
  * captured and frees them in mpc_graph_destroy, which first waits for party
  * 0's stream.  Destroy a context's graphs before the context:
  * mpc_ctx_destroy returns MPC_E_INVAL and frees nothing while any exists. */

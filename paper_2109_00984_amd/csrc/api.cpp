@@ -95,6 +95,16 @@ void* scratch_address(int device) {
 
 }  // namespace
 
+namespace {
+// Device memory of a context that grows on demand.
+struct Buffer {
+  uint8_t* p = nullptr;
+  size_t cap = 0;
+  // the smallest size that the device did not have, and what was free then
+  size_t refused = SIZE_MAX, refused_free = 0;
+};
+}  // namespace
+
 struct mpc_ctx {
   int device = 0;
   int num_cu = 256;
@@ -103,8 +113,7 @@ struct mpc_ctx {
   hipEvent_t ev[2] = {nullptr, nullptr};
   hipStream_t side = nullptr;  // non-blocking stream for uploads made during capture
   uint64_t seed = 0;
-  uint8_t* ws = nullptr;
-  size_t ws_cap = 0;
+  Buffer ws;
   UploadSlot slots[kSlots];
   int next_slot = 0;
   int cur_slot = -1;
@@ -131,8 +140,7 @@ struct mpc_ctx {
   // vendor BLAS handle of the fp64 limb form (created on first use)
   rocblas_handle blas = nullptr;
   // partial sums of split-K plain GEMMs (grown on demand)
-  uint8_t* splitk = nullptr;
-  size_t splitk_cap = 0;
+  Buffer splitk;
   // instantiated graphs not yet destroyed: they hold workspace addresses, so
   // no buffer may move while any exists
   int live_graphs = 0;
@@ -185,24 +193,48 @@ mpc_status sync_all(mpc_ctx* c) {
   return MPC_OK;
 }
 
-// Makes the workspace at least `bytes`.  Growing frees the old buffer, so it
-// first waits for both streams; it is refused while a graph is being captured.
-mpc_status ensure_ws(mpc_ctx* c, size_t bytes) {
-  if (bytes <= c->ws_cap) return MPC_OK;
-  // a live graph (or one being captured) holds the current workspace address
+// Makes a buffer at least `bytes` large (`cap` of them where that much can be
+// had).  Growing frees the old block first, after both streams have finished
+// with it.  Where the device refuses the new one, a block of the old size takes
+// its place, so that the calls it served still have it.  optional: the caller
+// has a way with less memory; it is not asked for again what the device refused
+// until more memory is free than then (the wait, the free and the allocations
+// would otherwise come with every such call).
+mpc_status grow_buffer(mpc_ctx* c, Buffer* b, size_t bytes, size_t cap, bool optional) {
+  if (bytes <= b->cap) return MPC_OK;
+  // a live graph (or one being captured) holds the current address
   if (c->capturing || c->live_graphs > 0) return MPC_E_NOMEM;
-  CHK(sync_all(c));
-  if (c->ws) HIPCHK(hipFree(c->ws));
-  c->ws = nullptr;
-  c->ws_cap = 0;
-  size_t cap = align_up(bytes + bytes / 4, 1 << 20);
-  if (hipMalloc((void**)&c->ws, cap) != hipSuccess) {
-    c->ws = nullptr;
-    (void)hipGetLastError();
-    return MPC_E_NOMEM;
+  size_t free = 0, total = 0;
+  if (optional && bytes >= b->refused) {
+    HIPCHK(hipMemGetInfo(&free, &total));
+    if (free <= b->refused_free) return MPC_E_NOMEM;
   }
-  c->ws_cap = cap;
-  return MPC_OK;
+  CHK(sync_all(c));
+  const size_t old = b->cap;
+  if (b->p) HIPCHK(hipFree(b->p));
+  b->p = nullptr;
+  b->cap = 0;
+  size_t tried = 0;
+  for (size_t n : {cap, bytes, old}) {
+    if (n <= b->cap || n == tried) continue;
+    tried = n;
+    if (hipMalloc((void**)&b->p, n) == hipSuccess) {
+      b->cap = n;
+    } else {
+      b->p = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  if (b->cap >= b->refused) b->refused = SIZE_MAX;
+  if (bytes <= b->cap) return MPC_OK;
+  b->refused = std::min(b->refused, bytes);
+  HIPCHK(hipMemGetInfo(&b->refused_free, &total));
+  return MPC_E_NOMEM;
+}
+
+// Makes the workspace at least `bytes`.
+mpc_status ensure_ws(mpc_ctx* c, size_t bytes, bool optional = false) {
+  return grow_buffer(c, &c->ws, bytes, align_up(bytes + bytes / 4, 1 << 20), optional);
 }
 
 // Bump allocator over the workspace for one call.
@@ -586,20 +618,7 @@ constexpr i64 kPlainMinSlice = 32;
 // Makes the split-K partial buffer at least `bytes` large; false when it
 // would have to move while a graph is being captured or still refers to it
 // (the caller then runs unsplit).
-bool ensure_splitk(mpc_ctx* c, size_t bytes) {
-  if (bytes <= c->splitk_cap) return true;
-  if (c->capturing || c->live_graphs > 0) return false;
-  if (sync_all(c) != MPC_OK) return false;
-  if (c->splitk) (void)hipFree(c->splitk);
-  c->splitk = nullptr;
-  c->splitk_cap = 0;
-  if (hipMalloc(&c->splitk, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  c->splitk_cap = bytes;
-  return true;
-}
+bool ensure_splitk(mpc_ctx* c, size_t bytes) { return grow_buffer(c, &c->splitk, bytes, bytes, true) == MPC_OK; }
 
 mpc_status plan_splitk(mpc_ctx* c, std::vector<PlainProblem>& probs) {
   i64 tiles = 0;
@@ -626,7 +645,7 @@ mpc_status plan_splitk(mpc_ctx* c, std::vector<PlainProblem>& probs) {
       const i64 per = (Kt + ks[q] - 1) / ks[q];
       p.kslice = (per + kPlainBK - 1) / kPlainBK * kPlainBK;
       p.ksplit = (int)((Kt + p.kslice - 1) / p.kslice);
-      p.partial = (u64*)(c->splitk + off);
+      p.partial = (u64*)(c->splitk.p + off);
       off += align_up((size_t)(ks[q] * p.M * p.N) * 8);
     } else {
       p.ksplit = 1;
@@ -1236,7 +1255,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
     };
     if (nslices[q] > 1) {
       const int ks = nslices[q];
-      u64* part = (u64*)(c->splitk + part_off);
+      u64* part = (u64*)(c->splitk.p + part_off);
       part_off += align_up((size_t)(ks * r.M * r.N) * 8);
       CHK(piece(0, 0, kbt, make_ep(nullptr, +1, 0, part, rowmajor_view(r.N)), ks));
       reduces.push_back(ReduceJob{part, ks, r.M, r.N, r.ep});
@@ -1457,11 +1476,12 @@ mpc_status issue_packed(mpc_ctx* c, Form form, Carve& cv, const std::vector<Pack
 template <class F>
 mpc_status ensure_form_ws(mpc_ctx* c, Form* form, bool automatic, F need) {
   if (*form == kFormResidue) {
-    if (ensure_ws(c, need(kFormResidue)) == MPC_OK) return MPC_OK;
+    if (ensure_ws(c, need(kFormResidue), true) == MPC_OK) return MPC_OK;
     *form = MPC_FORM_LIMB8;
   }
-  const mpc_status st = ensure_ws(c, need(*form));
-  if (st != MPC_E_NOMEM || !automatic || *form != MPC_FORM_LIMB8) return st;
+  const bool optional = automatic && *form == MPC_FORM_LIMB8;
+  const mpc_status st = ensure_ws(c, need(*form), optional);
+  if (st != MPC_E_NOMEM || !optional) return st;
   *form = MPC_FORM_PLAIN;
   return ensure_ws(c, need(*form));
 }
@@ -1608,8 +1628,8 @@ mpc_status mpc_ctx_destroy(mpc_ctx* c) {
   }
   for (hipEvent_t e : c->event_pool) (void)hipEventDestroy(e);
   if (c->blas) (void)rocblas_destroy_handle(c->blas);
-  if (c->splitk) (void)hipFree(c->splitk);
-  if (c->ws) (void)hipFree(c->ws);
+  if (c->splitk.p) (void)hipFree(c->splitk.p);
+  if (c->ws.p) (void)hipFree(c->ws.p);
   for (int p = 0; p < 2; ++p) {
     if (c->ev[p]) (void)hipEventDestroy(c->ev[p]);
     if (c->own[p] && c->s[p]) (void)hipStreamDestroy(c->s[p]);
@@ -1796,7 +1816,7 @@ mpc_status mpc_dealer_triples(mpc_ctx* c, mpc_triple_kind kind, uint64_t dseed, 
   CHK(hip_status(launch_prg_fill(st, key[kSlotC0], t->c0, nc)));
   c->stats.launches += 1;
   if (nc) {
-    Carve cv(c->ws);
+    Carve cv(c->ws.p);
     if (packs(form)) {
       const auto j = ops(form);
       std::vector<PackJob> jobs{place_job(j[0], cv, form), place_job(j[1], cv, form)};
@@ -1976,7 +1996,7 @@ mpc_status run_matmuls_fp64(mpc_ctx* c, const std::vector<MatmulPlan>& plans, in
   }
   CHK(fp64_ready(c));
   CHK(ensure_ws(c, need + fp));
-  Carve cv(c->ws);
+  Carve cv(c->ws.p);
   std::vector<OpenJob> opens;
   struct Opened { u64 *eps, *g, *del; };
   std::vector<Opened> op;
@@ -2072,8 +2092,9 @@ std::vector<Form> packing_forms(const std::vector<MatmulPlan>& plans) {
 
 // Every plan has a form of its own under the packing forms (`forms`: one per
 // plan, LIMB8 or residue); otherwise `form` is all plans' form.
+// automatic: the plain form takes their place where there is no memory for them.
 mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int trunc, Form form,
-                       std::vector<Form> forms = {}) {
+                       std::vector<Form> forms = {}, bool automatic = false) {
   if (packs(form) && forms.empty()) forms.assign(plans.size(), form);
   if (form == MPC_FORM_FP64LIMB) {
     CHK(run_matmuls_fp64(c, plans, trunc));
@@ -2081,13 +2102,15 @@ mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int tru
     // both forms' operands side by side in the workspace; where that much
     // cannot be had, every plan takes the limb form
     Form any = std::count(forms.begin(), forms.end(), kFormResidue) ? kFormResidue : MPC_FORM_LIMB8;
-    CHK(ensure_form_ws(c, &any, false, [&](Form f) {
+    CHK(ensure_form_ws(c, &any, automatic, [&](Form f) {
+      if (!packs(f)) return (size_t)0;  // its own branch asks
       size_t need = kAlign;
       for (size_t q = 0; q < plans.size(); ++q) need += matmul_ws(plans[q], f == kFormResidue ? forms[q] : f);
       return need;
     }));
+    if (!packs(any)) return run_matmuls(c, plans, trunc, any);
     if (any == MPC_FORM_LIMB8) forms.assign(plans.size(), any);
-    Carve cv(c->ws);
+    Carve cv(c->ws.p);
     std::vector<PackJob> jobs, rjobs;
     std::vector<LimbReq> reqs, rreqs;
     std::vector<std::array<i64, 3>> shapes;  // of all products: the list that a tuned schedule is kept under
@@ -2125,7 +2148,7 @@ mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int tru
     size_t need = kAlign;
     for (const MatmulPlan& m : plans) need += matmul_ws(m, form);
     CHK(ensure_ws(c, need));
-    Carve cv(c->ws);
+    Carve cv(c->ws.p);
     std::vector<OpenJob> opens;
     std::vector<PlainProblem> probs;
     for (const MatmulPlan& m : plans) matmul_plain(m, cv, trunc, opens, probs);
@@ -2156,10 +2179,7 @@ mpc_status mpc_beaver_matmul(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const 
   CHK(check_limb_k(form, K));
   if (M == 0 || N == 0) return MPC_OK;
   CHK(set_device(c));
-  mpc_status st = run_matmuls(c, {m}, trunc_bits, form);
-  // no memory for the packed operands, and nothing issued yet
-  if (st == MPC_E_NOMEM && automatic && packs(form)) st = run_matmuls(c, {m}, trunc_bits, MPC_FORM_PLAIN);
-  CHK(st);
+  CHK(run_matmuls(c, {m}, trunc_bits, form, {}, automatic));
   return end_call(c);
 }
 
@@ -2216,7 +2236,7 @@ mpc_status mpc_dealer_triples_packed(mpc_ctx* c, uint64_t dseed, uint64_t tag, i
   }));
   CHK(hip_status(launch_prg_fill(c->s[0], key[kSlotC0], t->c0, nc)));
   c->stats.launches++;
-  Carve cv(c->ws);
+  Carve cv(c->ws.p);
   uint8_t* pk = (uint8_t*)packed;
   const Epilogue ep = make_ep(t->c0, -1, 0, t->c1, rowmajor_view(N));
   std::vector<PackJob> jobs;
@@ -2381,7 +2401,7 @@ mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const ui
       return kAlign + job_bytes(j[0], f) + job_bytes(j[1], f) + (f == kFormResidue ? 2 * res_out_bytes(M, N, j[0].K, j[0].K) : 0);
     }));
   if (packs(form)) {
-    Carve cv(c->ws);
+    Carve cv(c->ws.p);
     const auto j = ops(form);
     const PackJob W = place_job(j[0], cv, form), X = place_job(j[1], cv, form);
     std::vector<LimbReq> reqs;
@@ -2398,7 +2418,7 @@ mpc_status mpc_beaver_conv1d(mpc_ctx* c, const mpc_conv1d_shape* shape, const ui
     if (fp && 2 * K >= kFp64MaxK) return MPC_E_UNSUPPORTED;
     if (fp) CHK(fp64_ready(c));
     CHK(ensure_ws(c, opened + (fp ? fp64_ws(M, N, 2 * K) : 0)));
-    Carve cv(c->ws);
+    Carve cv(c->ws.p);
     u64* eps = cv.take<u64>(nx);
     u64* g = cv.take<u64>(nx);
     u64* del = cv.take<u64>(nw);
@@ -2459,13 +2479,13 @@ mpc_status mpc_ring_gemm(mpc_ctx* c, int64_t M, int64_t N, int64_t K, const uint
       return kAlign + job_bytes(ja, f) + job_bytes(jb, f) + (f == kFormResidue ? res_out_bytes(M, N, K, 0) : 0);
     }));
   if (packs(form)) {
-    Carve cv(c->ws);
+    Carve cv(c->ws.p);
     const PackJob PA = place_job(ja, cv, form), PB = place_job(jb, cv, form);
     CHK(issue_packed(c, form, cv, {PA, PB}, {limb_req(M, N, K, 0, PA.dst[0], nullptr, PB.dst[0], nullptr, ep)}));
   } else if (form == MPC_FORM_FP64LIMB) {
     if (K >= kFp64MaxK) return MPC_E_UNSUPPORTED;
     CHK(ensure_ws(c, kAlign + fp64_ws(M, N, K)));
-    Carve cv(c->ws);
+    Carve cv(c->ws.p);
     CHK(issue_fp64(c, cv, M, N, K, 0, A, K, nullptr, 0, B, N, nullptr, 0, ep));
   } else {
     CHK(issue_plain(c, {plain_problem(M, N, K, 0, A, nullptr, K, nullptr, 0, B, nullptr, N, nullptr, 0, ep)}));
@@ -2615,7 +2635,7 @@ mpc_status mpc_autotune_matmul(mpc_ctx* c, size_t count, const int64_t* dims, mp
   for (const auto& s : shapes)
     need += 3 * align_up(packed_bytes(s[0], s[2])) + 3 * align_up(packed_bytes(s[1], s[2]));
   CHK(ensure_ws(c, need));
-  Carve cv(c->ws);
+  Carve cv(c->ws.p);
   std::vector<LimbReq> reqs[kBuckets];
   for (const auto& s : shapes) {
     const i64 M = s[0], N = s[1], K = s[2];
@@ -2631,7 +2651,7 @@ mpc_status mpc_autotune_matmul(mpc_ctx* c, size_t count, const int64_t* dims, mp
     for (LimbReq& r : reqs[b]) r.cls = b;
   // random limbs: the matrix cores' power draw, and so their clock, depends
   // on the data
-  CHK(hip_status(launch_prg_fill(c->s[0], stream_key(c->seed, 0x7475, 0), (u64*)c->ws, cv.off / 8)));
+  CHK(hip_status(launch_prg_fill(c->s[0], stream_key(c->seed, 0x7475, 0), (u64*)c->ws.p, cv.off / 8)));
   // outputs: one scratch buffer per party, the largest problem's size
   i64 maxmn = 0;
   for (const auto& s : shapes) maxmn = std::max(maxmn, s[0] * s[1]);
@@ -3134,7 +3154,7 @@ mpc_status mpc_mp_dealer_triples(mpc_ctx* c, int P, mpc_triple_kind kind, uint64
     return kAlign + align_up(na * 8) + align_up(nb * 8) + align_up(nc * 8) + (packs(f) ? job_bytes(ja, f) + job_bytes(jb, f) : 0) +
            (f == kFormResidue ? res_out_bytes(M, N, K, 0) : 0);
   }));
-  Carve cv(c->ws);
+  Carve cv(c->ws.p);
   u64* as = cv.take<u64>(na);
   u64* bs = cv.take<u64>(nb);
   u64* S = cv.take<u64>(nc);
@@ -3228,7 +3248,7 @@ mpc_status mpc_mp_beaver_matmul(mpc_ctx* c, int P, int64_t M, int64_t N, int64_t
                               : align_up(na * 8) + align_up(nb * 8)) +
            (f == kFormResidue ? (size_t)P * res_out_bytes(M, N, K, K) : 0);
   }));
-  Carve cv(c->ws);
+  Carve cv(c->ws.p);
   if (packs(form)) {
     PartyPackTables pt{};
     const JobSpec spec[2] = {left_job(M, K, K), right_job(K, N, N)};

@@ -3,6 +3,7 @@ import ctypes
 
 import pytest
 
+import paper_2109_00984_amd as m
 from tests.host_double import Double, form
 
 
@@ -91,3 +92,70 @@ def test_tuned_schedules_of_a_mixed_group(d, tmp_path, packed):
         elif n == "limb_problem":
             got[(f["M"], f["N"])] = sched
     assert got == {(17, 200): (12, 16, 1), (300, 220): (3, 4, 0), (40, 600): (3, 4, 0)}
+
+
+# ---------------------------------------------------------------- memory that the device does not have
+MB = 1 << 20
+
+
+def test_refused_residue_workspace_is_not_asked_for_again():
+    """2048^3 takes 604 MB of workspace in the residue form and 201 in the limb form."""
+    d = Double(limit=500 * MB)
+    assert form(d.matmul(2048, 2048, 2048)) == "limb" and d.counts()["refused"] > 0
+    for _ in range(2):
+        assert form(d.matmul(2048, 2048, 2048)) == "limb" and form(d.prepacked(2048, 2048, 2048)) == "limb"
+        c = d.counts()
+        assert c["mallocs"] == c["frees"] == c["syncs"] == 0
+    d.lib.double_limit(ctypes.c_size_t(2000 * MB))  # memory is free again
+    assert form(d.matmul(2048, 2048, 2048)) == "residue"
+    d.close()
+
+
+def test_workspace_without_the_slack():
+    """The workspace grows by a quarter more than asked where that can be had."""
+    d = Double(limit=700 * MB)
+    assert form(d.matmul(2048, 2048, 2048)) == "residue"
+    d.close()
+
+
+def test_refused_growth_keeps_the_workspace():
+    d = Double()
+    d.matmul(1024, 1024, 1024, "limb8")
+    used = d.counts()["used"]
+    with pytest.raises(m.MPCError):
+        d.call("mpc_reserve", ctypes.c_size_t(1 << 46))
+    assert d.counts()["used"] == used
+    d.call("mpc_graph_begin")
+    assert form(d.matmul(1024, 1024, 1024, "limb8")) == "limb"  # no room to grow under a capture
+    g = ctypes.c_void_p()
+    d.call("mpc_graph_end", ctypes.byref(g))
+    d._ok(d.lib.mpc_graph_destroy(g))
+    # a call that has no other way asks every time
+    for _ in range(2):
+        with pytest.raises(m.MPCError):
+            d.call("mpc_reserve", ctypes.c_size_t(1 << 46))
+        assert d.counts()["refused"] > 0
+    d.close()
+
+
+def test_refused_slices_are_not_asked_for_again():
+    d = Double()
+    d.call("mpc_reserve", ctypes.c_size_t(400 * MB))
+    d.lib.double_limit(ctypes.c_size_t(d.counts()["used"] + 2 * MB))
+    for first in (True, False):
+        log = d.matmul(500, 1100, 1000, "limb8")
+        assert form(log) == "limb" and "reduce" not in [n for n, _ in log]
+        assert (d.counts()["mallocs"] > 0) == first
+    d.lib.double_limit(ctypes.c_size_t(2000 * MB))
+    assert "reduce" in [n for n, _ in d.matmul(500, 1100, 1000, "limb8")]
+    d.close()
+
+
+def test_refused_limb_workspace_falls_back_to_plain():
+    d = Double(limit=5 * MB)
+    for first in (True, False, False):
+        assert form(d.matmul(300, 300, 300)) == "plain"
+        assert first or d.counts()["refused"] == d.counts()["syncs"] == 0
+    with pytest.raises(m.MPCError):
+        d.matmul(300, 300, 300, "limb8")
+    d.close()
