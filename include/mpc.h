@@ -256,7 +256,8 @@ mpc_status mpc_ring_gemm(mpc_ctx *ctx, int64_t M, int64_t N, int64_t K, const ui
  * sizes; the limb form also performs 36 int8 multiply-accumulates per ring
  * one, the fp64 limb form 6 or 10 float64 ones), and clears the record.  The
  * residue form that AUTO may take (18 int8 multiply-accumulates per ring one)
- * is recorded as the limb form.  In
+ * is recorded as the limb form, and a small Beaver matmul's one launch, which
+ * opens too, as one of the plain form.  In
  * the fp64 limb form the bracket covers its vendor-BLAS GEMM calls (one per
  * limb diagonal) as one launch.  Any output pointer may be NULL. */
 typedef struct {

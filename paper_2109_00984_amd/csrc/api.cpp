@@ -2090,6 +2090,20 @@ std::vector<Form> packing_forms(const std::vector<MatmulPlan>& plans) {
   return f;
 }
 
+// A small product: open and finish in one launch, no workspace.  It counts (and
+// is timed, unless the caller cannot allocate) as the plain form's finishes.
+mpc_status issue_small(mpc_ctx* c, const MatmulPlan& m, int trunc, bool no_alloc = false) {
+  const SmallMatmul s{m.M, m.N, m.K, m.x0, m.x1, m.y0, m.y1, m.t.a0, m.t.a1, m.t.b0, m.t.b1, m.t.c0, m.t.c1, m.z0, m.z1, trunc};
+  LaunchTimer tm(c, MPC_FORM_PLAIN, 4.0 * (double)m.M * (double)m.N * (double)m.K);
+  if (no_alloc) tm.on = false;
+  CHK(tm.start());
+  CHK(hip_status(launch_beaver_matmul_small(c->s[0], s)));
+  CHK(tm.stop());
+  c->stats.launches++;
+  c->stats.gemm_problems += 2;
+  return MPC_OK;
+}
+
 // Every plan has a form of its own under the packing forms (`forms`: one per
 // plan, LIMB8 or residue); otherwise `form` is all plans' form.
 // automatic: the plain form takes their place where there is no memory for them.
@@ -2138,12 +2152,7 @@ mpc_status run_matmuls(mpc_ctx* c, const std::vector<MatmulPlan>& plans, int tru
       CHK(issue_limb(c, jobs, reqs, c->sched_default));
     }
   } else if (plans.size() == 1 && small_matmul(plans[0].M, plans[0].N, plans[0].K)) {
-    // a small product: open and finish in one launch, no workspace
-    const MatmulPlan& m = plans[0];
-    const SmallMatmul s{m.M, m.N, m.K, m.x0, m.x1, m.y0, m.y1, m.t.a0, m.t.a1, m.t.b0, m.t.b1,
-                        m.t.c0, m.t.c1, m.z0, m.z1, trunc};
-    CHK(hip_status(launch_beaver_matmul_small(c->s[0], s)));
-    c->stats.launches++;
+    CHK(issue_small(c, plans[0], trunc));
   } else {
     size_t need = kAlign;
     for (const MatmulPlan& m : plans) need += matmul_ws(m, form);
@@ -2335,10 +2344,7 @@ mpc_status mpc_beaver_matmul_noalloc(mpc_ctx* c, int64_t M, int64_t N, int64_t K
   if (!c->scratch) return MPC_E_HIP;
   CHK(set_device(c));
   if (form == MPC_FORM_AUTO && small_matmul_auto(M, N, K)) {
-    // a small product: open and finish in one launch, no workspace at all
-    const SmallMatmul s{M, N, K, x0, x1, y0, y1, t->a0, t->a1, t->b0, t->b1, t->c0, t->c1, z0, z1, trunc_bits};
-    CHK(hip_status(launch_beaver_matmul_small(c->s[0], s)));
-    c->stats.launches++;
+    CHK(issue_small(c, m, trunc_bits, true));
   } else {
     // the limb form over `scratch`: descriptor tables inline, no split-K
     Carve cv(c->scratch);

@@ -159,3 +159,24 @@ def test_refused_limb_workspace_falls_back_to_plain():
     with pytest.raises(m.MPCError):
         d.matmul(300, 300, 300, "limb8")
     d.close()
+
+
+# ---------------------------------------------------------------- what a context counts
+def profile(d):
+    t = [m.GemmTiming() for _ in range(3)]
+    d.call("mpc_profile_read", *[ctypes.byref(g) for g in t])
+    return {n: (int(g.launches), float(g.ring_macs)) for n, g in zip(("limb8", "plain", "fp64limb"), t)}
+
+
+@pytest.mark.parametrize("M,N,K,f", [(128, 128, 128, "plain"), (64, 32, 128, "auto"), (300, 200, 100, "plain"), (500, 500, 40, "plain"), (300, 200, 100, "limb8")])
+def test_every_finish_is_counted_and_timed(d, M, N, K, f):
+    """Two GEMM problems over the summed k, recorded under the form that ran (the one launch as the plain form)."""
+    d.call("mpc_profile_enable", 1)
+    before = d.stats()["gemm_problems"]
+    log = d.matmul(M, N, K, f)
+    assert d.stats()["gemm_problems"] - before == 2
+    ran = "limb8" if form(log) == "limb" else "plain"
+    assert profile(d) == {n: (1, 2.0 * M * N * 2 * K) if n == ran else (0, 0.0) for n in ("limb8", "plain", "fp64limb")}
+    # a call that may not allocate makes no events
+    d.matmul(64, 32, 128, name="mpc_beaver_matmul_noalloc")
+    assert d.stats()["gemm_problems"] - before == 4 and profile(d)["plain"][0] == 0
