@@ -1027,6 +1027,7 @@ std::vector<Region> limb_regions(const LimbReq& r, const TileSched& ts) {
 // and 400 x 1000 x 500 none.  Beyond three workgroups a unit nothing gains (600
 // x 3000 x 1500, 940 tiles: 334 / 359).
 constexpr i64 kSliceMaxWorkgroups = 3;  // a unit
+constexpr i64 kSliceLongSteps = 40, kSliceManyTiles = 40;  // issue_limb's products of different k
 i64 limb_slices(i64 tiles, i64 steps, i64 min_slices, i64 outs, i64 cus) {
   i64 pick = 1;
   double best = -1;
@@ -1128,11 +1129,12 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
   const size_t nreq = reqs.size();
 
   // K pieces per request.  The int32 bound needs kbt / kLimbMaxKBlocks chunks,
-  // run as consecutive launches that add into the output.  When the whole
-  // launch fills at most half of the compute units, k is instead cut into slices
-  // (at least that many) that run side by side in one launch, each writing
-  // its raw sum to a partial buffer; a reduction adds them and applies the
-  // epilogue (split-K).
+  // run as consecutive launches that add into the output.  When the launch has
+  // fewer tiles than compute units (three a unit for the default tiles over one
+  // k length, if limb_slices finds a gain), k is instead cut into slices (at
+  // least that many) that run side by side in one launch, each writing its raw
+  // sum to a partial buffer; a reduction adds them and applies the epilogue
+  // (split-K).
   std::vector<int> nchunks(nreq), nslices(nreq, 1);
   auto sched_of = [&](size_t q) { return reqs[q].own_sched ? reqs[q].sched : sched; };
   // Output regions of each request, each run as a problem of its own.  Under
@@ -1163,15 +1165,25 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
   }
   size_t part_bytes = 0;
   // the default tiles, two workgroups a unit, over one k length
-  bool alike = true;
+  bool alike = true, uneven = false;
+  i64 longest = 0;
   for (size_t q = 0; q < nreq; ++q) {
     const int v = sched_of(q).variant;
-    alike = alike && (v == kLimbLds64x64 || v == kLimbClasses) && reqs[q].K0 == reqs[0].K0 && reqs[q].K1 == reqs[0].K1;
+    uneven = uneven || reqs[q].K0 != reqs[0].K0 || reqs[q].K1 != reqs[0].K1;
+    alike = alike && (v == kLimbLds64x64 || v == kLimbClasses);
+    longest = std::max(longest, (limb_kblocks(reqs[q].K0) + limb_kblocks(reqs[q].K1)) / 2);
   }
+  alike = alike && !uneven;
   if (!no_alloc && tiles_all > 0 && tiles_all < (alike ? kSliceMaxWorkgroups : 1) * c->num_cu) {
     // As many slices as give every unit one workgroup, or what the model of
-    // the default tiles' rounds says.
+    // the default tiles' rounds says.  Two a unit where the products' k differ,
+    // one of them is long and the tiles are many: so few slices would leave the
+    // longest one's to the end (12 products of up to 274 x 96 x 3957, 114 tiles,
+    // 224 us with one a unit, 188 with two; of 16 x 1129 x 5602, 244 tiles, 632 /
+    // 556; but of 1011 x 252 x 435, 180 tiles of 12 k steps, 35 / 45, and 6 of 1 x 4
+    // x 6724, 12 tiles, 40 / 44).
     i64 want = c->num_cu / tiles_all;
+    if (uneven && longest >= kSliceLongSteps && tiles_all >= kSliceManyTiles) want = (2 * c->num_cu + tiles_all - 1) / tiles_all;
     if (alike) {
       i64 outs = 0;
       for (const LimbReq& r : reqs) outs += r.M * r.N;

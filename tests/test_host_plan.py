@@ -180,3 +180,19 @@ def test_every_finish_is_counted_and_timed(d, M, N, K, f):
     # a call that may not allocate makes no events
     d.matmul(64, 32, 128, name="mpc_beaver_matmul_noalloc")
     assert d.stats()["gemm_problems"] - before == 4 and profile(d)["plain"][0] == 0
+
+
+# ---------------------------------------------------------------- k slices
+def slices(log):
+    return [f["slices"] for n, f in log if n == "limb_problem"]
+
+
+@pytest.mark.parametrize("shapes,per_unit", [([(250, 90, 4000 - 200 * i) for i in range(8)], 2),      # 128 tiles, up to 126 k steps
+                                             ([(250, 90, 1200 - 50 * i) for i in range(8)], 1),       # up to 38
+                                             ([(60, 64, 4000 - 200 * i) for i in range(8)], 1)])      # 16 tiles
+def test_slices_of_uneven_groups(d, shapes, per_unit):
+    """Long products of different k in a launch of many tiles: slices for two workgroups a unit, otherwise one."""
+    log = d.grouped(shapes, "limb8")
+    groups = 2 * sum(-(-M // 64) * -(-N // 64) for M, N, _ in shapes)
+    want = -(-512 // groups) if per_unit == 2 else 256 // groups
+    assert max(slices(log)) == min(want, max(2 * -(-K // 64) for _, _, K in shapes) // 4), log
