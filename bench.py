@@ -203,7 +203,7 @@ def main():
         "config": {"workload": "secure ring GEMM 4096x4096x4096 over Z/2^64: share both "
                                "operands, dealer matrix triple, Beaver matmul with 2^16 "
                                "truncation, reveal",
-                   "M": M, "N": N, "K": K, "form": args.form, "frac_bits": FRAC,
+                   "M": M, "N": N, "K": K, "form": "residue" if residue else args.form, "frac_bits": FRAC,
                    "triples": "offline-packed" if packed_triples else "plain",
                    "parties": 2, "parallelism": "single GPU, two party streams"},
         "roofline": roofline,
@@ -225,30 +225,32 @@ def main():
 
 def finish_in_residue_form(ctx, online):
     """Whether the library runs this Beaver matmul in the residue form, which
-    it records as the limb form: told by its launches (open + pack, GEMM,
-    combine), where the limb form without split-K has two."""
+    it records as the limb form: told by its launches (open + pack, a GEMM per
+    tile shape, combine), where the limb form, whose tiles here are far too many
+    for k slices, has two."""
     ctx.sync()
     before = ctx.stats()["launches"]
     online()
-    return ctx.stats()["launches"] - before == 3
+    return ctx.stats()["launches"] - before >= 3
 
 
 def traffic_file(kernel):
     return os.path.join(ROOT, "profiles", f"{kernel}_secure_gemm_4096_traffic.md")
 
 
-GEMM_SOURCES = {"k_res_gemm": ("gemm_residue.hip",)}  # else the limb GEMM's
+# what a GEMM's HBM traffic depends on: its source, and the tile order and loads that both packed forms share
+GEMM_SOURCES = {"k_res_gemm": ("gemm_residue.hip", "packed.h")}  # else the limb GEMM's
 API_SOURCE = os.path.join(ROOT, "paper_2109_00984_amd", "csrc", "api.cpp")
 
 
 def kernel_fingerprint(kernel):
-    """sha256 over the GEMM's source (comments and blank space dropped) and
+    """sha256 over the GEMM's sources (comments and blank space dropped) and
     the library's default tile schedule: what the GEMM's HBM traffic depends
     on."""
     import hashlib
     import re
     src = "".join(open(os.path.join(os.path.dirname(API_SOURCE), f)).read()
-                  for f in GEMM_SOURCES.get(kernel, ("gemm_limb.hip",)))
+                  for f in GEMM_SOURCES.get(kernel, ("gemm_limb.hip", "packed.h")))
     src = re.sub(r"//[^\n]*", "", src)
     src = "\n".join(" ".join(ln.split()) for ln in src.splitlines() if ln.strip())
     h = hashlib.sha256(src.encode())
