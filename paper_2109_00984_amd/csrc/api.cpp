@@ -816,10 +816,10 @@ mpc_status issue_fp64(mpc_ctx* c, Carve& cv, i64 M, i64 N, i64 K0, i64 K1, const
 }
 
 // ------------------------------------------------------------------ limb form
-// A pack job before its outputs are placed in the workspace.
 // Plane of a channels-last activation (ResConv), in whole blocks.
 i64 res_chan_plane(i64 batch, i64 cin, i64 len) { return align_up((size_t)(batch * ((cin + 63) / 64) * len) * 64, kResBlockBytes); }
 
+// A pack job before its outputs are placed in the workspace.
 struct JobSpec {
   int kind = kPackRow;
   int mode = kModeCopy;

@@ -651,7 +651,8 @@ __global__ void __launch_bounds__(256, G::kPerCU) k_res_gemm(ResGemmTables) {
       __builtin_amdgcn_sched_barrier(0);
       // step s: MFMAs on its fragments; reads of step s + 1's (past the last
       // step they return what an empty copy left: unused); copies of step
-      // s + kDepth into the buffer that step s's fragments were read from
+      // s + kAhead, into the buffer that step s's fragments were read from
+      // (kDepth == kAhead) or step s - 1's
       auto step = [&]<bool FIRST>(int s, const RFrags<G>& cur, RFrags<G>& nxt) {
         lds_u8* rbuf = lds + ((s + 1) % G::kDepth) * G::kStepBytes;
         lds_u8* wbuf = lds + ((s + G::kAhead) % G::kDepth) * G::kStepBytes;

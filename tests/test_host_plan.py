@@ -1,10 +1,14 @@
 """Which kernels a call launches, from the library's own host code without a GPU (tests/host_double.py)."""
 import ctypes
+import math
+import random
 
 import pytest
 
 import paper_2109_00984_amd as m
-from tests.host_double import Double, form
+import tests.test_gpu_residue as residue
+import tests.test_gpu_residue_tiles as residue_tiles
+from tests.host_double import Double, form, tiles
 
 
 @pytest.fixture()
@@ -196,3 +200,123 @@ def test_slices_of_uneven_groups(d, shapes, per_unit):
     groups = 2 * sum(-(-M // 64) * -(-N // 64) for M, N, _ in shapes)
     want = -(-512 // groups) if per_unit == 2 else 256 // groups
     assert max(slices(log)) == min(want, max(2 * -(-K // 64) for _, _, K in shapes) // 4), log
+
+
+# ---------------------------------------------------------------- the residue form's plan
+def res_problems(log):
+    return [f for n, f in log if n == "res_problem"]
+
+
+def check_plan(log, products):
+    """Every product's every chunk of k and modulus is computed once, by tiles that cover the output and stay inside its
+    padded residues; the chunks cut the k range without a gap into at most 173 blocks of 64 each; the launches' tile
+    lists are the problems'."""
+    outs = [f for n, f in log if n == "combine_out"]
+    assert len(outs) == products
+    seen = {}
+    for f in res_problems(log):
+        assert f["end"] - f["start"] == f["nm"] * f["ntm"] * f["ntn"] and f["nm"] > 0
+        seen.setdefault(f["R"], []).append(f)
+    for n, f in log:
+        if n == "res":
+            assert f["tiles"] == sum(p["end"] - p["start"] for p in res_problems(log) if (p["bm"], p["bn"]) == (f["bm"], f["bn"]))
+            assert 1 <= f["grid"] <= f["tiles"]
+    pad = lambda v: -(-v // 256) * 256  # noqa: E731
+    for o in outs:
+        at = 0
+        for ch in range(o["nch"]):
+            probs = seen.pop(o["R"] + ch * o["pc"])
+            assert sorted(i for f in probs for i in range(f["m0"], f["m0"] + f["nm"])) == list(range(18))
+            assert len({(f["kb_begin"], f["kb_end"]) for f in probs}) == 1
+            f = probs[0]
+            assert f["kb_begin"] == at and 0 < f["kb_end"] - at <= 173
+            at = f["kb_end"]
+            for f in probs:
+                assert o["M"] <= f["ntm"] * f["bm"] <= pad(o["M"]) and o["N"] <= f["ntn"] * f["bn"] <= pad(o["N"])
+                assert f["pr"] == pad(o["M"]) * pad(o["N"]) and f["n64"] == pad(o["N"]) // 64
+                assert f["pa"] == pad(o["M"]) * 64 * f["kbs"]
+        assert at in (f["kbs"], 2 * f["kbs"])
+    assert not seen
+
+
+def random_shapes(seed, n, lo, hi):
+    rng = random.Random(seed)
+    return [tuple(int(round(math.exp(rng.uniform(math.log(a), math.log(b))))) for a, b in zip(lo, hi)) for _ in range(n)]
+
+
+def test_residue_plan_covers_every_product(d):
+    found = set()
+    for M, N, K in random_shapes(7, 400, (200, 200, 1000), (5000, 5000, 30000)):
+        for log, products in ((d.matmul(M, N, K), 2), (d.ring(M, N, K), 1), (d.deal(M, N, K), 1), (d.party(3, M, N, K), 3)):
+            if form(log) == "residue":
+                check_plan(log, products)
+                found.update(tiles(log))
+    assert found == {(256, 256), (256, 128), (128, 256), (128, 128)}
+
+
+def test_residue_plan_of_groups(d):
+    taken = 0
+    for seed in range(12):
+        shapes = random_shapes(seed, 5, (300, 300, 1000), (3000, 3000, 9000))
+        log = d.grouped(shapes)
+        n = len([1 for name, _ in log if name == "combine_out"])
+        if n:
+            check_plan(log, n)
+            taken += n
+    assert taken > 20
+
+
+def test_residue_plan_of_convolutions(d):
+    direct = 0
+    for B, cin, L, cout, k, s in random_shapes(9, 300, (1, 40, 200, 128, 1, 1), (8, 600, 2000, 2500, 48, 3)):
+        log = d.conv(B, cin, L, cout, k, s)
+        if form(log) == "residue":
+            check_plan(log, 2)
+            direct += res_problems(log)[0]["ksz"] > 0
+    assert direct > 30
+
+
+# ---------------------------------------------------------------- the forms that the GPU tests of the residue form cover
+def cases(test):
+    """The argument lists of a parametrised test, by its parameters' names."""
+    return {mark.args[0]: mark.args[1] for mark in test.pytestmark if mark.name == "parametrize"}
+
+
+def test_forms_of_the_gpu_tests(d):
+    for s in cases(residue.test_ring_gemm_matches_plain)["M,N,K"] + [(2500, 2305, 4161)]:
+        assert form(d.ring(*s)) == "residue", s
+    for *s, _ in cases(residue.test_beaver_matmul_matches_plain)["M,N,K,trunc"]:
+        assert {form(d.matmul(*s)), form(d.prepacked(*s)), form(d.grouped([s]))} == {"residue"}, s
+    for s in cases(residue.test_dealt_packed_operands)["M,N,K"]:
+        assert form(d.deal_packed(*s)) == "residue", s
+    for P in cases(residue.test_multiparty_matches_plain)["P"]:
+        assert form(d.party(P, 2060, 2100, 2400)) == "residue"
+    assert form(d.grouped(GROUP)) == "residue+limb"
+    convs = cases(residue.test_conv_matches_plain)["B,cin,L,cout,k,s"]
+    # (two of the convolutions there take the limb form)
+    assert [form(d.conv(*s)) for s in convs].count("residue") == 6
+
+
+@pytest.mark.parametrize("shape,want", residue_tiles.MATMULS)
+def test_tiles_of_the_gpu_tests(d, shape, want):
+    log = d.matmul(*shape)
+    assert form(log) == "residue" and tiles(log) == want
+
+
+@pytest.mark.parametrize("shape,want,chunks,mid", residue_tiles.CONVS)
+def test_convolutions_of_the_gpu_tests(d, shape, want, chunks, mid):
+    log = d.conv(*shape)
+    probs = res_problems(log)
+    assert form(log) == "residue" and (want is None or tiles(log) == want)
+    if chunks is None:
+        assert all(f["ksz"] == 0 for f in probs)
+        return
+    assert all(f["ksz"] == shape[4] and f["stride"] == shape[5] for f in probs)
+    assert len({f["kb_begin"] for f in probs}) == chunks
+    assert any(f["kb_begin"] % f["kbs"] % f["ksz"] for f in probs) == mid
+
+
+@pytest.mark.parametrize("shape,want,direct", residue_tiles.DEALT)
+def test_dealt_convolutions_of_the_gpu_tests(d, shape, want, direct):
+    log = d.deal_conv(*shape)
+    assert form(log) == "residue" and tiles(log) == want and all((f["ksz"] > 0) == direct for f in res_problems(log))
