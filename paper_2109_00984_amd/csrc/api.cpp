@@ -533,15 +533,68 @@ double residue_gain_us(i64 M, i64 N, i64 K, int gemms, int outs, int segs, bool 
   const double res = gemm + packed + gemms * 34.0 * (double)M * (double)N / 4.4e6 + (grouped ? 0.0 : 6.0);
   return limb - 1.02 * res;
 }
+// k slices of a launch of `tiles` 64 x 64 tiles over `steps` k steps: what the
+// launch takes as whole rounds of two workgroups a unit (2.7 us a step) and a
+// last one, which takes less than half of that where no unit holds two of its
+// workgroups (1.2), and the slices' partial sums, written and read at 4.5 TB/s
+// by a launch more.  The 1.2 and 2.7 are a fit over 16 products, each at 1 to 8
+// slices; it picks the fastest or one within 3 % of it in all of them.  Beaver
+// matmuls, unsliced (or one workgroup a unit where that is more slices) against
+// its choice: 81 x 3157 x 4090 339 / 296 us (5), 128 x 5000 x 2000 275 / 249
+// (4), 500 x 1100 x 1000 103 / 94 (4), 515 x 515 x 4000 192 / 177 (3), 300 x
+// 4000 x 4000 678 / 650 (2), 250 x 771 x 1750 two slices of 8, 600 x 600 x 2000
+// and 400 x 1000 x 500 none.  Beyond three workgroups a unit nothing gains (600
+// x 3000 x 1500, 940 tiles: 334 / 359).
+constexpr i64 kSliceMaxWorkgroups = 3;  // a unit
+constexpr i64 kSliceLongSteps = 40, kSliceManyTiles = 40;  // issue_limb's products of different k
+struct SlicePlan {
+  i64 slices = 1;
+  double us = -1;
+};
+SlicePlan limb_slices(i64 tiles, i64 steps, i64 min_slices, i64 outs, i64 cus) {
+  SlicePlan best;
+  const i64 top = std::max(min_slices, std::min(std::max<i64>(tiles < cus ? 8 : 4, cus / tiles), steps / (i64)kLimbMinSliceSteps));
+  for (i64 s = 1; s <= top; ++s) {
+    if (s > 1 && s < min_slices) continue;
+    const i64 groups = tiles * s, last = groups % (2 * cus), n = (steps + s - 1) / s;
+    double us = (double)n * ((double)(groups / (2 * cus)) * 2.7 + (last == 0 ? 0.0 : last <= cus ? 1.2 : 2.7));
+    if (s > 1) us += 2 + (double)(outs * 16 * s) / 4.5e6;
+    if (best.us < 0 || us < best.us) best = SlicePlan{s, us};
+  }
+  return best;
+}
+
 // A convolution packed without im2col writes its activation once, not once per
-// tap, so only its k (against the combine, 18 bytes an output) and its whole
-// work (against the launches) have to be long.  Limb against residue, batch 8:
-// 250 -> 250 channels, 7 taps, 771 long 424 / 281 us; 512 -> 512, 3 taps, 398
-// long 334 / 268; 64 -> 128, 5 taps, 496 long 59 / 81; 128 -> 128, 9 taps, 992
-// long: batch 2 79 / 94, batch 4 113 / 111, batch 8 201 / 157.
+// tap, but pads its channels and, like every product of few columns, its tiles.
+// Its k (against the combine, 18 bytes an output) and its whole work (against
+// the launches) have to be long, and the residue form's time below the limb
+// form's: the limb GEMM by the rounds that limb_slices models, the residue GEMM
+// by res_plan (0.70 of it here, where its right operand stays in the L2), the
+// packs' bytes and the combine's at the rates that these fit over 426
+// convolutions of 2e8 to 2e10 multiply-adds, each forced into both forms (half of
+// them within 8 %, nine in ten within 18 %), which it has to miss by 3 %.  Limb
+// against residue, batch 8: 250 -> 250 channels, 7 taps, 771 long 424 / 281 us;
+// 512 -> 512, 3 taps, 398 long 334 / 268; 64 -> 128, 5 taps, 496 long 59 / 81; 128 ->
+// 128, 9 taps, 992 long: batch 2 79 / 94, batch 4 113 / 111, batch 8 201 / 157.  Few
+// columns: 1 x 176 x 93, 2311 channels out, 38 taps (56 of them) 303 / 668; 4 x 347 x
+// 47, 1165, 35 taps (52) 290 / 634; dealt, 4 x 454 x 99, 1628, 21 taps, stride 3
+// (108) 163 / 338.
 bool residue_pays_conv(const mpc_conv1d_shape& s, i64 N, i64 K, int gemms, int outs, int segs) {
-  if (!conv_direct(s)) return residue_gain_us(s.cout, N, K, gemms, outs, segs, false) > 0;
-  return s.cout >= 128 && K >= 1536 && (double)s.cout * (double)N * (double)K >= 1.3e9;
+  const i64 M = s.cout;
+  if (!conv_direct(s)) return residue_gain_us(M, N, K, gemms, outs, segs, false) > 0;
+  if (M < 128 || K < 1536 || (double)M * (double)N * (double)K < 1.3e9) return false;
+  const i64 tiles = gemms * ((M + 63) / 64) * ((N + 63) / 64), steps = (K + 63) / 64;
+  const double all = (double)gemms * (double)M * (double)N, weights = (double)M * (double)(K / segs);
+  double limb = 72.0 * 4096.0 * (double)tiles * (double)K / 3.1e9;
+  if (tiles < kSliceMaxWorkgroups * kPlanCUs)
+    limb = limb_slices(tiles, steps, (steps * 2 + kLimbMaxKBlocks - 1) / kLimbMaxKBlocks, gemms * M * N, kPlanCUs).us;
+  const int in = segs == 2 ? 32 : 16;  // bytes of shares read (drawn) an element
+  limb = 1.02 * limb + 25 + weights * (in + 8.0 * outs) / 7.5e6 + (double)N * (double)(K / segs) * 8.0 * outs / 3.5e6;
+  const i64 groups = (s.cin + 63) / 64, blocks = segs * groups * s.ksize, chunks = (blocks + kResMaxKBlocks - 1) / kResMaxKBlocks;
+  const double padded = (double)M * (double)(groups * 64 * s.ksize), chan = (double)s.batch * (double)(groups * 64) * (double)s.length;
+  const double res = 0.70 * res_plan(M, N, (blocks + chunks - 1) / chunks, gemms * kRes * chunks).us + 17 + padded * (in + 18.0 * outs) / 3.5e6 +
+                     chan * (in + 18.0 * outs) / 2.4e6 + all * (16 + 18.0 * (double)chunks) / 2.5e6;
+  return limb > 0.97 * res;
 }
 // The packing form of a Beaver matmul (P parties) over K k.
 Form packing_form(i64 M, i64 N, i64 K, int P = 2) {
@@ -1014,37 +1067,6 @@ std::vector<Region> limb_regions(const LimbReq& r, const TileSched& ts) {
   return limb_regions(r.M, r.N, r.cls, ts.variant, r.ep.view.ld_q == 0 && r.ep.view.n_div >= r.N);
 }
 
-// k slices of a launch of `tiles` 64 x 64 tiles over `steps` k steps: what the
-// launch takes as whole rounds of two workgroups a unit (2.7 us a step) and a
-// last one, which takes less than half of that where no unit holds two of its
-// workgroups (1.2), and the slices' partial sums, written and read at 4.5 TB/s
-// by a launch more.  The 1.2 and 2.7 are a fit over 16 products, each at 1 to 8
-// slices; it picks the fastest or one within 3 % of it in all of them.  Beaver
-// matmuls, unsliced (or one workgroup a unit where that is more slices) against
-// its choice: 81 x 3157 x 4090 339 / 296 us (5), 128 x 5000 x 2000 275 / 249
-// (4), 500 x 1100 x 1000 103 / 94 (4), 515 x 515 x 4000 192 / 177 (3), 300 x
-// 4000 x 4000 678 / 650 (2), 250 x 771 x 1750 two slices of 8, 600 x 600 x 2000
-// and 400 x 1000 x 500 none.  Beyond three workgroups a unit nothing gains (600
-// x 3000 x 1500, 940 tiles: 334 / 359).
-constexpr i64 kSliceMaxWorkgroups = 3;  // a unit
-constexpr i64 kSliceLongSteps = 40, kSliceManyTiles = 40;  // issue_limb's products of different k
-i64 limb_slices(i64 tiles, i64 steps, i64 min_slices, i64 outs, i64 cus) {
-  i64 pick = 1;
-  double best = -1;
-  const i64 top = std::max(min_slices, std::min(std::max<i64>(tiles < cus ? 8 : 4, cus / tiles), steps / (i64)kLimbMinSliceSteps));
-  for (i64 s = 1; s <= top; ++s) {
-    if (s > 1 && s < min_slices) continue;
-    const i64 groups = tiles * s, last = groups % (2 * cus), n = (steps + s - 1) / s;
-    double us = (double)n * ((double)(groups / (2 * cus)) * 2.7 + (last == 0 ? 0.0 : last <= cus ? 1.2 : 2.7));
-    if (s > 1) us += 2 + (double)(outs * 16 * s) / 4.5e6;
-    if (best < 0 || us < best) {
-      best = us;
-      pick = s;
-    }
-  }
-  return pick;
-}
-
 // The pack launches of one call: its jobs, ordered by kind and mode (the waves
 // of one workgroup then mostly run the same code), with the prefix sums of
 // their units, and the kernel for the kinds and modes among them.  One launch
@@ -1187,7 +1209,7 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
     if (alike) {
       i64 outs = 0;
       for (const LimbReq& r : reqs) outs += r.M * r.N;
-      want = limb_slices(tiles_all, (limb_kblocks(reqs[0].K0) + limb_kblocks(reqs[0].K1)) / 2, nchunks[0], outs, c->num_cu);
+      want = limb_slices(tiles_all, (limb_kblocks(reqs[0].K0) + limb_kblocks(reqs[0].K1)) / 2, nchunks[0], outs, c->num_cu).slices;
     }
     for (size_t q = 0; q < nreq; ++q) {
       const i64 steps = (limb_kblocks(reqs[q].K0) + limb_kblocks(reqs[q].K1)) / 2;

@@ -276,6 +276,16 @@ def test_residue_plan_of_convolutions(d):
     assert direct > 30
 
 
+@pytest.mark.parametrize("conv,online,dealt", [((1, 176, 93, 2311, 38, 1), "limb", "limb"), ((4, 347, 47, 1165, 35, 1), "limb", "limb"),
+                                               ((4, 454, 99, 1628, 21, 3), "limb", "limb"), ((2, 555, 218, 1217, 35, 1), "limb", "limb"),
+                                               ((16, 565, 69, 235, 40, 3), "limb", "limb"), ((8, 250, 777, 250, 7, 1), "residue", "residue"),
+                                               ((8, 250, 735, 2000, 32, 1), "residue", "residue"), ((1, 250, 777, 250, 7, 1), "limb", "limb"),
+                                               ((8, 512, 400, 512, 3, 1), "residue", "residue")])
+def test_convolutions_of_few_columns(d, conv, online, dealt):
+    """The residue form only where it is faster (2311 x 56 x 6688 took 668 us in it, 303 in the limb form)."""
+    assert form(d.conv(*conv)) == online and form(d.deal_conv(*conv)) == dealt
+
+
 # ---------------------------------------------------------------- the forms that the GPU tests of the residue form cover
 def cases(test):
     """The argument lists of a parametrised test, by its parameters' names."""
@@ -293,8 +303,8 @@ def test_forms_of_the_gpu_tests(d):
         assert form(d.party(P, 2060, 2100, 2400)) == "residue"
     assert form(d.grouped(GROUP)) == "residue+limb"
     convs = cases(residue.test_conv_matches_plain)["B,cin,L,cout,k,s"]
-    # (two of the convolutions there take the limb form)
-    assert [form(d.conv(*s)) for s in convs].count("residue") == 6
+    # (three of the convolutions there take the limb form)
+    assert [form(d.conv(*s)) for s in convs].count("residue") == 5
 
 
 @pytest.mark.parametrize("shape,want", residue_tiles.MATMULS)
@@ -307,7 +317,7 @@ def test_tiles_of_the_gpu_tests(d, shape, want):
 def test_convolutions_of_the_gpu_tests(d, shape, want, chunks, mid):
     log = d.conv(*shape)
     probs = res_problems(log)
-    assert form(log) == "residue" and (want is None or tiles(log) == want)
+    assert form(log) == "residue" and tiles(log) == want
     if chunks is None:
         assert all(f["ksz"] == 0 for f in probs)
         return
