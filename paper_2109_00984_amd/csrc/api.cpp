@@ -1103,6 +1103,8 @@ struct PackLaunch {
     else if (l.mode == kModePrgSum2) set = kPackDeal;
     else if (l.mode == kModePrgSum2A) set = kPackDealPre;
     else set = kPackRing;
+    for (const PackJob& j : jobs)
+      if (j.kind == kPackRow && j.mode == kModeSum2) set = kPackParties;
   }
   PackSet set_of(size_t L) const {
     if (starts.size() > 1 && set == kPackMatmul) return L ? kPackMatmulRight : kPackMatmulLeft;
@@ -3064,6 +3066,10 @@ mpc_status mpc_relu(mpc_ctx* c, size_t n, const uint64_t* x0, const uint64_t* x1
 
 namespace {
 
+// See mpc_mp_beaver_matmul.
+constexpr int kPartyChain = 8;
+constexpr i64 kPartyFewBlocks = 256, kPartyEagerBlocks = 48;
+
 mpc_status check_parties(int P) { return (P < 2 || P > kMaxParties) ? MPC_E_INVAL : MPC_OK; }
 
 MpKeys mp_keys(u64 seed, u64 tag, u64 base, int P) {
@@ -3281,40 +3287,66 @@ mpc_status mpc_mp_beaver_matmul(mpc_ctx* c, int P, int64_t M, int64_t N, int64_t
   CHK(check_limb_k(form, K));
   const hipStream_t st = c->s[0];
   // party p's finish z_p = c_p + [a_p + [p=0] eps | eps] @ [delta ; b_p]; the
-  // packing forms open eps (MxK) and delta (KxN) while they pack, the plain
-  // form into the workspace
+  // packing forms open eps (MxK) and delta (KxN) while they pack, the plain form
+  // into the workspace.  So does the limb form where a wave of that pack would
+  // chain many parties' blocks (1.7 us each) and leave most of the chip idle: each
+  // party's operand is then a pack job of its own, in more launches, which eager
+  // calls of very few blocks wait for.  As jobs against fused, captured / eager: 16
+  // parties' 74 x 10 x 30 (8 blocks) 24 / 38 us and 58 / 49, 237 x 3 x 191 (54) 40 /
+  // 52 and 58 / 58, 200 x 200 x 200 (112) 48 / 58 and 58 / 64, 100 x 400 x 600 (340)
+  // 73 / 73; 9 parties' 22 / 27 and 43 / 35, 30 / 36 and 43 / 43; with 8 the two are
+  // within 2 us.
+  const JobSpec spec[2] = {left_job(M, K, K), right_job(K, N, N)};
+  const i64 blocks = ((M + 31) / 32 + (N + 31) / 32) * limb_kblocks(K);
+  const bool many = P > kPartyChain && blocks <= kPartyFewBlocks;
+  const bool as_jobs = many && (c->capturing || blocks >= kPartyEagerBlocks);
+  auto opens = [&](Form f) { return !packs(f) || (f == MPC_FORM_LIMB8 && as_jobs); };
   CHK(ensure_form_ws(c, &form, want == MPC_FORM_AUTO, [&](Form f) {
-    return kAlign + (packs(f) ? (size_t)(P + 1) * (align_up(packed_bytes(M, K, f)) + align_up(packed_bytes(N, K, f)))
-                              : align_up(na * 8) + align_up(nb * 8)) +
-           (f == kFormResidue ? (size_t)P * res_out_bytes(M, N, K, K) : 0);
+    return kAlign + (packs(f) ? (size_t)(P + 1) * (align_up(packed_bytes(M, K, f)) + align_up(packed_bytes(N, K, f))) : 0) +
+           (opens(f) || many ? align_up(na * 8) + align_up(nb * 8) : 0) + (f == kFormResidue ? (size_t)P * res_out_bytes(M, N, K, K) : 0);
   }));
   Carve cv(c->ws.p);
+  u64 *eps = nullptr, *del = nullptr;
+  if (opens(form)) {
+    eps = cv.take<u64>(na);
+    del = cv.take<u64>(nb);
+    CHK(hip_status(launch_mp_open(st, xi, ai, P, na, eps)));
+    CHK(hip_status(launch_mp_open(st, yi, bi, P, nb, del)));
+    c->stats.launches += 2;
+  }
   if (packs(form)) {
     PartyPackTables pt{};
-    const JobSpec spec[2] = {left_job(M, K, K), right_job(K, N, N)};
+    std::vector<PackJob> jobs;
+    const uint8_t* dst[2][kMaxParties + 1];
     for (int side = 0; side < 2; ++side) {
       PartyPack& s = pt.side[side];
       s.job = place_job(spec[side], cv, form, 0);
       s.P = P;
-      for (int p = 0; p < P; ++p) {
-        s.x[p] = side ? yi.p[p] : xi.p[p];
-        s.a[p] = side ? bi.p[p] : ai.p[p];
+      for (int p = 0; p <= P; ++p) {
+        const u64* own = p == P ? (side ? del : eps) : side ? bi.p[p] : ai.p[p];
+        uint8_t* d = cv.take<uint8_t>(job_out_bytes(spec[side], form));
+        dst[side][p] = s.dst[p] = d;
+        if (p < P) {
+          s.x[p] = side ? yi.p[p] : xi.p[p];
+          s.a[p] = own;
+        }
+        if (!opens(form)) continue;
+        JobSpec j = spec[side];
+        if (side == 0 && p == 0) set_mode(j, kModeSum2, {own, eps});
+        else set_mode(j, kModeCopy, {own});
+        jobs.push_back(place_job(j, cv, form, 0));
+        jobs.back().dst[0] = d;
       }
-      for (int p = 0; p <= P; ++p) s.dst[p] = cv.take<uint8_t>(job_out_bytes(spec[side], form));
     }
-    CHK(hip_status(form == kFormResidue ? launch_res_pack_party(st, pt) : launch_pack_party(st, pt)));
-    c->stats.launches++;
+    if (!opens(form)) {
+      CHK(hip_status(form == kFormResidue ? launch_res_pack_party(st, pt) : launch_pack_party(st, pt)));
+      c->stats.launches++;
+    }
     std::vector<LimbReq> reqs;
     for (int p = 0; p < P; ++p)
-      reqs.push_back(limb_req(M, N, K, K, pt.side[0].dst[p], pt.side[0].dst[P], pt.side[1].dst[P], pt.side[1].dst[p],
-                              make_ep(ci.p[p], +1, 0, zo.p[p], rowmajor_view(N))));
-    CHK(issue_packed(c, form, cv, {}, reqs));
+      reqs.push_back(limb_req(M, N, K, K, dst[0][p], dst[0][P], dst[1][P], dst[1][p], make_ep(ci.p[p], +1, 0, zo.p[p], rowmajor_view(N))));
+    CHK(issue_packed(c, form, cv, jobs, reqs));
   } else {
-    u64* eps = cv.take<u64>(na);
-    u64* del = cv.take<u64>(nb);
-    CHK(hip_status(launch_mp_open(st, xi, ai, P, na, eps)));
-    CHK(hip_status(launch_mp_open(st, yi, bi, P, nb, del)));
-    c->stats.launches += 2;
     std::vector<PlainProblem> probs;
     for (int p = 0; p < P; ++p)
       probs.push_back(plain_problem(M, N, K, K, ai.p[p], p == 0 ? eps : nullptr, K, eps, K, del, nullptr, N,

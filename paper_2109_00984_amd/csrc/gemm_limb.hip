@@ -1390,6 +1390,7 @@ hipError_t launch_pack(hipStream_t s, const PackTables& t, i64 total_units, Pack
     case kPackDealPre: return launch_pack_set(s, t, total_units, SetPairs<kPackDealPre>::T{});
     case kPackDealConv: return launch_pack_set(s, t, total_units, SetPairs<kPackDealConv>::T{});
     case kPackRing: return launch_pack_set(s, t, total_units, SetPairs<kPackRing>::T{});
+    case kPackParties: return launch_pack_set(s, t, total_units, SetPairs<kPackParties>::T{});
     case kPackMatmulLeft: return launch_pack_set(s, t, total_units, SetPairs<kPackMatmulLeft>::T{});
     case kPackMatmulRight: return launch_pack_set(s, t, total_units, SetPairs<kPackMatmulRight>::T{});
     case kPackMatmulPreLeft: return launch_pack_set(s, t, total_units, SetPairs<kPackMatmulPreLeft>::T{});

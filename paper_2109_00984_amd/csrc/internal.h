@@ -332,7 +332,7 @@ struct PackTables {
 // operands in one launch, a kernel per set.
 enum PackSet : int {
   kPackMatmul, kPackMatmulPre, kPackConv, kPackConvDirect, kPackDeal, kPackDealPre, kPackDealConv, kPackDealConvDirect,
-  kPackRing,
+  kPackRing, kPackParties,
   // one side of a group's products
   kPackMatmulLeft, kPackMatmulRight, kPackMatmulPreLeft, kPackMatmulPreRight, kPackSets
 };

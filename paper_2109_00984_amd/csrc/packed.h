@@ -123,6 +123,7 @@ template <> struct SetPairs<kPackMatmulLeft> { using T = PackPairs<km(kPackRow, 
 template <> struct SetPairs<kPackMatmulRight> { using T = PackPairs<km(kPackCol, kModeOpenRight)>; };
 template <> struct SetPairs<kPackMatmulPreLeft> { using T = PackPairs<km(kPackRow, kModeOpenLeft2)>; };
 template <> struct SetPairs<kPackMatmulPreRight> { using T = PackPairs<km(kPackCol, kModeOpenRight1)>; };
+template <> struct SetPairs<kPackParties> { using T = PackPairs<km(kPackRow, kModeCopy), km(kPackRow, kModeSum2), km(kPackCol, kModeCopy)>; };
 template <> struct SetPairs<kPackRing> { using T = PackPairs<km(kPackRow, kModeCopy), km(kPackCol, kModeCopy)>; };
 
 // One block of one side of a P-party open: every party's two shares are read

@@ -55,3 +55,20 @@ def test_short_k_forms_agree(m, c, M, N, K):
     assert (z.s0 == p.s0).all() and (z.s1 == p.s1).all()
     xs, ys, tm = c.mp_share(A, 3, 0, 1), c.mp_share(B, 3, 1, 2), c.mp_dealer(3, m.TRIPLE_MATMUL, DSEED, 6, (M, N, K))
     assert (c.mp_reveal(c.mp_beaver_matmul(xs, ys, tm)) == want).all()
+
+
+@pytest.mark.parametrize("P", [8, 9, 16])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 0), (1, 1, 1), (37, 5, 65), (64, 96, 128), (33, 300, 70), (512, 480, 260), (513, 490, 260)])
+def test_many_parties(m, c, P, M, N, K):
+    """The limb form's fused open and pack, and a pack job per party where the parties are many and the blocks few."""
+    say(f"{P} parties {M}x{N}x{K}")
+    g = np.random.default_rng(P + K)
+    X, Y = (g.integers(0, 2**64, size=s, dtype=np.uint64) for s in ((M, K), (K, N)))
+    x, y = c.mp_share(dev(X), P, 0, 1), c.mp_share(dev(Y), P, P - 1, 2)
+    t = c.mp_dealer(P, m.TRIPLE_MATMUL, DSEED, 7, (M, N, K))
+    want = oracle.ring_gemm(X, Y)
+    p = c.mp_beaver_matmul(x, y, t, "plain")
+    for form in ("limb8", "auto"):
+        z = c.mp_beaver_matmul(x, y, t, form)
+        assert np.array_equal(c.mp_reveal(z).cpu().numpy().view(np.uint64), want)
+        assert all((a == b).all() for a, b in zip(z, p))

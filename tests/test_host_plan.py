@@ -330,3 +330,25 @@ def test_convolutions_of_the_gpu_tests(d, shape, want, chunks, mid):
 def test_dealt_convolutions_of_the_gpu_tests(d, shape, want, direct):
     log = d.deal_conv(*shape)
     assert form(log) == "residue" and tiles(log) == want and all((f["ksz"] > 0) == direct for f in res_problems(log))
+
+
+# ---------------------------------------------------------------- many parties
+@pytest.mark.parametrize("P,M,N,K,eager,captured", [(8, 74, 10, 30, "fused", "fused"), (9, 74, 10, 30, "fused", "jobs"), (16, 237, 3, 191, "jobs", "jobs"),
+                                                    (16, 32, 70, 100, "fused", "jobs"), (16, 100, 400, 600, "fused", "fused"), (12, 200, 200, 200, "jobs", "jobs")])
+def test_many_party_packs(P, M, N, K, eager, captured):
+    """Few blocks of many parties: a pack job per party where the launches are not waited for (16 parties' 237 x 3 x 191
+    40 us, in the fused pack's chain 52)."""
+    d = Double()
+    packs = lambda log: "fused" if "limb_pack_party" in [n for n, _ in log] else "jobs"  # noqa: E731
+    d.call("mpc_reserve", ctypes.c_size_t(1 << 20))
+    log = d.party(P, M, N, K, "limb8")
+    assert form(log) == "limb" and packs(log) == eager
+    if eager == "jobs":
+        assert [f["set"] for n, f in log if n == "limb_pack"] == [9, 9] and [n for n, _ in log].count("mp_open") == 2
+        assert sum(f["jobs"] for n, f in log if n == "limb_pack") == 2 * P + 2
+    d.call("mpc_graph_begin")  # the eager call made the workspace that this needs
+    assert packs(d.party(P, M, N, K, "limb8")) == captured
+    g = ctypes.c_void_p()
+    d.call("mpc_graph_end", ctypes.byref(g))
+    d._ok(d.lib.mpc_graph_destroy(g))
+    d.close()
