@@ -78,7 +78,7 @@ typedef enum {
  *          multiply-accumulates per party with k of at most 1024 (one launch,
  *          which PLAIN takes in the same range; beyond k of 48 also at most
  *          6 * 2^20 with the rows counted to a multiple of four, and below k of
- *          128 at most 2^14 blocks of 4 x 4 outputs unless it has at most 16
+ *          112 at most 2^14 blocks of 4 x 4 outputs unless it has at most 16
  *          rows or 8 columns).  Else LIMB8
  *          or, where each operand element enters many outputs, a residue form
  *          of its own: the product modulo

@@ -240,8 +240,9 @@ hipError_t launch_splitk_reduce_grouped(hipStream_t s, const ReduceTables& t, i6
 // 128 lanes of k and 512 threads, has most of them idle here.  This one against
 // that one: 256 x 256 x 1 5.5 / 16.2 us, 512 x 512 x 1 13.6 / 56.8, 256 x 256 x
 // 16 7.4 / 16.9, 256 x 256 x 32 10.9 / 18.3, 128 x 128 x 64 6.9 / 7.6, 128 x 128 x
-// 96 8.7 / 8.9; from 128 on the other way round (128 x 128 x 128 10.7 / 9.8, 128
-// x 128 x 192 14.2 / 11.9).
+// 96 8.7 / 8.8, 2048 x 8 x 104 9.1 / 8.7; over 18 shapes even at k of 112, where
+// its lanes' loops of eight begin to diverge (14 x 649 x 120 8.5 / 7.7, x 127 10.8 /
+// 7.8), and behind from there on (128 x 128 x 128 10.7 / 9.8, x 192 14.2 / 11.9).
 constexpr int kShortSide = 4, kShortOut = kShortSide * kShortSide, kShortKl = kThreads / kShortOut;
 
 __global__ void __launch_bounds__(kThreads) k_beaver_matmul_short(SmallMatmul s) {

@@ -265,7 +265,7 @@ struct SmallMatmul {
 // plain form and 16.5 in the limb form, 1024 x 1024 x 1 49 / 19 / 23, 32 x 32768
 // x 1 47 / 41 / 31, 100000 x 16 x 1 75 / 61 / 72, but 16 x 100000 x 1 77 / 99 / 71,
 // 200000 x 4 x 1 39 / 98 / 148, 262144 x 1 x 1 51 / 109 / 201.
-constexpr i64 kSmallMatmulMacs = (i64)3 << 20, kSmallMatmulK = 1024, kSmallMatmulShortK = 128;
+constexpr i64 kSmallMatmulMacs = (i64)3 << 20, kSmallMatmulK = 1024, kSmallMatmulShortK = 112;
 constexpr i64 kSmallMatmulSide = 4;  // a workgroup's block of outputs is 4 x 4
 inline i64 small_matmul_groups(i64 M, i64 N) {
   return ((M + kSmallMatmulSide - 1) / kSmallMatmulSide) * ((N + kSmallMatmulSide - 1) / kSmallMatmulSide);

@@ -24,7 +24,7 @@ def c(m):
     ctx.close()
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 1, 0), (1, 1, 1), (5, 7, 1), (4, 4, 15), (3, 5, 16), (9, 6, 17), (33, 30, 126), (64, 48, 127), (61, 47, 128),
+@pytest.mark.parametrize("M,N,K", [(1, 1, 0), (1, 1, 1), (5, 7, 1), (4, 4, 15), (3, 5, 16), (9, 6, 17), (33, 30, 111), (21, 34, 112), (33, 30, 126), (64, 48, 127), (61, 47, 128),
                                    (17, 19, 129), (5, 3, 255), (6, 9, 256), (7, 2, 257), (512, 511, 1), (513, 512, 1), (300, 700, 3), (1, 9000, 17),
                                    (9001, 1, 16), (16, 4099, 5), (1, 2000, 49), (2, 3, 1023), (3, 2, 1024)])
 @pytest.mark.parametrize("form", ["auto", "plain"])
