@@ -546,7 +546,6 @@ double residue_gain_us(i64 M, i64 N, i64 K, int gemms, int outs, int segs, bool 
 // and 400 x 1000 x 500 none.  Beyond three workgroups a unit nothing gains (600
 // x 3000 x 1500, 940 tiles: 334 / 359).
 constexpr i64 kSliceMaxWorkgroups = 3;  // a unit
-constexpr i64 kSliceLongSteps = 40, kSliceManyTiles = 40;  // issue_limb's products of different k
 struct SlicePlan {
   i64 slices = 1;
   double us = -1;
@@ -564,6 +563,43 @@ SlicePlan limb_slices(i64 tiles, i64 steps, i64 min_slices, i64 outs, i64 cus) {
   return best;
 }
 
+// Most k slices of a product in a launch over products of different k, fewer
+// than a tile a unit in all.  The launch takes as long as the longest slice, or
+// the whole work at two workgroups a unit (2.4 us a step, 1.2 where no unit holds
+// two; two steps a workgroup for its start and its end), and part of the shorter
+// of the two, as the long slices come first but not last; the slices' partial sums
+// by a launch more.  A fit over 322 random groups, each with six counts: its choice
+// is on average 0.8 % from the fastest of the six, at worst 12 %, where one
+// workgroup a unit, whatever the lengths, was 3 % and up to 40 %.  One a unit
+// against its choice: 12 products of up to 274 x 96 x 3957 223 / 184 us, of 16 x
+// 1129 x 5602 633 / 531, 17 x 490 x 3533 among five of a tenth of it 62 / 54, 1011 x
+// 252 x 435 and another 35 / 35.
+struct SliceWork {
+  i64 tiles, steps, min_slices, outs;
+};
+i64 uneven_slices(const std::vector<SliceWork>& work, i64 cus) {
+  i64 pick = 1;
+  double best = -1;
+  for (i64 want : {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32}) {
+    i64 groups = 0, total = 0, longest = 0;
+    double sums = 0;
+    for (const SliceWork& w : work) {
+      const i64 s = std::max(w.min_slices, std::max<i64>(1, std::min(want, w.steps / (i64)kLimbMinSliceSteps)));
+      const i64 len = (w.steps + s - 1) / s + 2;
+      groups += w.tiles * s;
+      total += w.tiles * s * len;
+      longest = std::max(longest, len);
+      if (s > 1) sums += (double)(w.outs * 16 * s) / 4.5e6;
+    }
+    const double one = (double)longest * (groups <= cus ? 1.2 : 2.4), all = (double)total * 2.4 / (2.0 * (double)cus);
+    const double us = std::max(one, all) + 0.4 * std::min(one, all) + sums + (sums > 0 ? 2 : 0);
+    if (best < 0 || us < best) {
+      best = us;
+      pick = want;
+    }
+  }
+  return pick;
+}
 // A convolution packed without im2col writes its activation once, not once per
 // tap, but pads its channels and, like every product of few columns, its tiles.
 // Its k (against the combine, 18 bytes an output) and its whole work (against
@@ -1190,32 +1226,29 @@ mpc_status issue_limb(mpc_ctx* c, const std::vector<PackJob>& jobs_in, const std
   size_t part_bytes = 0;
   // the default tiles, two workgroups a unit, over one k length
   bool alike = true, uneven = false;
-  i64 longest = 0;
+  auto steps_of = [&](size_t q) { return (limb_kblocks(reqs[q].K0) + limb_kblocks(reqs[q].K1)) / 2; };
   for (size_t q = 0; q < nreq; ++q) {
     const int v = sched_of(q).variant;
     uneven = uneven || reqs[q].K0 != reqs[0].K0 || reqs[q].K1 != reqs[0].K1;
     alike = alike && (v == kLimbLds64x64 || v == kLimbClasses);
-    longest = std::max(longest, (limb_kblocks(reqs[q].K0) + limb_kblocks(reqs[q].K1)) / 2);
   }
   alike = alike && !uneven;
   if (!no_alloc && tiles_all > 0 && tiles_all < (alike ? kSliceMaxWorkgroups : 1) * c->num_cu) {
     // As many slices as give every unit one workgroup, or what the model of
-    // the default tiles' rounds says.  Two a unit where the products' k differ,
-    // one of them is long and the tiles are many: so few slices would leave the
-    // longest one's to the end (12 products of up to 274 x 96 x 3957, 114 tiles,
-    // 224 us with one a unit, 188 with two; of 16 x 1129 x 5602, 244 tiles, 632 /
-    // 556; but of 1011 x 252 x 435, 180 tiles of 12 k steps, 35 / 45, and 6 of 1 x 4
-    // x 6724, 12 tiles, 40 / 44).
+    // the default tiles' rounds says; of products of different k, uneven_slices.
     i64 want = c->num_cu / tiles_all;
-    if (uneven && longest >= kSliceLongSteps && tiles_all >= kSliceManyTiles) want = (2 * c->num_cu + tiles_all - 1) / tiles_all;
+    if (uneven) {
+      std::vector<SliceWork> work(nreq);
+      for (size_t q = 0; q < nreq; ++q) work[q] = {tiles_of(q), steps_of(q), nchunks[q], reqs[q].M * reqs[q].N};
+      want = uneven_slices(work, c->num_cu);
+    }
     if (alike) {
       i64 outs = 0;
       for (const LimbReq& r : reqs) outs += r.M * r.N;
-      want = limb_slices(tiles_all, (limb_kblocks(reqs[0].K0) + limb_kblocks(reqs[0].K1)) / 2, nchunks[0], outs, c->num_cu).slices;
+      want = limb_slices(tiles_all, steps_of(0), nchunks[0], outs, c->num_cu).slices;
     }
     for (size_t q = 0; q < nreq; ++q) {
-      const i64 steps = (limb_kblocks(reqs[q].K0) + limb_kblocks(reqs[q].K1)) / 2;
-      const i64 sl = std::max<i64>(nchunks[q], std::min<i64>(want, steps / kLimbMinSliceSteps));
+      const i64 sl = std::max<i64>(nchunks[q], std::min<i64>(want, steps_of(q) / kLimbMinSliceSteps));
       if (sl > 1 && (want > 1 || tiles_all < c->num_cu)) {
         nslices[q] = (int)sl;
         part_bytes += align_up((size_t)(sl * reqs[q].M * reqs[q].N) * 8);

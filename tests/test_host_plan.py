@@ -187,19 +187,14 @@ def test_every_finish_is_counted_and_timed(d, M, N, K, f):
 
 
 # ---------------------------------------------------------------- k slices
-def slices(log):
-    return [f["slices"] for n, f in log if n == "limb_problem"]
-
-
-@pytest.mark.parametrize("shapes,per_unit", [([(250, 90, 4000 - 200 * i) for i in range(8)], 2),      # 128 tiles, up to 126 k steps
-                                             ([(250, 90, 1200 - 50 * i) for i in range(8)], 1),       # up to 38
-                                             ([(60, 64, 4000 - 200 * i) for i in range(8)], 1)])      # 16 tiles
-def test_slices_of_uneven_groups(d, shapes, per_unit):
-    """Long products of different k in a launch of many tiles: slices for two workgroups a unit, otherwise one."""
-    log = d.grouped(shapes, "limb8")
-    groups = 2 * sum(-(-M // 64) * -(-N // 64) for M, N, _ in shapes)
-    want = -(-512 // groups) if per_unit == 2 else 256 // groups
-    assert max(slices(log)) == min(want, max(2 * -(-K // 64) for _, _, K in shapes) // 4), log
+@pytest.mark.parametrize("shapes,want", [([(250, 90, 4000 - 200 * i) for i in range(8)], {(250, 90): 6}),  # 128 tiles of up to 126 k steps: one a unit is 2
+                                         ([(250, 90, 1200 - 50 * i) for i in range(8)], {(250, 90): 2}), ([(60, 64, 4000 - 200 * i) for i in range(8)], {(60, 64): 16}),
+                                         ([(27, 159, 312), (64, 17, 422), (286, 23, 278), (17, 490, 3533), (165, 84, 45), (24, 181, 1511)],
+                                          {(17, 490): 20, (24, 181): 12, (64, 17): 3, (27, 159): 2, (286, 23): 2, (165, 64): 1})])
+def test_slices_of_uneven_groups(d, shapes, want):
+    """Products of different k: the longest one's slices do not end long after the rest."""
+    got = {(f["M"], f["N"]): f["slices"] for n, f in d.grouped(shapes, "limb8") if n == "limb_problem"}
+    assert {k: got[k] for k in want} == want
 
 
 # ---------------------------------------------------------------- the residue form's plan
