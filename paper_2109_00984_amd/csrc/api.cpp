@@ -431,8 +431,8 @@ i64 conv_lout(const mpc_conv1d_shape& s) {
 }
 
 // Whether the residue form takes a convolution without im2col (ResConv):
-// channels padded to 64 add at
-// most a quarter to k, and 32-bit offsets reach a whole plane.
+// channels padded to 64 add at most a quarter to k, and 32-bit offsets reach a
+// whole plane.
 bool conv_direct(const mpc_conv1d_shape& s) {
   const i64 groups = (s.cin + 63) / 64;
   return groups * 64 * 4 <= s.cin * 5 && groups * s.ksize <= kResMaxSegK / 64 && s.batch * groups * s.length <= (i64)1 << 24 &&
@@ -600,6 +600,7 @@ i64 uneven_slices(const std::vector<SliceWork>& work, i64 cus) {
   }
   return pick;
 }
+
 // A convolution packed without im2col writes its activation once, not once per
 // tap, but pads its channels and, like every product of few columns, its tiles.
 // Its k (against the combine, 18 bytes an output) and its whole work (against

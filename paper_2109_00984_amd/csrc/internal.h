@@ -244,8 +244,6 @@ hipError_t launch_im2col(hipStream_t s, const u64* x, const u64* add, i64 B, i64
 // out = x + y
 hipError_t launch_add(hipStream_t s, const u64* x, const u64* y, size_t n, u64* out);
 
-// Plain ring GEMM (gemm_plain.hip): one launch over all problems of `probs`
-// (a device array), tiles listed by `map`.
 // A whole two-party Beaver matmul of a small product (plain arithmetic) in
 // one launch: operands, triple shares and outputs as in mpc_beaver_matmul.
 struct SmallMatmul {
@@ -284,6 +282,8 @@ inline bool small_matmul_auto(i64 M, i64 N, i64 K) {
   return small_matmul(M, N, K) && (K <= 48 || (M + 3) / 4 * 4 * N * K <= 2 * kSmallMatmulMacs);
 }
 hipError_t launch_beaver_matmul_small(hipStream_t s, const SmallMatmul& m);
+// Plain ring GEMM (gemm_plain.hip): one launch over all problems of `probs`
+// (a device array), tiles listed by `map`.
 hipError_t launch_plain_gemm(hipStream_t s, const PlainProblem* probs, TileMap map,
                              int total_tiles);
 int plain_tiles(i64 M, i64 N);
